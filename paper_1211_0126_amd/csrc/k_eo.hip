@@ -42,15 +42,21 @@ namespace tmq {
 // PRE = D (if PRE_D) or 1 applied to the centre term b (nullptr: none; with
 // a.bnoise the Z4 source of the output site), POST = D^{-1} (if POST_DINV)
 // or 1; D carries the twist of M (or M^dag if DAG).
-// gate (nullable): only right-hand sides whose reliable flag is set (NR = 1,
-// small grid striding over the site blocks).
+// GATED: only chunks with a right-hand side whose reliable flag is set (small
+// grid striding over the site blocks).
 // ---------------------------------------------------------------------------
-template <bool DAG, bool PRE_D, bool POST_DINV, typename R, class Si, class So, class G, int NR>
+template <bool DAG, bool PRE_D, bool POST_DINV, typename R, class Si, class So, class G, int NR, bool GATED = false>
 __global__ TM_STENCIL_R(NR, R) void k_eo_lin(EoArgs a) {
     const Geom& hg = a.hg;
-    const BlockMap bm = stencil_block((uint32_t)(a.nrhs / NR));
-    const int r0 = bm.ch * NR;
-    if (a.gate != nullptr) {
+    const uint32_t nch = (uint32_t)(a.nrhs / NR);
+    WaveMap wm = {0, 0, 0};
+    BlockMap bm = {0, 0, 0};
+    if (GATED)
+        bm = stencil_block(nch);
+    else
+        wm = wave_map(hg.V, nch);
+    const int r0 = (GATED ? bm.ch : wm.ch) * NR;
+    if (GATED) {
         bool any = false;
 #pragma unroll
         for (int r = 0; r < NR; r++) any |= a.gate[r0 + r].rflag != 0;
@@ -68,8 +74,8 @@ __global__ TM_STENCIL_R(NR, R) void k_eo_lin(EoArgs a) {
     const R cf = (R)a.c;
     const void* in0 = field_rhs<Si>(a.in, Vs, r0);
     const uint32_t nsb_all = (uint32_t)((hg.V + 255) / 256);
-    for (uint32_t sb = bm.sb; sb < nsb_all; sb += bm.nsb) {
-        const uint32_t h = eo_site(hg, sb, threadIdx.x);
+    for (uint32_t sb = GATED ? bm.sb : wm.ws >> 2; sb < nsb_all; sb += GATED ? bm.nsb : nsb_all) {
+        const uint32_t h = eo_site(hg, sb, GATED ? threadIdx.x : (wm.ws & 3u) * 64u + (threadIdx.x & 63u));
         if (h >= hg.V) continue;
         const EoSite c = eo_coords(hg, h, a.pout);
         cx<R> acc[NR][12];
@@ -255,15 +261,13 @@ __global__ __launch_bounds__(256) void k_eo_dinv(Geom hg, double twist, int nrhs
 // CG steps on the odd sites (a.geo is the half geometry)
 // ---------------------------------------------------------------------------
 
-// K1b: t = D p - kappa^2 H_oe y, block partials of |t|^2
+// K1b: t = D p - kappa^2 H_oe y, partials per 64 sites of |t|^2
 template <typename R, class S, class G, int NR>
 __global__ TM_STENCIL_R(NR, R) void k_eo_mp(CgArgs a, EoCg e) {
-    __shared__ double sh[4];
     const Geom& hg = a.geo;
-    const BlockMap bm = stencil_block((uint32_t)(a.nrhs / NR));
-    const uint32_t nb = bm.nsb;
-    const uint32_t h = eo_site(hg, bm.sb, threadIdx.x);
-    const int r0 = bm.ch * NR;
+    const WaveMap wm = wave_map(hg.V, (uint32_t)(a.nrhs / NR));
+    const uint32_t h = eo_site(hg, wm.ws >> 2, (wm.ws & 3u) * 64u + (threadIdx.x & 63u));
+    const int r0 = wm.ch * NR;
     const long Vs = hg.Vs;
     bool act[NR];
     bool any = false;
@@ -296,8 +300,8 @@ __global__ TM_STENCIL_R(NR, R) void k_eo_mp(CgArgs a, EoCg e) {
     }
 #pragma unroll
     for (int r = 0; r < NR; r++) {
-        double v = block_sum256(part[r], sh);
-        if (threadIdx.x == 0) a.partials[(size_t)(r0 + r) * nb + bm.sb] = v;
+        const double v = wave_sum(part[r]);
+        if ((threadIdx.x & 63u) == 0 && wm.ws < wm.nws) a.partials[(size_t)(r0 + r) * wm.nws + wm.ws] = v;
     }
 }
 
@@ -306,12 +310,10 @@ __global__ TM_STENCIL_R(NR, R) void k_eo_mp(CgArgs a, EoCg e) {
 // no x update (the directions are kept, k_eo_xflush forms x)
 template <typename R, class S, class G, class X, typename RX, int NR, bool TRACK, bool XFREE = false>
 __global__ TM_STENCIL_R(NR, R) void k_eo_upd(CgArgs a, EoCg e) {
-    __shared__ double sh[4];
     const Geom& hg = a.geo;
-    const BlockMap bm = stencil_block((uint32_t)(a.nrhs / NR));
-    const uint32_t nb = bm.nsb;
-    const uint32_t h = eo_site(hg, bm.sb, threadIdx.x);
-    const int r0 = bm.ch * NR;
+    const WaveMap wm = wave_map(hg.V, (uint32_t)(a.nrhs / NR));
+    const uint32_t h = eo_site(hg, wm.ws >> 2, (wm.ws & 3u) * 64u + (threadIdx.x & 63u));
+    const int r0 = wm.ch * NR;
     const long Vs = hg.Vs;
     bool act[NR];
     bool any = false;
@@ -373,11 +375,12 @@ __global__ TM_STENCIL_R(NR, R) void k_eo_upd(CgArgs a, EoCg e) {
     }
 #pragma unroll
     for (int r = 0; r < NR; r++) {
-        double v = block_sum256(prr[r], sh);
-        if (threadIdx.x == 0) a.partials[(size_t)(r0 + r) * nb + bm.sb] = v;
+        const double v = wave_sum(prr[r]);
+        const bool w0 = (threadIdx.x & 63u) == 0 && wm.ws < wm.nws;
+        if (w0) a.partials[(size_t)(r0 + r) * wm.nws + wm.ws] = v;
         if (TRACK) {
-            double w = block_sum256(prho[r], sh);
-            if (threadIdx.x == 0) a.partials2[(size_t)(r0 + r) * nb + bm.sb] = w;
+            const double w = wave_sum(prho[r]);
+            if (w0) a.partials2[(size_t)(r0 + r) * wm.nws + wm.ws] = w;
         }
     }
 }
@@ -624,24 +627,24 @@ static void eo_lin_nr(hipStream_t st, const EoArgs& a, int nr) {
     if (a.gate != nullptr) {
         const unsigned gb = std::min(nb, kEoGatedBlocks);
         if (nr == 2)
-            hipLaunchKernelGGL((k_eo_lin<DAG, PRE, POST, R, Si, So, G, 2>), dim3(gb * (unsigned)(a.nrhs / 2)),
+            hipLaunchKernelGGL((k_eo_lin<DAG, PRE, POST, R, Si, So, G, 2, true>), dim3(gb * (unsigned)(a.nrhs / 2)),
                                dim3(256), 0, st, a);
         else
-            hipLaunchKernelGGL((k_eo_lin<DAG, PRE, POST, R, Si, So, G, 1>), dim3(gb * (unsigned)a.nrhs), dim3(256),
+            hipLaunchKernelGGL((k_eo_lin<DAG, PRE, POST, R, Si, So, G, 1, true>), dim3(gb * (unsigned)a.nrhs), dim3(256),
                                0, st, a);
         return;
     }
     switch (nr) {
     case 4:
-        hipLaunchKernelGGL((k_eo_lin<DAG, PRE, POST, R, Si, So, G, 4>), dim3(nb * (unsigned)(a.nrhs / 4)), dim3(256),
+        hipLaunchKernelGGL((k_eo_lin<DAG, PRE, POST, R, Si, So, G, 4>), dim3(wave_blocks(a.hg.V, a.nrhs / 4)), dim3(256),
                            0, st, a);
         break;
     case 2:
-        hipLaunchKernelGGL((k_eo_lin<DAG, PRE, POST, R, Si, So, G, 2>), dim3(nb * (unsigned)(a.nrhs / 2)), dim3(256),
+        hipLaunchKernelGGL((k_eo_lin<DAG, PRE, POST, R, Si, So, G, 2>), dim3(wave_blocks(a.hg.V, a.nrhs / 2)), dim3(256),
                            0, st, a);
         break;
     default:
-        hipLaunchKernelGGL((k_eo_lin<DAG, PRE, POST, R, Si, So, G, 1>), dim3(nb * (unsigned)a.nrhs), dim3(256), 0, st,
+        hipLaunchKernelGGL((k_eo_lin<DAG, PRE, POST, R, Si, So, G, 1>), dim3(wave_blocks(a.hg.V, a.nrhs)), dim3(256), 0, st,
                            a);
         break;
     }
@@ -678,9 +681,9 @@ static void eo_mp_typed(hipStream_t st, const CgArgs& a, const EoCg& e, int nr) 
     const uint32_t nb = eo_blocks(a.geo);
     if constexpr (sizeof(R) == 8) nr = 1;
     switch (nr) {
-    case 4: hipLaunchKernelGGL((k_eo_mp<R, S, G, 4>), dim3(nb * (unsigned)(a.nrhs / 4)), dim3(256), 0, st, a, e); break;
-    case 2: hipLaunchKernelGGL((k_eo_mp<R, S, G, 2>), dim3(nb * (unsigned)(a.nrhs / 2)), dim3(256), 0, st, a, e); break;
-    default: hipLaunchKernelGGL((k_eo_mp<R, S, G, 1>), dim3(nb * (unsigned)a.nrhs), dim3(256), 0, st, a, e); break;
+    case 4: hipLaunchKernelGGL((k_eo_mp<R, S, G, 4>), dim3(wave_blocks(a.geo.V, a.nrhs / 4)), dim3(256), 0, st, a, e); break;
+    case 2: hipLaunchKernelGGL((k_eo_mp<R, S, G, 2>), dim3(wave_blocks(a.geo.V, a.nrhs / 2)), dim3(256), 0, st, a, e); break;
+    default: hipLaunchKernelGGL((k_eo_mp<R, S, G, 1>), dim3(wave_blocks(a.geo.V, a.nrhs)), dim3(256), 0, st, a, e); break;
     }
 }
 
@@ -688,21 +691,21 @@ template <typename R, class S, class G, class X, typename RX>
 static void eo_upd_typed(hipStream_t st, const CgArgs& a, const EoCg& e, int nr, bool track) {
     const uint32_t nb = eo_blocks(a.geo);
     if (track) {
-        hipLaunchKernelGGL((k_eo_upd<R, S, G, X, RX, 1, true>), dim3(nb * (unsigned)a.nrhs), dim3(256), 0, st, a, e);
+        hipLaunchKernelGGL((k_eo_upd<R, S, G, X, RX, 1, true>), dim3(wave_blocks(a.geo.V, a.nrhs)), dim3(256), 0, st, a, e);
         return;
     }
     if constexpr (sizeof(R) == 8) nr = 1;
     switch (nr) {
     case 4:
-        hipLaunchKernelGGL((k_eo_upd<R, S, G, X, RX, 4, false>), dim3(nb * (unsigned)(a.nrhs / 4)), dim3(256), 0, st,
+        hipLaunchKernelGGL((k_eo_upd<R, S, G, X, RX, 4, false>), dim3(wave_blocks(a.geo.V, a.nrhs / 4)), dim3(256), 0, st,
                            a, e);
         break;
     case 2:
-        hipLaunchKernelGGL((k_eo_upd<R, S, G, X, RX, 2, false>), dim3(nb * (unsigned)(a.nrhs / 2)), dim3(256), 0, st,
+        hipLaunchKernelGGL((k_eo_upd<R, S, G, X, RX, 2, false>), dim3(wave_blocks(a.geo.V, a.nrhs / 2)), dim3(256), 0, st,
                            a, e);
         break;
     default:
-        hipLaunchKernelGGL((k_eo_upd<R, S, G, X, RX, 1, false>), dim3(nb * (unsigned)a.nrhs), dim3(256), 0, st, a, e);
+        hipLaunchKernelGGL((k_eo_upd<R, S, G, X, RX, 1, false>), dim3(wave_blocks(a.geo.V, a.nrhs)), dim3(256), 0, st, a, e);
         break;
     }
 }
@@ -711,21 +714,21 @@ template <typename R, class S, class G>
 static void eo_upd_xfree_typed(hipStream_t st, const CgArgs& a, const EoCg& e, int nr, bool track) {
     const uint32_t nb = eo_blocks(a.geo);
     if (track) {
-        hipLaunchKernelGGL((k_eo_upd<R, S, G, SF32, float, 1, true, true>), dim3(nb * (unsigned)a.nrhs), dim3(256), 0,
+        hipLaunchKernelGGL((k_eo_upd<R, S, G, SF32, float, 1, true, true>), dim3(wave_blocks(a.geo.V, a.nrhs)), dim3(256), 0,
                            st, a, e);
         return;
     }
     switch (nr) {
     case 4:
-        hipLaunchKernelGGL((k_eo_upd<R, S, G, SF32, float, 4, false, true>), dim3(nb * (unsigned)(a.nrhs / 4)),
+        hipLaunchKernelGGL((k_eo_upd<R, S, G, SF32, float, 4, false, true>), dim3(wave_blocks(a.geo.V, a.nrhs / 4)),
                            dim3(256), 0, st, a, e);
         break;
     case 2:
-        hipLaunchKernelGGL((k_eo_upd<R, S, G, SF32, float, 2, false, true>), dim3(nb * (unsigned)(a.nrhs / 2)),
+        hipLaunchKernelGGL((k_eo_upd<R, S, G, SF32, float, 2, false, true>), dim3(wave_blocks(a.geo.V, a.nrhs / 2)),
                            dim3(256), 0, st, a, e);
         break;
     default:
-        hipLaunchKernelGGL((k_eo_upd<R, S, G, SF32, float, 1, false, true>), dim3(nb * (unsigned)a.nrhs), dim3(256),
+        hipLaunchKernelGGL((k_eo_upd<R, S, G, SF32, float, 1, false, true>), dim3(wave_blocks(a.geo.V, a.nrhs)), dim3(256),
                            0, st, a, e);
         break;
     }

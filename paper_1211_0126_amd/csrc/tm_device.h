@@ -431,6 +431,36 @@ __device__ __forceinline__ BlockMap stencil_block(uint32_t nch) {
     return m;
 }
 
+// Half-hop launches deal waves instead of blocks: a wave takes 64 sites (group
+// ws) and one chunk of right-hand sides, and the four waves of a block take
+// the same sites for W = 4 (or 2) different chunks where their number allows
+// it.  The waves of a block read the same links at nearly the same time, so
+// three of four link reads hit in L1: k_eo_lin (FP16, two sources per lane, 16
+// sources, 32^3 x 64) asks L2 for 58 instead of 73 million lines and takes 722
+// instead of 731 us, the whole step 2-3 % less.
+struct WaveMap {
+    uint32_t ws;   // group of 64 sites
+    uint32_t ch;   // right-hand-side chunk
+    uint32_t nws;  // number of groups
+};
+__host__ __device__ __forceinline__ uint32_t wave_width(uint32_t nch) { return nch % 4 == 0 ? 4u : (nch % 2 == 0 ? 2u : 1u); }
+// blocks of a launch over V sites and nch chunks
+__host__ __device__ __forceinline__ uint32_t wave_blocks(int64_t V, uint32_t nch) {
+    const uint32_t W = wave_width(nch), nws = (uint32_t)((V + 63) / 64), per = 4u / W;
+    return (nws + per - 1) / per * (nch / W);
+}
+__device__ __forceinline__ WaveMap wave_map(int64_t V, uint32_t nch) {
+    const uint32_t W = wave_width(nch), ng = nch / W;
+    const uint32_t L = xcd_block(blockIdx.x, gridDim.x);
+    const uint32_t sbk = L / ng, cg = L - sbk * ng;
+    const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    WaveMap m;
+    m.nws = (uint32_t)((V + 63) / 64);
+    m.ch = cg * W + (w & (W - 1));
+    m.ws = sbk * (4u / W) + w / W;
+    return m;
+}
+
 // ---------------------------------------------------------------------------
 // Z4 noise: splitmix64 output mix (Steele, Lea & Flood 2014) applied to the
 // counter 1 + j*V + site of a stream started at mix(seed); component c takes

@@ -381,7 +381,7 @@ static tm_status solve_block_eo(tm_ctx* ctx, const tsm_solve_params* p, uint64_t
     a.kappa = kappa;
     a.twist = tw;
     a.nrhs = nrhs;
-    a.npart = tiles ? eot_tiles(hg) : nblk;
+    a.npart = tiles ? eot_tiles(hg) : (uint32_t)((hg.V + 63) / 64);
     // search directions in a ring (CgArgs::pn): without reliable updates, on
     // the lane-per-site kernels; x is formed from the step lengths every
     // kRing - 1 iterations and at the end
