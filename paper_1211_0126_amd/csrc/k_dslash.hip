@@ -45,7 +45,7 @@ __global__ TM_STENCIL_R(NR, R) void k_apply(Geom geo, const void* gauge, R kappa
     // gated launches use a small grid that strides over the site blocks
     const uint32_t nsb_all = (uint32_t)((geo.V + 255) / 256);
     for (uint32_t sb = bm.sb; sb < nsb_all; sb += bm.nsb) {
-        const uint32_t s = sb * 256u + threadIdx.x;
+        const uint32_t s = slab_order(geo, sb * 256u + threadIdx.x);
         if (s >= geo.V) continue;
         const Site c = site_coords(geo, s);
         cx<R> acc[NR][12];
@@ -115,7 +115,7 @@ __global__ TM_STENCIL_R(NR, R) void k_cg_mp(CgArgs a) {
     __shared__ double sh[4];
     const BlockMap bm = stencil_block((uint32_t)(a.nrhs / NR));
     const uint32_t nb = bm.nsb;
-    const uint32_t s = bm.sb * 256u + threadIdx.x;
+    const uint32_t s = slab_order(a.geo, bm.sb * 256u + threadIdx.x);
     const int r0 = bm.ch * NR;
     const long Vs = a.geo.Vs;
     bool act[NR];
@@ -193,7 +193,7 @@ __global__ TM_STENCIL_R(NR, R) void k_cg_upd(CgArgs a) {
     __shared__ double sh[4];
     const BlockMap bm = stencil_block((uint32_t)(a.nrhs / NR));
     const uint32_t nb = bm.nsb;
-    const uint32_t s = bm.sb * 256u + threadIdx.x;
+    const uint32_t s = slab_order(a.geo, bm.sb * 256u + threadIdx.x);
     const int r0 = bm.ch * NR;
     const long Vs = a.geo.Vs;
     bool act[NR];
@@ -489,7 +489,7 @@ __global__ TM_STENCIL_R(1, double) void k_true_resid(CgArgs a, const void* gauge
     __shared__ double sh[4];
     const BlockMap bm = stencil_block((uint32_t)a.nrhs);
     const uint32_t nb = bm.nsb;
-    const uint32_t s = bm.sb * 256u + threadIdx.x;
+    const uint32_t s = slab_order(a.geo, bm.sb * 256u + threadIdx.x);
     const int r = bm.ch;
     const long Vs = a.geo.Vs;
     double pr = 0, pe = 0;

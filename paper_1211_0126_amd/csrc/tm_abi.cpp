@@ -319,6 +319,33 @@ bool geom_setup(const tm_lattice* lat, Geom* gp, Geom* hp, bool* eo_ok, std::str
         else
             h.m[0] = (uint32_t)m;
     }
+    // slab order of the sites: slabs of the bz planes (bz divides Lz) whose
+    // time slice comes closest to 900 sites of the half or 1800 of the whole
+    // lattice.  At 24^3 x 48 (288 half sites a plane), 32 FP16 LP solves take
+    // 19.1 ms in the natural order and 19.1, 18.2, 18.5, 18.3, 18.7 ms with bz
+    // = 2, 3, 4, 6, 8; two FP64 applications of M 2.31 ms and 2.17, 2.13,
+    // 2.15, 2.14, 2.19 ms.
+    auto set_slab = [](Geom& q, double target) {
+        q.slab = q.slab_m = 0;
+        const double plane = (double)(q.V / ((long)q.L[2] * q.L[3]));
+        uint64_t S = 0;
+        double best = 1e300;
+        for (int bz = 1; bz <= q.L[2]; bz++) {
+            const double d = std::fabs(std::log(plane * bz / target));
+            if (q.L[2] % bz == 0 && d < best) {
+                best = d;
+                S = (uint64_t)plane * bz;
+            }
+        }
+        // exact division of every site index by S
+        const uint64_t m = S > 1 ? ((1ULL << 32) + S - 1) / S : 0;
+        if (S > 1 && (uint64_t)q.V * (m * S - (1ULL << 32)) < (1ULL << 32)) {
+            q.slab = (uint32_t)S;
+            q.slab_m = (uint32_t)m;
+        }
+    };
+    set_slab(g, 1800.0);
+    if (*eo_ok) set_slab(h, 900.0);
 #ifndef TM_EO_NATURAL
     // brick order of the half-lattice site blocks: a wave is 64 / (Lx/2)
     // whole rows, a block four z planes of them

@@ -403,6 +403,21 @@ __device__ __forceinline__ uint32_t nb_bwd(const Geom& g, uint32_t s, const Site
     }
 }
 
+// Site visited n-th in the slab order: the lattice is cut into slabs of a few
+// z planes, and each slab is swept through all time slices before the next
+// one.  The planes of one time slice that a sweep has just used as its
+// forward time neighbours are then still in the XCD's L2 when they are the
+// backward ones; in the natural order a whole time slice (larger than L2 on
+// any lattice that fills the chip) lies between the two.  Consecutive n stay
+// consecutive sites within a chunk of `slab` sites, so a wave reads the same
+// runs of memory.  Any n >= V is returned as it is.
+__device__ __forceinline__ uint32_t slab_order(const Geom& g, uint32_t n) {
+    if (g.slab == 0 || n >= (uint32_t)g.V) return n;
+    const uint32_t c = fdiv(n, g.slab_m), off = n - c * g.slab;
+    const uint32_t Lt = (uint32_t)g.L[3], k = c / Lt, t = c - k * Lt;
+    return off + g.slab * k + (uint32_t)g.V / Lt * t;
+}
+
 // Blocks are dealt round-robin to the 8 XCDs; remap so that each XCD works
 // on one contiguous range of the lattice (its neighbours then sit in that
 // XCD's L2).

@@ -34,8 +34,8 @@ __device__ __forceinline__ EoSite eo_coords(const Geom& hg, uint32_t h, int par)
     return c;
 }
 
-// Half-site of thread tid in site block sb.  Natural order: 256 consecutive
-// half-sites.  Brick order (hg.brick = rows per wave, Lx/2 * hg.brick = 64):
+// Half-site of thread tid in site block sb.  Slab order (slab_order): 256
+// consecutive half-sites of it, for every lattice without bricks.  Brick order (hg.brick = rows per wave, Lx/2 * hg.brick = 64):
 // a wave covers hg.brick consecutive rows of one z plane (1 KiB per plane of
 // an FP32 field, as in the natural order), the block's four waves four
 // consecutive z planes of one time slice; the blocks run through the bricks
@@ -44,7 +44,7 @@ __device__ __forceinline__ EoSite eo_coords(const Geom& hg, uint32_t h, int par)
 // same XCD and its time neighbours to blocks a y row of bricks away (both
 // served from that XCD's L2 instead of HBM).
 __device__ __forceinline__ uint32_t eo_site(const Geom& hg, uint32_t sb, uint32_t tid) {
-    if (hg.brick == 0) return sb * 256u + tid;
+    if (hg.brick == 0) return slab_order(hg, sb * 256u + tid);
     const uint32_t Lxh = (uint32_t)hg.L[0] >> 1, by = hg.brick;
     const uint32_t Lt = (uint32_t)hg.L[3], nty = (uint32_t)hg.L[1] / by;
     const uint32_t ty = sb % nty, rest = sb / nty;

@@ -60,7 +60,12 @@ struct Geom {
     int64_t V;
     int64_t Vs;     // padded plane stride of native fields (multiple of 256)
     uint32_t m[3];  // ceil(2^32 / L[d]) for exact division of site indices
-    uint32_t brick; // half lattice: rows per wave of the brick order of site blocks (0: natural order)
+    uint32_t brick; // half lattice: rows per wave of the brick order of site blocks (0: slab order)
+    // slab order of the sites (slab_order): chunks of `slab` consecutive sites
+    // (whole z planes of one time slice), the time slices of a slab of z planes
+    // before the next slab; slab_m divides by slab (slab 0: natural order)
+    uint32_t slab;
+    uint32_t slab_m;
 };
 
 enum SPrec { P_F64 = 0, P_F32 = 1, P_F16 = 2, P_BF16 = 3, P_BH = 4 /* network-internal bfloat16, half-split planes */ };
