@@ -63,15 +63,22 @@ static int default_block(const tsm_solve_params* p) {
     return p->reliable ? 8 : 16;
 }
 
-// right-hand sides per lane in the stencil kernels: the tuned choice when it
-// divides the block, else the largest of 4, 2, 1 that does
-static int lane_rhs(const tm_ctx* ctx, const tsm_solve_params* p, int block) {
+// Right-hand sides per lane in the stencil kernels of blocks of `block` (at
+// most nsrc) sources: the tuned choice when it divides the block, else 2 where
+// the launch still fills the chip with it and 1 below.  Two sources share
+// every link a lane loads but halve the waves in flight.  The line lies where
+// LP solves cross over (blocks of 4 and 16, 8^4 to 24^3 x 48, lane widths 1 /
+// 2 / 4): FP16 even-odd 12^3 x 24 x 4 sources 428 / 442 / 618 us, x 16 855 /
+// 813 / 982, 24^3 x 48 x 16 10.3 / 9.1 / 9.7 ms; with FP32 links in the
+// half-hops (FP32, BF16) 16^3 x 32 x 16 3.3 / 3.8 / 4.6 ms, 24^3 x 48 x 16
+// 16.3 / 15.6 / 18.7 ms.  Four is never the fastest.
+static int lane_rhs(const tm_ctx* ctx, const tsm_solve_params* p, int block, int nsrc) {
     if (p->prec == TM_PREC_F64 || (p->stop == TM_STOP_TRUE && !p->reliable)) return 1;
     const int t = ctx->lane_rhs[p->prec];
     if (t > 0 && block % t == 0) return t;
-    if (block % 4 == 0) return 4;
-    if (block % 2 == 0) return 2;
-    return 1;
+    const bool wide = p->prec == TM_PREC_F32 || (p->prec == TM_PREC_BF16 && p->solver == TM_SOLVER_CG_EO);
+    const double work = (double)ctx->geo.V * std::min(block, nsrc);
+    return block % 2 == 0 && nsrc > 1 && work >= (wide ? 8e6 : 5e5) ? 2 : 1;
 }
 
 // time slices per lane of the time-marching K1 / K2 (0: lane per site)
@@ -1257,7 +1264,7 @@ tm_status tsm_solve_batch(tm_ctx* ctx, const tsm_solve_params* params, uint64_t 
     if (nsrc == 0) return TM_OK;
     const Geom& g = ctx->geo;
     const int blk = default_block(params);
-    const int nr = lane_rhs(ctx, params, blk);
+    const int nr = lane_rhs(ctx, params, blk, nsrc);
     // ids padded to a multiple of the lane width with repeats of the last id
     const int npad = (nsrc + nr - 1) / nr * nr;
     std::vector<uint64_t> ids(ids_host, ids_host + nsrc);
@@ -1363,7 +1370,7 @@ tm_status tsm_loops(tm_ctx* ctx, const tsm_params* P, double* loops_host, double
     const uint64_t sm = seed_mix(P->seed);
 
     const int blp = default_block(&P->lp), bhp = default_block(&P->hp);
-    const int nr_lp = lane_rhs(ctx, &P->lp, blp), nr_hp = lane_rhs(ctx, &P->hp, bhp);
+    const int nr_lp = lane_rhs(ctx, &P->lp, blp, N), nr_hp = lane_rhs(ctx, &P->hp, bhp, std::max(P->n_hp, 1));
     // LP buffers sized for the LP blocks from the first (smaller) HP-set
     // block on, HP buffers for the padded HP-set blocks
     {
