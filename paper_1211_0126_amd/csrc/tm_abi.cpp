@@ -224,10 +224,21 @@ static tm_status dslash_run(tm_ctx* ctx, int op, int prec, int nrhs, int layout,
                             void* stage_in, void* stage_out, void* tmp, bool prof) {
     const Geom& g = ctx->geo;
     const void* gauge = prec == TM_PREC_F64 ? ctx->gauge64 : ctx->gauge32;
-    const int nr = (prec == TM_PREC_F64) ? 1 : (nrhs % 4 == 0 ? 4 : (nrhs % 2 == 0 ? 2 : 1));
+    // Two right-hand sides per lane share the link loads where the spinors are
+    // small against the links and the launch fills the chip anyway (M, 24^3 x
+    // 48, 4 fields, one / two per lane: FP16 170 / 157 us, FP32 301 / 307, FP64
+    // 784 / 799; 9 x 11 x 7 x 13, M^dag M: FP16 15 / 20).
+    const int nr = prec >= TM_PREC_F16 && nrhs % 2 == 0 && (double)g.V * nrhs >= 5e5 ? 2 : 1;
+    const bool canonical = layout == TM_LAYOUT_CANONICAL;
+    // Canonical fields are read and written in place as 16-byte vectors: the
+    // two passes through the native layout cost more than the operator (one
+    // FP32 field at 16^3 x 32: 34 us with them, 16 without; four FP64 fields at
+    // 24^3 x 48: 1584 and 784).  A field that is not so aligned (a view at an
+    // odd offset) still goes through the staging buffers.
+    const bool direct = canonical && (((uintptr_t)in_dev | (uintptr_t)out_dev) & 15) == 0;
     const void* in = in_dev;
     void* out = out_dev;
-    if (layout == TM_LAYOUT_CANONICAL) {
+    if (canonical && !direct) {
         launch_field_convert(ctx->stream, g, prec, nrhs, true, in_dev, stage_in);
         in = stage_in;
         out = stage_out;
@@ -235,18 +246,22 @@ static tm_status dslash_run(tm_ctx* ctx, int op, int prec, int nrhs, int layout,
     const double bs = prec == TM_PREC_F64 ? 8 : (prec == TM_PREC_F32 ? 4 : 2);
     const double gb = prec == TM_PREC_F64 ? 4 * 18 * 8 : 4 * 12 * 4;
     const double bytes_one = (double)g.V * (nrhs * 48.0 * bs + gb);
-    auto apply = [&](int o, const void* src, void* dst) {
+    auto apply = [&](int o, const void* src, bool csrc, void* dst, bool cdst) {
         if (prof) prof_begin(ctx, TM_KC_APPLY);
-        launch_apply(ctx->stream, g, prec, gauge, ctx->lat.kappa, ctx->twist, o, nrhs, src, dst, nr, nullptr);
+        if (csrc || cdst)
+            launch_apply_canon(ctx->stream, g, prec, gauge, ctx->lat.kappa, ctx->twist, o, nrhs, src, csrc, dst, cdst,
+                               nr);
+        else
+            launch_apply(ctx->stream, g, prec, gauge, ctx->lat.kappa, ctx->twist, o, nrhs, src, dst, nr, nullptr);
         if (prof) prof_end(ctx, TM_KC_APPLY, bytes_one);
     };
     if (op == TM_OP_MDAGM) {
-        apply(TM_OP_M, in, tmp);
-        apply(TM_OP_MDAG, tmp, out);
+        apply(TM_OP_M, in, direct, tmp, false);
+        apply(TM_OP_MDAG, tmp, false, out, direct);
     } else {
-        apply(op, in, out);
+        apply(op, in, direct, out, direct);
     }
-    if (layout == TM_LAYOUT_CANONICAL) launch_field_convert(ctx->stream, g, prec, nrhs, false, out, out_dev);
+    if (canonical && !direct) launch_field_convert(ctx->stream, g, prec, nrhs, false, out, out_dev);
     TM_HIP(hipGetLastError());
     return TM_OK;
 }

@@ -308,6 +308,93 @@ __device__ __forceinline__ void* field_rhs(void* base, long Vs, int r) {
 }
 
 // ---------------------------------------------------------------------------
+// canonical spinor fields of storage S ([rhs][site][12] complex, 16-byte
+// aligned): the same 16-byte vectors as the native planes, NV of one site back
+// to back.  A wave's loads of one vector are NV * 16 bytes apart, but its NV
+// loads together cover every line they touch, so memory is read once as long
+// as the lines stay in L1 between them.
+// ---------------------------------------------------------------------------
+template <class S>
+struct Canon {
+    using V = typename S::V;
+    static constexpr int NV = S::NV;
+};
+template <class S>
+struct IsCanon : std::false_type {};
+template <class S>
+struct IsCanon<Canon<S>> : std::true_type {};
+// sites between the right-hand sides of a field (field_rhs)
+template <class S>
+__device__ __forceinline__ long field_stride(const Geom& g) {
+    return IsCanon<S>::value ? (long)g.V : (long)g.Vs;
+}
+// vector k of site s (32-bit offsets: 192 V < 2^32 follows from tm_create's bound)
+template <int NV>
+__device__ __forceinline__ uint4 ld_canon(const void* base, int k, uint32_t s) {
+    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rsrc_of(base), s * (NV * 16u) + k * 16u, 0, 0));
+}
+template <int NV>
+__device__ __forceinline__ void st_canon(void* base, int k, uint32_t s, uint4 val) {
+    using V4 = unsigned int __attribute__((ext_vector_type(4)));
+    const V4 v = __builtin_bit_cast(V4, val);
+    __builtin_amdgcn_raw_buffer_store_b128(v, rsrc_of(base), s * (NV * 16u) + k * 16u, 0, 0);
+    asm volatile("s_nop 4" ::"v"(v) : "memory");  // (see st_plane)
+}
+// spinor loads and stores of either layout
+template <class S, typename R>
+__device__ __forceinline__ void load_site(const void* base, long stride, uint32_t s, cx<R> p[12]) {
+    if constexpr (!IsCanon<S>::value) {
+        load_spinor<S, R>(base, stride, s, p);
+    } else {
+        constexpr int NV = S::NV;
+#pragma unroll
+        for (int k = 0; k < NV; k++) {
+            const uint4 v = ld_canon<NV>(base, k, s);
+            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+            if constexpr (NV == 12) {
+                const double2 d = __builtin_bit_cast(double2, v);
+                p[k] = {(R)d.x, (R)d.y};
+            } else if constexpr (NV == 6) {
+                p[2 * k] = {(R)__uint_as_float(w[0]), (R)__uint_as_float(w[1])};
+                p[2 * k + 1] = {(R)__uint_as_float(w[2]), (R)__uint_as_float(w[3])};
+            } else {
+                constexpr bool BF = std::is_same<S, Canon<SBF16>>::value;
+#pragma unroll
+                for (int j = 0; j < 4; j++)
+                    p[4 * k + j] = {(R)(BF ? bf16_to_f32(w[j] & 0xFFFFu) : f16_to_f32(w[j] & 0xFFFFu)),
+                                    (R)(BF ? bf16_to_f32(w[j] >> 16) : f16_to_f32(w[j] >> 16))};
+            }
+        }
+    }
+}
+template <class S, typename R>
+__device__ __forceinline__ void store_site(void* base, long stride, uint32_t s, const cx<R> p[12]) {
+    if constexpr (!IsCanon<S>::value) {
+        store_spinor<S, R>(base, stride, s, p);
+    } else {
+        constexpr int NV = S::NV;
+#pragma unroll
+        for (int k = 0; k < NV; k++) {
+            uint4 v;
+            if constexpr (NV == 12) {
+                v = __builtin_bit_cast(uint4, make_double2((double)p[k].re, (double)p[k].im));
+            } else if constexpr (NV == 6) {
+                v = __builtin_bit_cast(uint4, make_float4((float)p[2 * k].re, (float)p[2 * k].im, (float)p[2 * k + 1].re,
+                                                          (float)p[2 * k + 1].im));
+            } else {
+                constexpr bool BF = std::is_same<S, Canon<SBF16>>::value;
+                uint32_t w[4];
+#pragma unroll
+                for (int j = 0; j < 4; j++)
+                    w[j] = BF ? pack2_bf16(p[4 * k + j].re, p[4 * k + j].im) : pack2_f16(p[4 * k + j].re, p[4 * k + j].im);
+                v = make_uint4(w[0], w[1], w[2], w[3]);
+            }
+            st_canon<NV>(base, k, s, v);
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
 // native gauge storage (no boundary sign folded in)
 //   GF64: double2 [4][9][Vs]   full 3x3 links
 //   GF32: float4  [4][3][Vs]   rows 0 and 1 (12 reals); row 2 rebuilt as

@@ -177,6 +177,8 @@ void launch_eo_merge(hipStream_t st, const Geom& g, const Geom& hg, const void* 
 // operator
 void launch_apply(hipStream_t st, const Geom& g, int prec, const void* gauge, double kappa, double twist, int op,
                   int nrhs, const void* in, void* out, int nr, const CgScal* gate);
+void launch_apply_canon(hipStream_t st, const Geom& g, int prec, const void* gauge, double kappa, double twist, int op,
+                        int nrhs, const void* in, bool cin, void* out, bool cout, int nr);
 // CG
 void launch_scal_init(hipStream_t st, CgScal* sc, int n, double tol2, int maxit, int stop, int reliable,
                       double delta2);

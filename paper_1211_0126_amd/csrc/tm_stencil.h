@@ -166,7 +166,7 @@ template <int MU, bool DAG, typename R, class S, class G, int NR>
 __device__ __forceinline__ void hop_mu(const Geom& geo, const void* gauge, const void* in, uint32_t s, const Site& c,
                                        cx<R> (&acc)[NR][12]) {
     constexpr int SF = DAG ? -1 : 1;
-    const long Vs = geo.Vs;
+    const long Vs = geo.Vs, Fs = field_stride<S>(geo);
     {
         const uint32_t y = nb_fwd(geo, s, c, MU);
         const bool flip = (MU == 3) && (c.t + 1 == geo.L[3]) && (geo.t_bc < 0);
@@ -175,7 +175,7 @@ __device__ __forceinline__ void hop_mu(const Geom& geo, const void* gauge, const
 #pragma unroll
         for (int r = 0; r < NR; r++) {
             cx<R> p[12], h[6], g[6];
-            load_spinor<S, R>(field_rhs<S>(in, Vs, r), Vs, y, p);
+            load_site<S, R>(field_rhs<S>(in, Fs, r), Fs, y, p);
             proj<MU, SF>(p, h);
             if (flip) negate6(h);
             su3_mul(U, h, g);
@@ -194,7 +194,7 @@ __device__ __forceinline__ void hop_mu(const Geom& geo, const void* gauge, const
 #pragma unroll
         for (int r = 0; r < NR; r++) {
             cx<R> p[12], h[6], g[6];
-            load_spinor<S, R>(field_rhs<S>(in, Vs, r), Vs, y, p);
+            load_site<S, R>(field_rhs<S>(in, Fs, r), Fs, y, p);
             proj<MU, -SF>(p, h);
             if (flip) negate6(h);
             su3_dag_mul(U, h, g);

@@ -1,0 +1,95 @@
+"""The order in which the stencils visit the lattice and how they deal right-
+hand sides to waves: lattices of several slabs whose sites do not fill the
+last wave, blocks of every width class (4, 2 and 1 chunks per block).  FP64
+iterates against the oracle to 1e-12 (the bound of the other operator tests);
+every source of a block bit for bit what it is alone."""
+
+import numpy as np
+import pytest
+
+from lattice_inputs import make_gauge, random_spinor
+
+pytestmark = pytest.mark.gpu
+
+KAPPA, MU = 0.1632, 0.004
+# several slabs of 3, 2 and 7 planes (whole lattice and half), ragged waves
+LATTICES = [(10, 6, 12, 6), (14, 10, 4, 6), (6, 18, 14, 4)]
+
+
+def _ctx(dims):
+    import paper_1211_0126_amd as tq
+    U = make_gauge(dims, 0.25, 17)
+    ctx = tq.tm_create(dims, KAPPA, MU, -1)
+    tq.tm_gauge_load(ctx, U)
+    return ctx, U
+
+
+@pytest.mark.parametrize("dims", LATTICES)
+def test_operator_in_slab_order(orc, dims):
+    import torch
+    import paper_1211_0126_amd as tq
+    ctx, U = _ctx(dims)
+    x = random_spinor(dims, 5, 3)
+    y = tq.tm_dslash(ctx, tq.OP_MDAGM, tq.PREC_F64, torch.from_numpy(x).cuda()).cpu().numpy()
+    ctx.close()
+    for r in range(3):
+        ref = orc.apply_op(dims, -1, KAPPA, MU, tq.OP_MDAGM, U, x[r])
+        assert np.linalg.norm(y[r] - ref) < 1e-12 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("dims", LATTICES)
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 6, 8])
+def test_evenodd_blocks(orc, dims, n):
+    import torch
+    import paper_1211_0126_amd as tq
+    ctx, U = _ctx(dims)
+    ids = [3 * i + 1 for i in range(n)]
+
+    def solve(prec, which, block):
+        p = tq.solve_params(prec=prec, tol=0.0, max_iter=3, rhs_block=block, solver=tq.SOLVER_CG_EO, true_resid=0)
+        return tq.tsm_solve_batch(ctx, p, 29, which)[0]
+
+    x = solve(tq.PREC_F64, ids, n)
+    ref, _ = orc.cgnr_eo(dims, -1, KAPPA, MU, U, orc.noise_z4(dims, 29, ids[-1]), 0.0, 3)
+    assert np.linalg.norm(x[-1].cpu().numpy() - ref) < 1e-12 * np.linalg.norm(ref)
+    for prec in (tq.PREC_F64, tq.PREC_F32, tq.PREC_F16):
+        for nr in (1, 2):
+            if n % nr == 0:
+                tq.tm_set_lane_rhs(ctx, prec, nr)
+                x = solve(prec, ids, n)
+                for i in range(n):
+                    assert torch.equal(x[i], solve(prec, ids[i:i + 1], 1)[0]), (prec, nr, i)
+    ctx.close()
+
+
+@pytest.mark.parametrize("prec", [0, 1, 2, 3])
+@pytest.mark.parametrize("n", [1, 2, 3])
+def test_canonical_fields_at_any_alignment(prec, n):
+    """Canonical fields in place (16-byte aligned) and through the staging
+    buffers (views one complex number further): the same kernel arithmetic,
+    bit for bit, and the native layout's result."""
+    import torch
+    import paper_1211_0126_amd as tq
+    dims = LATTICES[0]
+    ctx, _ = _ctx(dims)
+    x = torch.from_numpy(random_spinor(dims, 3, n)).cuda()
+    if prec == tq.PREC_F32:
+        x = x.to(torch.complex64)
+    elif prec != tq.PREC_F64:
+        x = torch.view_as_real(x).to(torch.float16 if prec == tq.PREC_F16 else torch.bfloat16).contiguous()
+    step = 1 if x.is_complex() else 2
+    odd = torch.empty(x.numel() + step, dtype=x.dtype, device="cuda")[step:].view(x.shape)
+    odd.copy_(x)
+    for op in (tq.OP_M, tq.OP_MDAG, tq.OP_MDAGM, tq.OP_HOP):
+        y = tq.tm_dslash(ctx, op, prec, x)
+        z = torch.empty(x.numel() + step, dtype=x.dtype, device="cuda")[step:].view(x.shape)
+        assert torch.equal(y, tq.tm_dslash(ctx, op, prec, odd, out=z))
+        assert torch.equal(y, tq.tm_dslash(ctx, op, prec, odd))
+        assert torch.equal(y, tq.tm_dslash(ctx, op, prec, x, out=z))
+        nb = tq.tm_field_bytes(ctx, prec, n, tq.LAYOUT_NATIVE)
+        a, b = (torch.empty(nb, dtype=torch.uint8, device="cuda") for _ in range(2))
+        tq.tm_field_convert(ctx, prec, n, True, x, a)
+        tq.tm_dslash(ctx, op, prec, a, out=b, layout=tq.LAYOUT_NATIVE, nrhs=n)
+        tq.tm_field_convert(ctx, prec, n, False, b, z)
+        assert torch.equal(y, z)
+    ctx.close()
