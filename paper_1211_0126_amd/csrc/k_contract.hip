@@ -68,6 +68,31 @@ __device__ __forceinline__ void load_half_spinor<SF32>(const void* base, long Vs
     }
 }
 
+template <>
+__device__ __forceinline__ void load_half_spinor<Canon<SF64>>(const void* base, long, uint32_t s, int h, cx<double> p[6]) {
+#pragma unroll
+    for (int k = 0; k < 6; k++) {
+        const uint32_t off = s * 192u + (uint32_t)h * 96u + k * 16u;
+        const double2 v =
+            __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(rsrc_of(base), off, 0u, 0));
+        p[k] = {v.x, v.y};
+    }
+}
+
+// Row and spin half of lane tid of a stage-A launch: native planes one half
+// after the other; canonical records with the two halves of a site in
+// neighbouring lanes, which together read each record whole.
+template <class S>
+__device__ __forceinline__ void row_half(long tid, long nrow, long& q, int& h) {
+    if (IsCanon<S>::value) {
+        h = (int)(tid & 1);
+        q = tid >> 1;
+    } else {
+        h = tid >= nrow ? 1 : 0;
+        q = tid - h * nrow;
+    }
+}
+
 // the six components of spin rows 2h, 2h+1 in arithmetic A (FP32 only from
 // an FP32 field)
 template <class S, typename A>
@@ -149,16 +174,17 @@ __global__ __launch_bounds__(256) void k_contract_a(ContractArgs a) {
     const long tid = (long)blockIdx.x * 256 + threadIdx.x;
     const int r = blockIdx.y;
     if (tid >= 2 * nrow) return;
-    const int h = tid >= nrow ? 1 : 0;
-    const long q = tid - h * nrow;
-    const int x = (int)(q % Lx);
-    const long q2 = q / Lx;
+    long row;
+    int h;
+    row_half<S>(tid, nrow, row, h);
+    const int x = (int)(row % Lx);
+    const long q2 = row / Lx;
     const int z = (int)(q2 % Lz);
     const int t = (int)(q2 / Lz);
     const int npy = a.npy;
     static_assert(!HALVES || (E == 0 && (std::is_same<S, SF32>::value || std::is_same<S, SF16>::value)),
                   "halves: standard loop, FP32 or FP16");
-    const void* sol = field_rhs<S>(a.sol, HALVES ? a.hgeo.Vs : g.Vs, r);
+    const void* sol = field_rhs<S>(a.sol, HALVES ? (long)a.hgeo.Vs : field_stride<S>(g), r);
     const void* sol_e = HALVES ? field_rhs<S>(a.sol_e, a.hgeo.Vs, r) : nullptr;
     const uint64_t id = a.ids[r];
     // the y sums of the standard loop of an FP32 solution in FP32
@@ -202,7 +228,8 @@ __global__ __launch_bounds__(256) void k_contract_a(ContractArgs a) {
 #pragma unroll
                 for (int k = 0; k < 6; k++) u[k] = h ? q[6 + k] : q[k];
             } else {
-                load_half_spinor<S>(field_rhs<S>(a.dsol, g.Vs, r), g.Vs, s, h, u);  // (D s in s's precision)
+                using D = typename std::conditional<IsCanon<S>::value, SF64, S>::type;
+                load_half_spinor<D>(field_rhs<D>(a.dsol, g.Vs, r), g.Vs, s, h, u);  // (D s, native, in s's precision)
             }
 #pragma unroll
             for (int b = 0; b < 2; b++)
@@ -263,9 +290,10 @@ __device__ __forceinline__ void su3_apply_d(const cx<A> U[3][3], bool fwd, A ph,
 // about 1e-6 relative); an FP64 one FP64 throughout.
 template <class S>
 __global__ __launch_bounds__(256) void k_contract_d(ContractArgs a) {
-    using A = typename std::conditional<std::is_same<S, SF64>::value, double, float>::type;
-    using GL = typename std::conditional<std::is_same<S, SF64>::value, GF64, GF32>::type;
-    const void* gl = std::is_same<S, SF64>::value ? a.gauge64 : a.gauge32;
+    constexpr bool F64 = S::NV == 12;
+    using A = typename std::conditional<F64, double, float>::type;
+    using GL = typename std::conditional<F64, GF64, GF32>::type;
+    const void* gl = F64 ? a.gauge64 : a.gauge32;
     const Geom& g = a.geo;
     const int Lx = g.L[0], Ly = g.L[1], Lz = g.L[2], Lt = g.L[3];
     const long nrow = (long)Lx * Lz * Lt;
@@ -275,14 +303,15 @@ __global__ __launch_bounds__(256) void k_contract_d(ContractArgs a) {
     const int r = blockIdx.x;
     const int mu = blockIdx.z;
     if (tid >= 2 * nrow) return;
-    const int h = tid >= nrow ? 1 : 0;
-    const long q = tid - h * nrow;
-    const int x = (int)(q % Lx);
-    const long q2 = q / Lx;
+    long row;
+    int h;
+    row_half<S>(tid, nrow, row, h);
+    const int x = (int)(row % Lx);
+    const long q2 = row / Lx;
     const int z = (int)(q2 % Lz);
     const int t = (int)(q2 / Lz);
     const int npy = a.npy;
-    const void* sol = field_rhs<S>(a.sol, g.Vs, r);
+    const void* sol = field_rhs<S>(a.sol, field_stride<S>(g), r);
     const uint64_t id = a.ids[r];
     const uint64_t V = (uint64_t)g.V;
     cx<A> acc[3][8];
@@ -445,7 +474,7 @@ __global__ __launch_bounds__(256) void k_contract_c(ContractArgs a) {
     o[((size_t)gn * a.n_mom + m) * Lt + t] = make_double2(acc.re, acc.im);
 }
 
-void launch_contract(hipStream_t st, const ContractArgs& a0, int xprec) {
+void launch_contract(hipStream_t st, const ContractArgs& a0, int xprec, bool canon) {
     const Geom& g = a0.geo;
     const long nrow = 2L * g.L[0] * g.L[2] * g.L[3];
     dim3 ga((unsigned)((nrow + 255) / 256), (unsigned)a0.nrhs);
@@ -454,14 +483,18 @@ void launch_contract(hipStream_t st, const ContractArgs& a0, int xprec) {
     a.nrhs = a0.nrhs * a0.nmu;
     if (a0.est == 3) {
         dim3 gd(ga.y, ga.x, 4);
-        if (xprec == P_F64)
+        if (canon)
+            hipLaunchKernelGGL((k_contract_d<Canon<SF64>>), gd, dim3(256), 0, st, a0);
+        else if (xprec == P_F64)
             hipLaunchKernelGGL((k_contract_d<SF64>), gd, dim3(256), 0, st, a0);
         else
             hipLaunchKernelGGL((k_contract_d<SF32>), gd, dim3(256), 0, st, a0);
     }
     auto run_a = [&](auto est) {
         constexpr int E = decltype(est)::value;
-        if (xprec == P_F64)
+        if (canon)
+            hipLaunchKernelGGL((k_contract_a<Canon<SF64>, E>), ga, dim3(256), 0, st, a0);
+        else if (xprec == P_F64)
             hipLaunchKernelGGL((k_contract_a<SF64, E>), ga, dim3(256), 0, st, a0);
         else
             hipLaunchKernelGGL((k_contract_a<SF32, E>), ga, dim3(256), 0, st, a0);
@@ -610,7 +643,7 @@ __global__ __launch_bounds__(256) void k_allmom_x(ContractArgs a, double2* out, 
     const int y0 = (int)(blockIdx.x % nyb) * NL;
     const bool pow2 = (Lx & (Lx - 1)) == 0;
     const int lg = ilog2(Lx);
-    const void* sol = field_rhs<S>(a.sol, g.Vs, r);
+    const void* sol = field_rhs<S>(a.sol, field_stride<S>(g), r);
     const uint64_t id = a.ids[r];
     for (int i = threadIdx.x; i < Lx * NL; i += blockDim.x) {
         const int x = pow2 ? (i & (Lx - 1)) : i % Lx, l = pow2 ? (i >> lg) : i / Lx;
@@ -726,8 +759,7 @@ static int pick_lines(int n, int L, int w, int cap) {
     return k;
 }
 
-void launch_contract_all_momenta(hipStream_t st, const ContractArgs& a, int xprec, double2* buf0, double2* buf1,
-                                 const double2* tw) {
+void launch_contract_all_momenta(hipStream_t st, const ContractArgs& a, bool canon, double2* buf0, const double2* tw) {
     const Geom& g = a.geo;
     const int Lx = g.L[0], Ly = g.L[1], Lz = g.L[2], Lt = g.L[3];
     const int NL = pick_lines(Ly, Lx, 16, 8);
@@ -735,10 +767,10 @@ void launch_contract_all_momenta(hipStream_t st, const ContractArgs& a, int xpre
     const dim3 gx((unsigned)((long)Lt * Lz * (Ly / NL)), (unsigned)a.nrhs);
     // one thread per site of the block's lines (at least a wave, at most 256)
     const unsigned bx = (unsigned)std::min(256, std::max(64, (Lx * NL + 63) / 64 * 64));
-    if (xprec == P_F64)
-        hipLaunchKernelGGL(k_allmom_x<SF64>, gx, dim3(bx), lds_x, st, a, buf0, tw, NL);
+    if (canon)
+        hipLaunchKernelGGL(k_allmom_x<Canon<SF64>>, gx, dim3(bx), lds_x, st, a, buf0, tw, NL);
     else
-        hipLaunchKernelGGL(k_allmom_x<SF32>, gx, dim3(bx), lds_x, st, a, buf0, tw, NL);
+        hipLaunchKernelGGL(k_allmom_x<SF64>, gx, dim3(bx), lds_x, st, a, buf0, tw, NL);
     // y transform in place: one block per (r, t, z, kx) line group
     hipLaunchKernelGGL(k_dft_axis, dim3((unsigned)((long)a.nrhs * g.V / Ly)), dim3(256),
                        (unsigned)(sizeof(double2) * 17 * Ly), st, (const double2*)buf0, buf0, Ly, 16L * Lx, tw + Lx);
@@ -748,7 +780,6 @@ void launch_contract_all_momenta(hipStream_t st, const ContractArgs& a, int xpre
     const unsigned lds_z = (unsigned)(sizeof(double2) * (Lz * std::max(16, 8 * T) + Lz));
     hipLaunchKernelGGL(k_allmom_z, dim3((unsigned)((long)Lx * Ly * (Lt / T) * 2), (unsigned)a.nrhs), dim3(256),
                        lds_z, st, a, (const double2*)buf0, tw + Lx + Ly, T);
-    (void)buf1;
 }
 
 // TSM combination of Eq. 4 from the per-source loops ps[j][slot][k]
