@@ -116,9 +116,8 @@ __device__ inline void cg_finish_step(CgScal& q, double rrn, double rhon) {
 // K1: t = M p and alpha
 template <typename R, class S, class G, int NR>
 __global__ TM_STENCIL_R(NR, R) void k_cg_mp(CgArgs a) {
-    __shared__ double sh[4];
     const BlockMap bm = stencil_block((uint32_t)(a.nrhs / NR));
-    const uint32_t nb = bm.nsb;
+    const uint32_t ws = bm.sb * 4u + (threadIdx.x >> 6), nws = (uint32_t)((a.geo.V + 63) / 64);
     const uint32_t s = slab_order(a.geo, bm.sb * 256u + threadIdx.x);
     const int r0 = bm.ch * NR;
     const long Vs = a.geo.Vs;
@@ -144,6 +143,7 @@ __global__ TM_STENCIL_R(NR, R) void k_cg_mp(CgArgs a) {
             cx<R> pc[12], t[12];
             load_spinor<S, R>(field_rhs<S>(p0, Vs, r), Vs, s, pc);
             diag_combine(pc, acc[r], (R)a.kappa, (R)a.twist, t);
+            settle<12>(t);
             round_storage<S, R>(t);
             store_spinor_cp<S, R, TM_CP_K1T>(field_rhs<S>(a.t, Vs, r0 + r), Vs, s, t);
             part[r] = spinor_norm2(t);
@@ -151,14 +151,15 @@ __global__ TM_STENCIL_R(NR, R) void k_cg_mp(CgArgs a) {
     }
 #pragma unroll
     for (int r = 0; r < NR; r++) {
-        double v = block_sum256(part[r], sh);
-        if (threadIdx.x == 0) a.partials[(size_t)(r0 + r) * nb + bm.sb] = v;
+        const double v = wave_sum(part[r]);
+        if ((threadIdx.x & 63u) == 0 && ws < nws) a.partials[(size_t)(r0 + r) * nws + ws] = v;
     }
 }
 
 // Block partials of one right-hand side in a fixed order (the stencil
 // launch that wrote them has completed); valid in thread 0.
 __device__ __forceinline__ double sum_block_partials(const double* p, uint32_t n, double* sh) {
+    if (n <= kOrderParts) return wave_partials(p, n);
     double v = 0;
     for (uint32_t i = threadIdx.x; i < n; i += 256) v += p[i];
     return block_sum256(v, sh);
@@ -194,9 +195,8 @@ __global__ __launch_bounds__(256) void k_cg_beta(CgArgs a, uint32_t nb) {
 // optionally rho -= alpha t (recursive true residual)
 template <typename R, class S, class G, class X, typename RX, int NR, bool TRACK>
 __global__ TM_STENCIL_R(NR, R) void k_cg_upd(CgArgs a) {
-    __shared__ double sh[4];
     const BlockMap bm = stencil_block((uint32_t)(a.nrhs / NR));
-    const uint32_t nb = bm.nsb;
+    const uint32_t ws = bm.sb * 4u + (threadIdx.x >> 6), nws = (uint32_t)((a.geo.V + 63) / 64);
     const uint32_t s = slab_order(a.geo, bm.sb * 256u + threadIdx.x);
     const int r0 = bm.ch * NR;
     const long Vs = a.geo.Vs;
@@ -208,6 +208,9 @@ __global__ TM_STENCIL_R(NR, R) void k_cg_upd(CgArgs a) {
         any |= act[r];
     }
     if (!any) return;
+    double alphas[NR];
+#pragma unroll
+    for (int r = 0; r < NR; r++) alphas[r] = step_alpha(a, r0 + r, bm.sb == 0 && threadIdx.x == 0);
     double prr[NR], prho[NR];
 #pragma unroll
     for (int r = 0; r < NR; r++) prr[r] = prho[r] = 0;
@@ -219,7 +222,7 @@ __global__ TM_STENCIL_R(NR, R) void k_cg_upd(CgArgs a) {
 #pragma unroll
         for (int r = 0; r < NR; r++) {
             if (!act[r]) continue;
-            const double alpha = a.scal[r0 + r].alpha;
+            const double alpha = alphas[r];
             cx<R> tc[12], q[12], rv[12], pv[12];
             load_spinor<S, R>(field_rhs<S>(t0, Vs, r), Vs, s, tc);
             diag_combine(tc, acc[r], (R)a.kappa, (R)(-a.twist), q);
@@ -228,6 +231,7 @@ __global__ TM_STENCIL_R(NR, R) void k_cg_upd(CgArgs a) {
             const R al = (R)alpha;
 #pragma unroll
             for (int k = 0; k < 12; k++) rv[k] = rv[k] - al * q[k];
+            settle<12>(rv);
             round_storage<S, R>(rv);
             store_spinor_cp<S, R, TM_CP_K2>(rp, Vs, s, rv);
             prr[r] = spinor_norm2(rv);
@@ -253,11 +257,12 @@ __global__ TM_STENCIL_R(NR, R) void k_cg_upd(CgArgs a) {
     }
 #pragma unroll
     for (int r = 0; r < NR; r++) {
-        double v = block_sum256(prr[r], sh);
-        if (threadIdx.x == 0) a.partials[(size_t)(r0 + r) * nb + bm.sb] = v;
+        const double v = wave_sum(prr[r]);
+        const bool w0 = (threadIdx.x & 63u) == 0 && ws < nws;
+        if (w0) (a.scal_next ? a.partials2 : a.partials)[(size_t)(r0 + r) * nws + ws] = v;
         if (TRACK) {
-            double w = block_sum256(prho[r], sh);
-            if (threadIdx.x == 0) a.partials2[(size_t)(r0 + r) * nb + bm.sb] = w;
+            const double w = wave_sum(prho[r]);
+            if (w0) a.partials2[(size_t)(r0 + r) * nws + ws] = w;
         }
     }
 }
@@ -267,14 +272,32 @@ template <typename R, class S>
 __global__ __launch_bounds__(256) void k_cg_p(CgArgs a) {
     const uint32_t s = blockIdx.x * 256u + threadIdx.x;
     const int r = blockIdx.y;
-    if (s >= a.geo.V) return;
-    const CgScal& q = a.scal[r];
-    if (!q.active) return;
-    const R beta = (R)q.beta;
-    cx<R> rv[12], pv[12];
-    load_spinor_cp<S, R, TM_CP_K3>(field_rhs<S>(a.r, a.geo.Vs, r), a.geo.Vs, s, rv);
+    const bool on = s < a.geo.V;
     void* pp = field_rhs<S>(a.p, a.geo.Vs, r);
-    load_spinor_cp<S, R, TM_CP_K3>(pp, a.geo.Vs, s, pv);
+    cx<R> rv[12], pv[12];
+    double b;
+    if (a.scal_next) {  // merged reductions: finish the step here (the fields are loaded meanwhile)
+        if (on) {
+            load_spinor<S, R>(field_rhs<S>(a.r, a.geo.Vs, r), a.geo.Vs, s, rv);
+            load_spinor<S, R>(pp, a.geo.Vs, s, pv);
+        }
+        TM_MEM_FENCE();
+        CgScal q = a.scal[r];
+        if (q.active) cg_finish_step(q, wave_partials(a.partials2 + (size_t)r * a.npart, a.npart), 0.0);
+        if (s == 0) a.scal_next[r] = q;
+        if (!q.active) return;
+        b = q.beta;
+    } else {
+        const CgScal& q = a.scal[r];
+        if (!q.active) return;
+        b = q.beta;
+        if (on) {
+            load_spinor_cp<S, R, TM_CP_K3>(field_rhs<S>(a.r, a.geo.Vs, r), a.geo.Vs, s, rv);
+            load_spinor_cp<S, R, TM_CP_K3>(pp, a.geo.Vs, s, pv);
+        }
+    }
+    if (!on) return;
+    const R beta = (R)b;
 #pragma unroll
     for (int k = 0; k < 12; k++) pv[k] = rv[k] + beta * pv[k];
     store_spinor<S, R>(a.pn ? field_rhs<S>(a.pn, a.geo.Vs, r) : pp, a.geo.Vs, s, pv);

@@ -323,6 +323,9 @@ __global__ TM_STENCIL_R(NR, R) void k_eo_upd(CgArgs a, EoCg e) {
         any |= act[r];
     }
     if (!any) return;
+    double alphas[NR];
+#pragma unroll
+    for (int r = 0; r < NR; r++) alphas[r] = step_alpha(a, r0 + r, wm.ws == 0 && (threadIdx.x & 63u) == 0);
     double prr[NR], prho[NR];
 #pragma unroll
     for (int r = 0; r < NR; r++) prr[r] = prho[r] = 0;
@@ -334,7 +337,7 @@ __global__ TM_STENCIL_R(NR, R) void k_eo_upd(CgArgs a, EoCg e) {
 #pragma unroll
         for (int r = 0; r < NR; r++) {
             if (!act[r]) continue;
-            const double alpha = a.scal[r0 + r].alpha;
+            const double alpha = alphas[r];
             cx<R> tc[12], q[12], rv[12], pv[12];
             load_spinor<S, R>(field_rhs<S>(a.t, Vs, r0 + r), Vs, h, tc);
 #pragma unroll
@@ -377,7 +380,7 @@ __global__ TM_STENCIL_R(NR, R) void k_eo_upd(CgArgs a, EoCg e) {
     for (int r = 0; r < NR; r++) {
         const double v = wave_sum(prr[r]);
         const bool w0 = (threadIdx.x & 63u) == 0 && wm.ws < wm.nws;
-        if (w0) a.partials[(size_t)(r0 + r) * wm.nws + wm.ws] = v;
+        if (w0) (a.scal_next ? a.partials2 : a.partials)[(size_t)(r0 + r) * wm.nws + wm.ws] = v;
         if (TRACK) {
             const double w = wave_sum(prho[r]);
             if (w0) a.partials2[(size_t)(r0 + r) * wm.nws + wm.ws] = w;

@@ -373,7 +373,7 @@ bool geom_setup(const tm_lattice* lat, Geom* gp, Geom* hp, bool* eo_ok, std::str
 }
 
 size_t partials_per_rhs(const Geom& g, const Geom& hg, bool eo_ok) {
-    size_t n = (size_t)((g.V + 255) / 256);
+    size_t n = (size_t)((g.V + 63) / 64);
     // time-marching kernels: a partial per 256 sites of a time slice and per
     // segment (at most one segment per slice)
     n = std::max(n, (size_t)((g.V / g.L[3] + 255) / 256) * (size_t)g.L[3]);

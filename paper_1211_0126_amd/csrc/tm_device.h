@@ -592,6 +592,20 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
+// Sum of n partials by one wave, in every lane (lane l adds l, l + 64, ... in
+// order; eight loads in flight).
+__device__ __forceinline__ double wave_partials(const double* p, uint32_t n) {
+    double v = 0;
+    for (uint32_t i = threadIdx.x & 63u; i < n; i += 512) {
+        double x[8];
+#pragma unroll
+        for (uint32_t j = 0; j < 8; j++) x[j] = i + 64 * j < n ? p[i + 64 * j] : 0.0;
+#pragma unroll
+        for (uint32_t j = 0; j < 8; j++) v += x[j];
+    }
+    return wave_sum(v);
+}
+
 // Sum of v over a 256-thread block; result valid in thread 0.
 __device__ __forceinline__ double block_sum256(double v, double* sh /*[4]*/) {
     v = wave_sum(v);
@@ -620,6 +634,22 @@ template <int NR>
 struct StencilOcc {
     static constexpr int waves = NR == 1 ? TM_WAVES_NR1 : (NR == 2 ? TM_WAVES_NR2 : (NR == 4 ? TM_WAVES_NR4 : 1));
 };
+
+// Step length of right-hand side r for K2: alpha as k_cg_alpha left it, or with
+// merged reductions formed by every wave from K1's partials (and recorded by
+// the lane that says it is first)
+template <class Args>
+__device__ __forceinline__ double step_alpha(const Args& a, int r, bool first) {
+    if (!a.scal_next) return a.scal[r].alpha;
+    const double tt = wave_partials(a.partials + (size_t)r * a.npart, a.npart);
+    const double alpha = tt > 0 ? a.scal[r].rr / tt : 0.0;
+    if (first && a.scal[r].active) {
+        a.scal[r].tt = tt;
+        a.scal[r].alpha = alpha;
+        if (a.ahist) a.ahist[(size_t)r * a.ring + (a.scal[r].iters % a.ring)] = alpha;
+    }
+    return alpha;
+}
 
 }  // namespace tmq
 

@@ -31,7 +31,22 @@ struct CgArgs {
     void* pn;           // nullable: p = r + beta p in place
     double* ahist;      // nullable: [nrhs][ring]
     int ring;
+    // Small lattices (merged reductions): K2 forms alpha itself from K1's
+    // partials and writes its own to partials2, K3 forms beta and the stop test
+    // from those and writes the state after the step to scal_next (another
+    // array: its blocks still read scal).  Null: launch_cg_alpha / _beta do.
+    CgScal* scal_next;
 };
+// K2 and K3 sum the partials themselves up to this many per right-hand side, or
+// kOrderParts on launches of few waves: every wave reads them all, which costs
+// more than the two launches it saves once they are tens of megabytes
+constexpr uint32_t kMergeParts = 512;
+// partials up to this many are summed in one order (a wave's) by every kernel
+// that sums them, so that merging may depend on the launch
+constexpr uint32_t kOrderParts = 2048;
+inline bool merge_parts(uint32_t npart, int nrhs) {
+    return npart <= kMergeParts || (npart <= kOrderParts && (double)npart * npart * nrhs <= 5e6);
+}
 
 struct ContractArgs {
     Geom geo;
@@ -135,6 +150,11 @@ struct EoCg {
     const void* godd;   // links of the odd sites
     const void* y;      // intermediate even half field
 };
+// small launches: a direction per wave (k_quad.hip); e null for the whole lattice
+bool use_quad(int64_t V, int nrhs);
+void launch_quad_lin(hipStream_t st, const EoArgs& a, int prec, bool dag);
+void launch_quad_mp(hipStream_t st, const CgArgs& a, const EoCg* e, int prec);
+void launch_quad_upd(hipStream_t st, const CgArgs& a, const EoCg* e, int prec, bool xfree);
 // kinds of launch_eo_lin: out = POST(PRE(b) + c H in)
 enum { EO_Y = 0, EO_Y_DAG = 1, EO_T = 2, EO_T_DAG = 3, EO_SRC = 4, EO_REC = 5 };
 // etahat = eta_o + kappa H_oe D^{-1} eta_e on the odd sites from the Z4 hash

@@ -282,7 +282,7 @@ tm_status solve_f64_history(tm_ctx* ctx, uint64_t seed_mixed, const uint64_t* id
     a.kappa = ctx->lat.kappa;
     a.twist = ctx->twist;
     a.nrhs = 1;
-    a.npart = (uint32_t)nblk;
+    a.npart = (uint32_t)((g.V + 63) / 64);
     a.p = ws_get(ctx, "h_p", fb, &s);
     a.t = ws_get(ctx, "h_t", fb, &s);
     a.r = ws_get(ctx, "h_r", fb, &s);
@@ -408,7 +408,8 @@ static tm_status solve_block_eo(tm_ctx* ctx, const tsm_solve_params* p, uint64_t
     a.r = ws_get(ctx, tag + "_eo_r", fbc, &s);
     a.x = ws_get(ctx, tag + "_eo_x", field_bytes(hg, xprec, nc), &s);
     void* y = ws_get(ctx, tag + "_eo_y", fbc, &s);
-    a.scal = (CgScal*)ws_get(ctx, tag + "_scal", sizeof(CgScal) * kMaxBlock, &s);
+    CgScal* const scal0 = (CgScal*)ws_get(ctx, tag + "_scal", sizeof(CgScal) * 2 * kMaxBlock, &s);
+    a.scal = scal0;
     const size_t npart_max = partials_per_rhs(g, hg, ctx->eo_ok);
     a.partials = (double*)ws_get(ctx, "partials", sizeof(double) * npart_max * kMaxBlock, &s);
     a.partials2 = (double*)ws_get(ctx, "partials2", sizeof(double) * npart_max * kMaxBlock, &s);
@@ -514,6 +515,11 @@ static tm_status solve_block_eo(tm_ctx* ctx, const tsm_solve_params* p, uint64_t
     ec64.geven = g64e;
     ec64.godd = g64o;
     ec64.y = y64;
+    // merged reductions: the state alternates between two arrays, iteration k
+    // reads array k % 2
+    const bool merged = !rel && !track && !tiles && merge_parts(a.npart, nrhs);
+    const bool quad = !tiles && use_quad(hg.V, nrhs);
+    auto state = [&](int k) { return scal0 + (merged && (k & 1) ? kMaxBlock : 0); };
     const CgArgs a0 = a;
     const int vtag = prof_tag(prec, prec == P_F64 ? 1 : nr, TM_SOLVER_CG_EO, 0, rel);
     const int dflt = rel ? 16 : 8;
@@ -547,6 +553,10 @@ static tm_status solve_block_eo(tm_ctx* ctx, const tsm_solve_params* p, uint64_t
         auto steps = [&](int n) {
             for (int i = 0; i < n; i++) {
                 CgArgs a = a0;  // this iteration's direction slots
+                if (merged) {
+                    a.scal = state(done + i);
+                    a.scal_next = state(done + i + 1);
+                }
                 if (ringm) {
                     a.p = slot(done + i);
                     a.pn = slot(done + i + 1);
@@ -556,23 +566,31 @@ static tm_status solve_block_eo(tm_ctx* ctx, const tsm_solve_params* p, uint64_t
                 prof_begin(ctx, TM_KC_EO_HOP, vtag);
                 if (tiles)
                     launch_eot_y(st, ey, prec, nr, false, a.scal);
+                else if (quad)
+                    launch_quad_lin(st, ey, prec, false);
                 else
                     launch_eo_lin(st, ey, prec, nr, EO_Y);
                 prof_end(ctx, TM_KC_EO_HOP, by.hop);
                 prof_begin(ctx, TM_KC_DSLASH, vtag);
                 if (tiles)
                     launch_eot_mp(st, a, ec, prec, nr, false, a.p, a.t);
+                else if (quad)
+                    launch_quad_mp(st, a, &ec, prec);
                 else
                     launch_eo_mp(st, a, ec, prec, nr);
                 prof_end(ctx, TM_KC_DSLASH, by.mp);
-                prof_begin(ctx, TM_KC_OTHER);
-                launch_cg_alpha(st, a);
-                prof_end(ctx, TM_KC_OTHER, 0.0);
+                if (!merged) {
+                    prof_begin(ctx, TM_KC_OTHER);
+                    launch_cg_alpha(st, a);
+                    prof_end(ctx, TM_KC_OTHER, 0.0);
+                }
                 EoArgs ey2 = lin(0, false, a.t, y, nullptr, 1.0, nrhs);
                 ey2.act = a.scal;
                 prof_begin(ctx, TM_KC_EO_HOP_DAG, vtag);
                 if (tiles)
                     launch_eot_y(st, ey2, prec, nr, true, a.scal);
+                else if (quad)
+                    launch_quad_lin(st, ey2, prec, true);
                 else
                     launch_eo_lin(st, ey2, prec, nr, EO_Y_DAG);
                 prof_end(ctx, TM_KC_EO_HOP_DAG, by.hop);
@@ -580,14 +598,18 @@ static tm_status solve_block_eo(tm_ctx* ctx, const tsm_solve_params* p, uint64_t
                 prof_begin(ctx, TM_KC_DSLASH_UPD, utag);
                 if (tiles)
                     launch_eot_upd(st, a, ec, prec, track ? 1 : nr, track);
+                else if (quad && !track)
+                    launch_quad_upd(st, a, &ec, prec, ringm);
                 else if (ringm)
                     launch_eo_upd_xfree(st, a, ec, prec, track ? 1 : nr, track);
                 else
                     launch_eo_upd(st, a, ec, prec, track ? 1 : nr, track);
                 prof_end(ctx, TM_KC_DSLASH_UPD, by.upd);
-                prof_begin(ctx, TM_KC_OTHER);
-                launch_cg_beta(st, a, track);
-                prof_end(ctx, TM_KC_OTHER, 0.0);
+                if (!merged) {
+                    prof_begin(ctx, TM_KC_OTHER);
+                    launch_cg_beta(st, a, track);
+                    prof_end(ctx, TM_KC_OTHER, 0.0);
+                }
                 if (rel) {
                     // gated on the reliable flag: x64 += x, t64 = Mhat x64,
                     // r = b64 - Mhat^dag t64
@@ -617,7 +639,7 @@ static tm_status solve_block_eo(tm_ctx* ctx, const tsm_solve_params* p, uint64_t
                           "eo|%p|%p|%p|%p|%p|%p|%p|%p|%p|%p|%p|%p|%p|%p|%d|%d|%d|%d|%d|%d|%d|%d|%llx", a0.p, a0.t,
                           a0.r, a0.x, y, a0.rho, (void*)a0.scal, (void*)a0.partials, (void*)a0.partials2, x64, t64,
                           b64, y64, (void*)a0.ahist, prec, nr, (int)track, (int)rel, nrhs, k,
-                          ringm ? done % kRing : -1, (int)tiles, (unsigned long long)ctx->ws_digest);
+                          ringm ? done % kRing : (merged ? done & 1 : -1), (int)tiles, (unsigned long long)ctx->ws_digest);
             auto it = ctx->graphs.find(key);
             if (it == ctx->graphs.end()) {
                 hipGraph_t graph;
@@ -638,6 +660,7 @@ static tm_status solve_block_eo(tm_ctx* ctx, const tsm_solve_params* p, uint64_t
         }
         TM_HIP(hipGetLastError());
         done += k;
+        a.scal = state(done);
         TM_HIP(hipMemcpyAsync(ctx->scal_host, a.scal, sizeof(CgScal) * nrhs, hipMemcpyDeviceToHost, st));
         TM_HIP(hipStreamSynchronize(st));
         n_active = active_count(ctx, nrhs);
@@ -770,13 +793,14 @@ static tm_status solve_block(tm_ctx* ctx, const tsm_solve_params* p, uint64_t se
     a.nrhs = nrhs;
     // time-marching K1 / K2 when a segment length is set for this precision
     a.tseg = march_tseg(ctx, p, nr);
-    a.npart = a.tseg > 0 ? march_partials(g, a.tseg) : (uint32_t)nblk;
+    a.npart = a.tseg > 0 ? march_partials(g, a.tseg) : (uint32_t)((g.V + 63) / 64);
     const size_t npart_max = partials_per_rhs(g, ctx->hgeo, ctx->eo_ok);
     a.p = ws_get(ctx, tag + "_p", fb, &s);
     a.t = ws_get(ctx, tag + "_t", fb, &s);
     a.r = ws_get(ctx, tag + "_r", fb, &s);
     a.x = ws_get(ctx, tag + "_x", fx, &s);
-    a.scal = (CgScal*)ws_get(ctx, tag + "_scal", sizeof(CgScal) * kMaxBlock, &s);
+    CgScal* const scal0 = (CgScal*)ws_get(ctx, tag + "_scal", sizeof(CgScal) * 2 * kMaxBlock, &s);
+    a.scal = scal0;
     a.partials = (double*)ws_get(ctx, "partials", sizeof(double) * npart_max * kMaxBlock, &s);
     a.partials2 = (double*)ws_get(ctx, "partials2", sizeof(double) * npart_max * kMaxBlock, &s);
     if (track) a.rho = ws_get(ctx, tag + "_rho", fb, &s);
@@ -814,6 +838,11 @@ static tm_status solve_block(tm_ctx* ctx, const tsm_solve_params* p, uint64_t se
     prof_end(ctx, TM_KC_OTHER, 0.0);
     TM_HIP(hipGetLastError());
 
+    // merged reductions (as in solve_block_eo)
+    const bool merged = !rel && !track && a.tseg == 0 && merge_parts(a.npart, nrhs);
+    const bool quad = a.tseg == 0 && use_quad(g.V, nrhs);
+    auto state = [&](int k) { return scal0 + (merged && (k & 1) ? kMaxBlock : 0); };
+    const CgArgs a0 = a;
     const int vtag = prof_tag(prec, prec == P_F64 ? 1 : nr, TM_SOLVER_CG, a.tseg);
     const int dflt = rel ? 16 : 8;
     const std::string ckey = chunk_key(p, tag, nrhs);
@@ -832,24 +861,37 @@ static tm_status solve_block(tm_ctx* ctx, const tsm_solve_params* p, uint64_t se
         const CgBytes by = cg_bytes(g, prec, n_active, rel, track);
         auto steps = [&](int n) {
             for (int i = 0; i < n; i++) {
+                CgArgs a = a0;
+                if (merged) {
+                    a.scal = state(done + i);
+                    a.scal_next = state(done + i + 1);
+                }
                 prof_begin(ctx, TM_KC_DSLASH, vtag);
                 if (a.tseg > 0)
                     launch_tm_mp(st, a, prec, nr);
+                else if (quad)
+                    launch_quad_mp(st, a, nullptr, prec);
                 else
                     launch_cg_mp(st, a, prec, nr);
                 prof_end(ctx, TM_KC_DSLASH, by.k1);
-                prof_begin(ctx, TM_KC_OTHER);
-                launch_cg_alpha(st, a);
-                prof_end(ctx, TM_KC_OTHER, 0.0);
+                if (!merged) {
+                    prof_begin(ctx, TM_KC_OTHER);
+                    launch_cg_alpha(st, a);
+                    prof_end(ctx, TM_KC_OTHER, 0.0);
+                }
                 prof_begin(ctx, TM_KC_DSLASH_UPD, track ? prof_tag(prec, 1, TM_SOLVER_CG, a.tseg) : vtag);
                 if (a.tseg > 0)
                     launch_tm_upd(st, a, prec, nr, track);
+                else if (quad && !track)
+                    launch_quad_upd(st, a, nullptr, prec, false);
                 else
                     launch_cg_upd(st, a, prec, nr, track);
                 prof_end(ctx, TM_KC_DSLASH_UPD, by.k2);
-                prof_begin(ctx, TM_KC_OTHER);
-                launch_cg_beta(st, a, track);
-                prof_end(ctx, TM_KC_OTHER, 0.0);
+                if (!merged) {
+                    prof_begin(ctx, TM_KC_OTHER);
+                    launch_cg_beta(st, a, track);
+                    prof_end(ctx, TM_KC_OTHER, 0.0);
+                }
                 if (rel) {
                     prof_begin(ctx, TM_KC_OTHER);
                     launch_rel_flush(st, a, x64, 0);
@@ -867,9 +909,10 @@ static tm_status solve_block(tm_ctx* ctx, const tsm_solve_params* p, uint64_t se
             // the chunk's launches depend only on the buffers and the launch
             // configuration, so one captured graph serves every chunk
             char key[512];
-            std::snprintf(key, sizeof(key), "cg|%p|%p|%p|%p|%p|%p|%p|%p|%p|%p|%p|%p|%d|%d|%d|%d|%d|%d|%d|%llx", a.p,
-                          a.t, a.r, a.x, a.rho, (void*)a.scal, (void*)a.partials, (void*)a.partials2, x64, t64, b64,
-                          (void*)a.eta64, prec, nr, a.tseg, (int)track, (int)rel, nrhs, k,
+            std::snprintf(key, sizeof(key), "cg|%p|%p|%p|%p|%p|%p|%p|%p|%p|%p|%p|%p|%d|%d|%d|%d|%d|%d|%d|%d|%llx", a0.p,
+                          a0.t, a0.r, a0.x, a0.rho, (void*)a0.scal, (void*)a0.partials, (void*)a0.partials2, x64, t64,
+                          b64, (void*)a0.eta64, prec, nr, a0.tseg, (int)track, (int)rel, nrhs, k,
+                          merged ? done & 1 : -1,
                           (unsigned long long)ctx->ws_digest);
             auto it = ctx->graphs.find(key);
             if (it == ctx->graphs.end()) {
@@ -891,6 +934,7 @@ static tm_status solve_block(tm_ctx* ctx, const tsm_solve_params* p, uint64_t se
         }
         TM_HIP(hipGetLastError());
         done += k;
+        a.scal = state(done);
         TM_HIP(hipMemcpyAsync(ctx->scal_host, a.scal, sizeof(CgScal) * nrhs, hipMemcpyDeviceToHost, st));
         TM_HIP(hipStreamSynchronize(st));
         n_active = active_count(ctx, nrhs);
@@ -1135,7 +1179,7 @@ static tm_status contract_all_momenta(tm_ctx* ctx, uint64_t seed, int32_t nsrc, 
 // buffers of the solver path, each rounded to 256 B.  The partial arrays
 // shared by every solve of a call are counted by ws_partials.
 static size_t ws_block(const Geom& g, const Geom& hg, const tsm_solve_params* p, int nc) {
-    const size_t scal = align256(sizeof(CgScal) * kMaxBlock);
+    const size_t scal = align256(sizeof(CgScal) * 2 * kMaxBlock);
     const int prec = p->prec;
     const bool rel = p->reliable != 0;
     const bool track = p->stop == TM_STOP_TRUE && !rel;

@@ -235,11 +235,25 @@ __device__ __forceinline__ void diag_combine(const cx<R> p[12], const cx<R> acc[
         out[k] = {p[k].re - kappa * acc[k].re + tw * p[k].im, p[k].im - kappa * acc[k].im - tw * p[k].re};
 }
 
+// The values as they are here, in FP32 or FP64: a following rounding to FP16 is
+// then a rounding of them (the compiler may otherwise round to FP16 within the
+// last multiply-add, of some components and not of others, which the kernels of
+// different lane widths do not share).
+template <int N, typename R>
+__device__ __forceinline__ void settle(cx<R>* v) {
+#pragma unroll
+    for (int k = 0; k < N; k++) asm("" : "+v"(v[k].re), "+v"(v[k].im));
+}
+
+// (explicit FMAs: the same sum in every kernel)
 template <typename R>
 __device__ __forceinline__ double spinor_norm2(const cx<R> v[12]) {
     double s = 0;
 #pragma unroll
-    for (int k = 0; k < 12; k++) s += (double)v[k].re * (double)v[k].re + (double)v[k].im * (double)v[k].im;
+    for (int k = 0; k < 12; k++) {
+        s = fma((double)v[k].re, (double)v[k].re, s);
+        s = fma((double)v[k].im, (double)v[k].im, s);
+    }
     return s;
 }
 
