@@ -57,6 +57,9 @@ struct tm_ctx {
     // the keys of captured graphs, which hold buffer addresses)
     uint64_t ws_digest = 0;
 
+    // pinned staging of large results (copy_out; allocated by the first one,
+    // kept until tm_destroy)
+    char* out_stage = nullptr;
     tmq::CgScal* scal_host = nullptr;  // pinned mirror for stop checks
     int scal_host_n = 0;
     // device memory of the network weight fragments (TM_NET_MAX_LAYERS layers,
@@ -163,6 +166,10 @@ tm_status copy_sync(tm_ctx* ctx, void* dst, const void* src, size_t bytes, hipMe
         const tm_status cs_ = ::tmq::copy_sync(ctx, (dst), (src), (bytes), (kind)); \
         if (cs_ != TM_OK) return cs_;                                           \
     } while (0)
+
+// Results to the caller's (pageable) memory, after all work queued on the
+// context's stream; waits.
+tm_status copy_out(tm_ctx* ctx, void* dst_host, const void* src_dev, size_t bytes);
 
 // instrumentation around a launch of kernel class kc moving `bytes`
 // tag: prof_tag(prec, lane_rhs, solver) of the launched kernel, -1 if none

@@ -1167,9 +1167,7 @@ static tm_status contract_all_momenta(tm_ctx* ctx, uint64_t seed, int32_t nsrc, 
         prof_end(ctx, TM_KC_CONTRACT, (double)g.V * nb * (24.0 * 8 + 5 * 16 * 16.0));
         TM_HIP(hipGetLastError());
     }
-    TM_HIP(hipMemcpyAsync(loops_host, out, sizeof(double) * 2 * nl * nsrc, hipMemcpyDeviceToHost, st));
-    TM_HIP(hipStreamSynchronize(st));
-    return TM_OK;
+    return copy_out(ctx, loops_host, out, sizeof(double) * 2 * nl * nsrc);
 }
 
 // ---- workspace bounds (tm_workspace_bytes) ----
@@ -1400,9 +1398,7 @@ tm_status tsm_contract_est(tm_ctx* ctx, int32_t estimator, uint64_t seed, int32_
                        nullptr, canon);
         TM_HIP(hipGetLastError());
     }
-    TM_HIP(hipMemcpyAsync(loops_host, out, sizeof(double) * 2 * nl * nsrc, hipMemcpyDeviceToHost, ctx->stream));
-    TM_HIP(hipStreamSynchronize(ctx->stream));
-    return TM_OK;
+    return copy_out(ctx, loops_host, out, sizeof(double) * 2 * nl * nsrc);
 }
 
 tm_status tsm_loops(tm_ctx* ctx, const tsm_params* P, double* loops_host, double* err_host, double* per_source_host,
@@ -1515,8 +1511,9 @@ tm_status tsm_loops(tm_ctx* ctx, const tsm_params* P, double* loops_host, double
     auto t2 = clk::now();
     TM_COPY(loops_host, fin, sizeof(double) * 2 * 3 * nl, hipMemcpyDeviceToHost);
     if (err_host) TM_COPY(err_host, fin + 2 * 3 * nl, sizeof(double) * 2 * 3 * nl, hipMemcpyDeviceToHost);
-    if (per_source_host && N > 0)
-        TM_COPY(per_source_host, ps, sizeof(double) * 2 * 2 * nl * N, hipMemcpyDeviceToHost);
+    if (per_source_host && N > 0) {
+        if ((s = copy_out(ctx, per_source_host, ps, sizeof(double) * 2 * 2 * nl * N)) != TM_OK) return s;
+    }
     rs.ms_hp_phase = std::chrono::duration<double, std::milli>(t1 - t0).count();
     rs.ms_lp_phase = std::chrono::duration<double, std::milli>(t2 - t1).count();
     if (run_stats) *run_stats = rs;
