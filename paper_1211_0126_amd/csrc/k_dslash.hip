@@ -191,9 +191,10 @@ __global__ __launch_bounds__(256) void k_cg_beta(CgArgs a, uint32_t nb) {
     if (threadIdx.x == 0) cg_finish_step(a.scal[r], rrn, rhon);
 }
 
-// K2: q = M^dag t, r -= alpha q, x += alpha p (x of storage X), |r|^2,
+// K2: q = M^dag t, r -= alpha q, x += alpha p (x of storage X; XFREE: none, the
+// directions are kept), |r|^2,
 // optionally rho -= alpha t (recursive true residual)
-template <typename R, class S, class G, class X, typename RX, int NR, bool TRACK>
+template <typename R, class S, class G, class X, typename RX, int NR, bool TRACK, bool XFREE = false>
 __global__ TM_STENCIL_R(NR, R) void k_cg_upd(CgArgs a) {
     const BlockMap bm = stencil_block((uint32_t)(a.nrhs / NR));
     const uint32_t ws = bm.sb * 4u + (threadIdx.x >> 6), nws = (uint32_t)((a.geo.V + 63) / 64);
@@ -235,14 +236,16 @@ __global__ TM_STENCIL_R(NR, R) void k_cg_upd(CgArgs a) {
             round_storage<S, R>(rv);
             store_spinor_cp<S, R, TM_CP_K2>(rp, Vs, s, rv);
             prr[r] = spinor_norm2(rv);
-            load_spinor_cp<S, R, TM_CP_K2>(field_rhs<S>(a.p, Vs, r0 + r), Vs, s, pv);
-            cx<RX> xv[12];
-            void* xp = field_rhs<X>(a.x, Vs, r0 + r);
-            load_spinor_cp<X, RX, TM_CP_K2>(xp, Vs, s, xv);
-            const RX alx = (RX)alpha;
+            if (!XFREE) {
+                load_spinor_cp<S, R, TM_CP_K2>(field_rhs<S>(a.p, Vs, r0 + r), Vs, s, pv);
+                cx<RX> xv[12];
+                void* xp = field_rhs<X>(a.x, Vs, r0 + r);
+                load_spinor_cp<X, RX, TM_CP_K2>(xp, Vs, s, xv);
+                const RX alx = (RX)alpha;
 #pragma unroll
-            for (int k = 0; k < 12; k++) xv[k] = {xv[k].re + alx * (RX)pv[k].re, xv[k].im + alx * (RX)pv[k].im};
-            store_spinor_cp<X, RX, TM_CP_K2>(xp, Vs, s, xv);
+                for (int k = 0; k < 12; k++) xv[k] = {xv[k].re + alx * (RX)pv[k].re, xv[k].im + alx * (RX)pv[k].im};
+                store_spinor_cp<X, RX, TM_CP_K2>(xp, Vs, s, xv);
+            }
             if (TRACK) {
                 cx<R> rh[12];
                 void* hp = field_rhs<S>(a.rho, Vs, r0 + r);
@@ -346,6 +349,7 @@ __device__ inline void cg_start(CgScal& q, double bb, double ee) {
     q.rflag = 0;
     q.n_reliable = 0;
     q.alpha = q.beta = 0;
+    q.kf = q.xacc = 0;
     if (bb <= 0 || 1.0 <= q.tol2) {
         q.status = 1;
     } else if (q.maxit == 0) {
@@ -393,7 +397,7 @@ __global__ __launch_bounds__(256) void k_rel_init(CgArgs a, const void* b64, voi
         }
         store_spinor<S, float>(field_rhs<S>(a.r, Vs, r), Vs, s, rf);
         store_spinor<S, float>(field_rhs<S>(a.p, Vs, r), Vs, s, rf);
-        store_spinor<SF32, float>(field_rhs<SF32>(a.x, Vs, r), Vs, s, zf);
+        if (!a.ring) store_spinor<SF32, float>(field_rhs<SF32>(a.x, Vs, r), Vs, s, zf);
         store_spinor<SF64, double>(field_rhs<SF64>(x64, Vs, r), Vs, s, z);
     }
     double v = block_sum256(pb, sh);
@@ -496,6 +500,8 @@ __global__ __launch_bounds__(256) void k_rel_fin(CgArgs a, uint32_t nb) {
         q.maxrr = q.rr;
         q.sigma = sn;
         q.rflag = 0;
+        q.kf = q.iters;  // (kept directions: x64 has them all)
+        q.xacc = 0;
         q.n_reliable += 1;
         if (q.stop == 1) q.rho2 = rho2;
         if (q.stop == 1 ? rho2 <= q.tol2 * q.ee : rrn <= q.tol2 * q.bb) {
@@ -701,26 +707,40 @@ static void cg_mp_typed(hipStream_t st, const CgArgs& a, int nr) {
     }
 }
 
-template <typename R, class S, class G, class X, typename RX>
-static void cg_upd_typed(hipStream_t st, const CgArgs& a, int nr, bool track) {
+template <typename R, class S, class G, class X, typename RX, bool XFREE>
+static void cg_upd_x(hipStream_t st, const CgArgs& a, int nr, bool track) {
     const Geom& g = a.geo;
     if (track) {
-        hipLaunchKernelGGL((k_cg_upd<R, S, G, X, RX, 1, true>), stencil_grid(g, a.nrhs), dim3(256), 0, st, a);
-    } else if constexpr (sizeof(R) == 8) {
-        hipLaunchKernelGGL((k_cg_upd<R, S, G, X, RX, 1, false>), stencil_grid(g, a.nrhs), dim3(256), 0, st, a);
-    } else {
-        switch (nr) {
-        case 4:
-            hipLaunchKernelGGL((k_cg_upd<R, S, G, X, RX, 4, false>), stencil_grid(g, a.nrhs / 4), dim3(256), 0, st, a);
-            break;
-        case 2:
-            hipLaunchKernelGGL((k_cg_upd<R, S, G, X, RX, 2, false>), stencil_grid(g, a.nrhs / 2), dim3(256), 0, st, a);
-            break;
-        default:
-            hipLaunchKernelGGL((k_cg_upd<R, S, G, X, RX, 1, false>), stencil_grid(g, a.nrhs), dim3(256), 0, st, a);
-            break;
+        hipLaunchKernelGGL((k_cg_upd<R, S, G, X, RX, 1, true, XFREE>), stencil_grid(g, a.nrhs), dim3(256), 0, st, a);
+        return;
+    }
+    if constexpr (sizeof(R) == 8) nr = 1;
+    switch (nr) {
+    case 4:
+        if constexpr (sizeof(R) == 4)
+            hipLaunchKernelGGL((k_cg_upd<R, S, G, X, RX, 4, false, XFREE>), stencil_grid(g, a.nrhs / 4), dim3(256), 0,
+                               st, a);
+        break;
+    case 2:
+        if constexpr (sizeof(R) == 4)
+            hipLaunchKernelGGL((k_cg_upd<R, S, G, X, RX, 2, false, XFREE>), stencil_grid(g, a.nrhs / 2), dim3(256), 0,
+                               st, a);
+        break;
+    default:
+        hipLaunchKernelGGL((k_cg_upd<R, S, G, X, RX, 1, false, XFREE>), stencil_grid(g, a.nrhs), dim3(256), 0, st, a);
+        break;
+    }
+}
+// without the x update where the directions are kept (16-bit storage)
+template <typename R, class S, class G, class X, typename RX>
+static void cg_upd_typed(hipStream_t st, const CgArgs& a, int nr, bool track) {
+    if constexpr (S::NV == 3) {
+        if (a.ring) {
+            cg_upd_x<R, S, G, X, RX, true>(st, a, nr, track);
+            return;
         }
     }
+    cg_upd_x<R, S, G, X, RX, false>(st, a, nr, track);
 }
 
 template <typename R, class S>

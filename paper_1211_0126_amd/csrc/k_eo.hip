@@ -420,6 +420,73 @@ __global__ __launch_bounds__(256) void k_eo_xflush(CgArgs a, const void* dirs, s
     store_spinor_cp<XO, float, kStream>(field_rhs<XO>(out, Vs, r), Vs, h, xv);
 }
 
+// Kept directions with reliable updates (a.geo either lattice): each source
+// counts its own (CgScal::kf, xacc).  x32 (+)= sum of those not yet in x, before
+// the ring overwrites them (k_ring_fin then counts them as done) ...
+template <class S>
+__device__ __forceinline__ void ring_sum(const CgArgs& a, const CgScal& q, const void* dirs, size_t slot_bytes, int r,
+                                         uint32_t h, cx<float> xv[12]) {
+    const long Vs = a.geo.Vs;
+    if (q.xacc) {
+        load_spinor_cp<SF32, float, kStream>(field_rhs<SF32>(a.x, Vs, r), Vs, h, xv);
+    } else {
+#pragma unroll
+        for (int c = 0; c < 12; c++) xv[c] = {0.f, 0.f};
+    }
+    for (int k = q.kf; k < q.iters; k++) {
+        const float al = (float)a.ahist[(size_t)r * a.ring + (k % a.ring)];
+        cx<float> pv[12];
+        load_spinor_cp<S, float, kStream>(field_rhs<S>((const char*)dirs + (size_t)(k % a.ring) * slot_bytes, Vs, r), Vs,
+                                          h, pv);
+#pragma unroll
+        for (int c = 0; c < 12; c++) xv[c] = {xv[c].re + al * pv[c].re, xv[c].im + al * pv[c].im};
+    }
+}
+template <class S>
+__global__ __launch_bounds__(256) void k_ring_add(CgArgs a, const void* dirs, size_t slot_bytes) {
+    const uint32_t h = blockIdx.x * 256u + threadIdx.x;
+    const int r = blockIdx.y;
+    const CgScal& q = a.scal[r];
+    if (h >= a.geo.V || q.kf >= q.iters) return;
+    cx<float> xv[12];
+    ring_sum<S>(a, q, dirs, slot_bytes, r, h, xv);
+    store_spinor_cp<SF32, float, kStream>(field_rhs<SF32>(a.x, a.geo.Vs, r), a.geo.Vs, h, xv);
+}
+__global__ void k_ring_fin(CgArgs a) {
+    const int r = threadIdx.x;
+    if (r >= a.nrhs) return;
+    CgScal& q = a.scal[r];
+    if (q.kf < q.iters) {
+        q.kf = q.iters;
+        q.xacc = 1;
+    }
+}
+// ... and x64 += sigma times the whole, where the reliable flag is set (or
+// always if force); k_rel_fin then counts them as done.  The x32 of a cycle is
+// summed in the same order as if it were updated each iteration.
+template <class S>
+__global__ __launch_bounds__(256) void k_ring_rel_flush(CgArgs a, const void* dirs, size_t slot_bytes, void* x64,
+                                                        int force) {
+    const int r = blockIdx.y;
+    const CgScal& q = a.scal[r];
+    if ((!force && !q.rflag) || (!q.xacc && q.kf >= q.iters)) return;
+    const long Vs = a.geo.Vs;
+    const uint32_t nsb = (uint32_t)((a.geo.V + 255) / 256);
+    void* xdp = field_rhs<SF64>(x64, Vs, r);
+    const double sg = q.sigma;
+    for (uint32_t sb = blockIdx.x; sb < nsb; sb += gridDim.x) {
+        const uint32_t h = sb * 256u + threadIdx.x;
+        if (h >= a.geo.V) continue;
+        cx<float> xv[12];
+        ring_sum<S>(a, q, dirs, slot_bytes, r, h, xv);
+        cx<double> xd[12];
+        load_spinor<SF64, double>(xdp, Vs, h, xd);
+#pragma unroll
+        for (int k = 0; k < 12; k++) xd[k] = {xd[k].re + sg * (double)xv[k].re, xd[k].im + sg * (double)xv[k].im};
+        store_spinor<SF64, double>(xdp, Vs, h, xd);
+    }
+}
+
 // Reliable update (gated, FP64): r64 = b64 - (D^dag t64 - kappa^2 H_oe^dag
 // y64) with t64 = Mhat x64 and y64 = D^{-dag} H_eo^dag t64, r32 = r64, block
 // partials of |r64|^2 and (a.eta64 = etahat set) of |etahat - t64|^2; NR
@@ -769,6 +836,24 @@ void launch_eo_xflush(hipStream_t st, const CgArgs& a, int prec, const void* dir
         eo_xflush_out<SF16>(st, a, prec, dirs, slot_bytes, k0, k1, out);
     else
         eo_xflush_out<SF32>(st, a, prec, dirs, slot_bytes, k0, k1, out);
+}
+
+// kept directions with reliable updates, 16-bit storage
+void launch_ring_add(hipStream_t st, const CgArgs& a, int prec, const void* dirs, size_t slot_bytes) {
+    const dim3 grid(eo_blocks(a.geo), (unsigned)a.nrhs);
+    if (prec == P_F16)
+        hipLaunchKernelGGL(k_ring_add<SF16>, grid, dim3(256), 0, st, a, dirs, slot_bytes);
+    else
+        hipLaunchKernelGGL(k_ring_add<SBF16>, grid, dim3(256), 0, st, a, dirs, slot_bytes);
+    hipLaunchKernelGGL(k_ring_fin, dim3(1), dim3(64), 0, st, a);
+}
+void launch_ring_rel_flush(hipStream_t st, const CgArgs& a, int prec, const void* dirs, size_t slot_bytes, void* x64,
+                           int force) {
+    const dim3 grid(std::min(eo_blocks(a.geo), 512u), (unsigned)a.nrhs);
+    if (prec == P_F16)
+        hipLaunchKernelGGL(k_ring_rel_flush<SF16>, grid, dim3(256), 0, st, a, dirs, slot_bytes, x64, force);
+    else
+        hipLaunchKernelGGL(k_ring_rel_flush<SBF16>, grid, dim3(256), 0, st, a, dirs, slot_bytes, x64, force);
 }
 
 void launch_eo_mp(hipStream_t st, const CgArgs& a, const EoCg& e, int prec, int nr) {

@@ -420,7 +420,7 @@ static void quad_mp_typed(hipStream_t st, const CgArgs& a, const EoCg& e) {
 }
 template <bool EO, typename R, class S, class G, class X, typename RX>
 static void quad_upd_typed(hipStream_t st, const CgArgs& a, const EoCg& e, bool xfree) {
-    if constexpr (EO && sizeof(R) == 4) {
+    if constexpr (EO ? sizeof(R) == 4 : S::NV == 3) {
         if (xfree) {
             hipLaunchKernelGGL((k_quad_upd<EO, R, S, G, X, RX, true>), quad_grid(a.geo, a.nrhs), dim3(256), 0, st, a, e);
             return;

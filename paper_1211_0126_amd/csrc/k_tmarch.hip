@@ -182,9 +182,9 @@ __global__ TM_MARCH_R(NR, R) void k_tm_mp(CgArgs a) {
     }
 }
 
-// K2: q = M^dag t, r -= alpha q, x += alpha p (x of storage X), block
+// K2: q = M^dag t, r -= alpha q, x += alpha p (x of storage X; XFREE: none), block
 // partials of |r|^2, optionally rho -= alpha t and its norm
-template <typename R, class S, class G, class X, typename RX, int NR, bool TRACK>
+template <typename R, class S, class G, class X, typename RX, int NR, bool TRACK, bool XFREE = false>
 __global__ TM_MARCH_R(NR, R) void k_tm_upd(CgArgs a) {
     __shared__ double sh[4];
     const Geom& g = a.geo;
@@ -229,15 +229,17 @@ __global__ TM_MARCH_R(NR, R) void k_tm_upd(CgArgs a) {
                     round_storage<S, R>(rv);
                     store_spinor_cp<S, R, TM_CP_K2>(rp, Vs, s, rv);
                     prr[r] += spinor_norm2(rv);
-                    cx<R> pv[12];
-                    load_spinor_cp<S, R, TM_CP_K2>(field_rhs<S>(a.p, Vs, r0 + r), Vs, s, pv);
-                    cx<RX> xv[12];
-                    void* xp = field_rhs<X>(a.x, Vs, r0 + r);
-                    load_spinor_cp<X, RX, TM_CP_K2>(xp, Vs, s, xv);
+                    if (!XFREE) {
+                        cx<R> pv[12];
+                        load_spinor_cp<S, R, TM_CP_K2>(field_rhs<S>(a.p, Vs, r0 + r), Vs, s, pv);
+                        cx<RX> xv[12];
+                        void* xp = field_rhs<X>(a.x, Vs, r0 + r);
+                        load_spinor_cp<X, RX, TM_CP_K2>(xp, Vs, s, xv);
 #pragma unroll
-                    for (int k = 0; k < 12; k++)
-                        xv[k] = {xv[k].re + alx[r] * (RX)pv[k].re, xv[k].im + alx[r] * (RX)pv[k].im};
-                    store_spinor_cp<X, RX, TM_CP_K2>(xp, Vs, s, xv);
+                        for (int k = 0; k < 12; k++)
+                            xv[k] = {xv[k].re + alx[r] * (RX)pv[k].re, xv[k].im + alx[r] * (RX)pv[k].im};
+                        store_spinor_cp<X, RX, TM_CP_K2>(xp, Vs, s, xv);
+                    }
                     if (TRACK) {
                         cx<R> tc[12], rh[12];
                         load_spinor<S, R>(field_rhs<S>(a.t, Vs, r0 + r), Vs, s, tc);
@@ -389,21 +391,30 @@ static void tm_mp_typed(hipStream_t st, const CgArgs& a, int nr) {
     }
 }
 
-template <typename R, class S, class G, class X, typename RX>
-static void tm_upd_typed(hipStream_t st, const CgArgs& a, int nr, bool track) {
+template <typename R, class S, class G, class X, typename RX, bool XFREE>
+static void tm_upd_x(hipStream_t st, const CgArgs& a, int nr, bool track) {
     const unsigned nb = march_partials(a.geo, a.tseg);
     if (track) {
-        hipLaunchKernelGGL((k_tm_upd<R, S, G, X, RX, 1, true>), dim3(nb * a.nrhs), dim3(256), 0, st, a);
+        hipLaunchKernelGGL((k_tm_upd<R, S, G, X, RX, 1, true, XFREE>), dim3(nb * a.nrhs), dim3(256), 0, st, a);
         return;
     }
-    if constexpr (sizeof(R) == 8) {
-        hipLaunchKernelGGL((k_tm_upd<R, S, G, X, RX, 1, false>), dim3(nb * a.nrhs), dim3(256), 0, st, a);
-    } else {
-        if (nr == 2)
-            hipLaunchKernelGGL((k_tm_upd<R, S, G, X, RX, 2, false>), dim3(nb * (a.nrhs / 2)), dim3(256), 0, st, a);
-        else
-            hipLaunchKernelGGL((k_tm_upd<R, S, G, X, RX, 1, false>), dim3(nb * a.nrhs), dim3(256), 0, st, a);
+    if constexpr (sizeof(R) == 4) {
+        if (nr == 2) {
+            hipLaunchKernelGGL((k_tm_upd<R, S, G, X, RX, 2, false, XFREE>), dim3(nb * (a.nrhs / 2)), dim3(256), 0, st, a);
+            return;
+        }
     }
+    hipLaunchKernelGGL((k_tm_upd<R, S, G, X, RX, 1, false, XFREE>), dim3(nb * a.nrhs), dim3(256), 0, st, a);
+}
+template <typename R, class S, class G, class X, typename RX>
+static void tm_upd_typed(hipStream_t st, const CgArgs& a, int nr, bool track) {
+    if constexpr (S::NV == 3) {
+        if (a.ring) {
+            tm_upd_x<R, S, G, X, RX, true>(st, a, nr, track);
+            return;
+        }
+    }
+    tm_upd_x<R, S, G, X, RX, false>(st, a, nr, track);
 }
 
 template <class S>

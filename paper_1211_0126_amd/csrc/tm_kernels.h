@@ -171,6 +171,9 @@ void launch_eo_upd(hipStream_t st, const CgArgs& a, const EoCg& e, int prec, int
 // of the source), p_k in slot k % ring of `dirs` (slot_bytes apart)
 void launch_eo_upd_xfree(hipStream_t st, const CgArgs& a, const EoCg& e, int prec, int nr, bool track);
 // (the sum is written to out in out_prec, P_F32 or P_F16; out nullptr: a.x)
+void launch_ring_add(hipStream_t st, const CgArgs& a, int prec, const void* dirs, size_t slot_bytes);
+void launch_ring_rel_flush(hipStream_t st, const CgArgs& a, int prec, const void* dirs, size_t slot_bytes, void* x64,
+                           int force);
 void launch_eo_xflush(hipStream_t st, const CgArgs& a, int prec, const void* dirs, size_t slot_bytes, int k0, int k1,
                       void* out = nullptr, int out_prec = P_F32);
 uint32_t eo_gated_blocks(const Geom& hg);

@@ -21,8 +21,14 @@
 namespace tmq {
 
 static const int kIterCap = 20000;  // safety cap for max_iter = -1
-// search directions kept by the even-odd CG without reliable updates
+// Search directions kept instead of updating x each iteration (which reads p
+// and reads and writes the FP32 x): the even-odd CG in every storage but FP64,
+// with reliable updates and on the whole lattice in 16-bit storage (where x is
+// four times a direction).  A reliable cycle takes about ten iterations, so
+// that with 16 the directions mostly go straight into x64.
 constexpr int kEoRing = 8;
+constexpr int kRelRing = 16;
+static bool half_storage(int prec) { return prec == P_F16 || prec == P_BF16; }
 // sources per launch of the FP32 solution reconstruction (a multiple of every
 // right-hand-sides-per-lane setting)
 constexpr int kRecSub = 8;
@@ -133,14 +139,13 @@ static void remember_chunk(tm_ctx* ctx, const std::string& key, int nrhs) {
 struct CgBytes {
     double k1, k2, k3;
 };
-static CgBytes cg_bytes(const Geom& g, int prec, int nrhs, bool reliable_x64, bool track) {
+static CgBytes cg_bytes(const Geom& g, int prec, int nrhs, bool xfree, bool track) {
     const double bs = prec == P_F64 ? 8 : (prec == P_F32 ? 4 : 2);
     const double bx = prec == P_F64 ? 8 : 4;
     const double gb = prec == P_F64 ? 4 * 18 * 8 : 4 * 12 * 4;
-    (void)reliable_x64;
     CgBytes b;
     b.k1 = (double)g.V * (nrhs * 48.0 * bs + gb);
-    b.k2 = (double)g.V * (nrhs * (24.0 * bs + 48.0 * bs + 24.0 * bs + 48.0 * bx + (track ? 48.0 * bs : 0.0)) + gb);
+    b.k2 = (double)g.V * (nrhs * (72.0 * bs + (xfree ? 0.0 : 24.0 * bs + 48.0 * bx) + (track ? 48.0 * bs : 0.0)) + gb);
     b.k3 = (double)g.V * nrhs * 72.0 * bs;
     return b;
 }
@@ -392,8 +397,8 @@ static tm_status solve_block_eo(tm_ctx* ctx, const tsm_solve_params* p, uint64_t
     // search directions in a ring (CgArgs::pn): without reliable updates, on
     // the lane-per-site kernels; x is formed from the step lengths every
     // kRing - 1 iterations and at the end
-    const bool ringm = !rel && prec != P_F64 && !tiles;
-    constexpr int kRing = kEoRing;
+    const bool ringm = !tiles && (rel ? half_storage(prec) : prec != P_F64);
+    const int kRing = rel ? kRelRing : kEoRing;
     void* dirs = nullptr;
     if (ringm) {
         dirs = ws_get(ctx, tag + "_eo_dirs", fbc * kRing, &s);
@@ -536,7 +541,10 @@ static tm_status solve_block_eo(tm_ctx* ctx, const tsm_solve_params* p, uint64_t
     auto flush = [&](int k1) {
         if (k1 > k0) {
             prof_begin(ctx, TM_KC_OTHER);
-            launch_eo_xflush(st, a, prec, dirs, fbh, k0, k1);
+            if (rel)
+                launch_ring_add(st, a, prec, dirs, fbh);
+            else
+                launch_eo_xflush(st, a, prec, dirs, fbh, k0, k1);
             prof_end(ctx, TM_KC_OTHER, 0.0);
         }
         k0 = k1;
@@ -614,7 +622,10 @@ static tm_status solve_block_eo(tm_ctx* ctx, const tsm_solve_params* p, uint64_t
                     // gated on the reliable flag: x64 += x, t64 = Mhat x64,
                     // r = b64 - Mhat^dag t64
                     prof_begin(ctx, TM_KC_OTHER);
-                    launch_rel_flush(st, a, x64, 0);
+                    if (ringm)
+                        launch_ring_rel_flush(st, a, prec, dirs, fbh, x64, 0);
+                    else
+                        launch_rel_flush(st, a, x64, 0);
                     EoArgs e1 = lin(0, true, x64, y64, nullptr, 1.0, nrhs);
                     e1.gate = a.scal;
                     launch_eo_lin(st, e1, P_F64, nr64, EO_Y);
@@ -677,7 +688,7 @@ static tm_status solve_block_eo(tm_ctx* ctx, const tsm_solve_params* p, uint64_t
         launch_eo_xflush(st, a, prec, dirs, fbh, k0, done, y, P_F16);
         prof_end(ctx, TM_KC_OTHER, 0.0);
         k0 = done;
-    } else if (ringm) {
+    } else if (ringm && !rel) {
         flush(done);
     }
 
@@ -722,7 +733,10 @@ static tm_status solve_block_eo(tm_ctx* ctx, const tsm_solve_params* p, uint64_t
         return TM_OK;
     }
     if (rel) {
-        launch_rel_flush(st, a, x64, 1);
+        if (ringm)
+            launch_ring_rel_flush(st, a, prec, dirs, fbh, x64, 1);
+        else
+            launch_rel_flush(st, a, x64, 1);
         launch_eo_rec_full(st, lin(0, true, x64, nullptr, nullptr, kappa, nrhs), P_F64, nr64, g, xfull);
     } else if (tiles) {
         launch_eot_rec(st, lin(0, false, a.x, nullptr, nullptr, kappa, nrhs), nr, g, xfull);
@@ -795,7 +809,20 @@ static tm_status solve_block(tm_ctx* ctx, const tsm_solve_params* p, uint64_t se
     a.tseg = march_tseg(ctx, p, nr);
     a.npart = a.tseg > 0 ? march_partials(g, a.tseg) : (uint32_t)((g.V + 63) / 64);
     const size_t npart_max = partials_per_rhs(g, ctx->hgeo, ctx->eo_ok);
-    a.p = ws_get(ctx, tag + "_p", fb, &s);
+    // directions in a ring, as in solve_block_eo
+    const bool ringm = !rel && half_storage(prec);
+    const int kRing = kEoRing;
+    void* dirs = nullptr;
+    if (ringm) {
+        dirs = ws_get(ctx, tag + "_dirs", fb * kRing, &s);
+        a.ahist = (double*)ws_get(ctx, tag + "_ahist", sizeof(double) * kMaxBlock * kRing, &s);
+        a.ring = kRing;
+        a.p = dirs;
+    } else {
+        a.p = ws_get(ctx, tag + "_p", fb, &s);
+    }
+    const size_t slot_bytes = field_bytes(g, prec, nrhs);
+    auto slot = [&](int k) { return (void*)((char*)dirs + (size_t)(k % kRing) * slot_bytes); };
     a.t = ws_get(ctx, tag + "_t", fb, &s);
     a.r = ws_get(ctx, tag + "_r", fb, &s);
     a.x = ws_get(ctx, tag + "_x", fx, &s);
@@ -833,7 +860,9 @@ static tm_status solve_block(tm_ctx* ctx, const tsm_solve_params* p, uint64_t se
     } else {
         launch_noise_native(st, g, prec, seed_mixed, ids_dev, nrhs, eta);
         launch_apply(st, g, prec, a.gauge, ctx->lat.kappa, ctx->twist, 1, nrhs, eta, a.r, nr, nullptr);
-        launch_cg_init(st, a, prec, track, eta);
+        CgArgs ai = a;
+        if (ringm) ai.x = nullptr;  // (written by the first pass over the kept directions)
+        launch_cg_init(st, ai, prec, track, eta);
     }
     prof_end(ctx, TM_KC_OTHER, 0.0);
     TM_HIP(hipGetLastError());
@@ -854,14 +883,29 @@ static tm_status solve_block(tm_ctx* ctx, const tsm_solve_params* p, uint64_t se
         n_active = active_count(ctx, nrhs);
     }
     int done = 0;
+    int k0 = 0;  // ring: first iteration not yet added to x
+    auto flush = [&](int k1) {
+        prof_begin(ctx, TM_KC_OTHER);
+        launch_eo_xflush(st, a, prec, dirs, slot_bytes, k0, k1);
+        prof_end(ctx, TM_KC_OTHER, 0.0);
+        k0 = k1;
+    };
     for (;;) {
         int k = chunk;
         if (p->max_iter >= 0) k = std::max(1, std::min(chunk, p->max_iter - done));
         chunk = later_chunk(ctx, dflt);
-        const CgBytes by = cg_bytes(g, prec, n_active, rel, track);
+        if (ringm) {
+            if (done - k0 >= kRing - 1) flush(done);
+            k = std::min(k, kRing - 1 - (done - k0));
+        }
+        const CgBytes by = cg_bytes(g, prec, n_active, ringm, track);
         auto steps = [&](int n) {
             for (int i = 0; i < n; i++) {
                 CgArgs a = a0;
+                if (ringm) {
+                    a.p = slot(done + i);
+                    a.pn = slot(done + i + 1);
+                }
                 if (merged) {
                     a.scal = state(done + i);
                     a.scal_next = state(done + i + 1);
@@ -883,7 +927,7 @@ static tm_status solve_block(tm_ctx* ctx, const tsm_solve_params* p, uint64_t se
                 if (a.tseg > 0)
                     launch_tm_upd(st, a, prec, nr, track);
                 else if (quad && !track)
-                    launch_quad_upd(st, a, nullptr, prec, false);
+                    launch_quad_upd(st, a, nullptr, prec, ringm);
                 else
                     launch_cg_upd(st, a, prec, nr, track);
                 prof_end(ctx, TM_KC_DSLASH_UPD, by.k2);
@@ -912,7 +956,7 @@ static tm_status solve_block(tm_ctx* ctx, const tsm_solve_params* p, uint64_t se
             std::snprintf(key, sizeof(key), "cg|%p|%p|%p|%p|%p|%p|%p|%p|%p|%p|%p|%p|%d|%d|%d|%d|%d|%d|%d|%d|%llx", a0.p,
                           a0.t, a0.r, a0.x, a0.rho, (void*)a0.scal, (void*)a0.partials, (void*)a0.partials2, x64, t64,
                           b64, (void*)a0.eta64, prec, nr, a0.tseg, (int)track, (int)rel, nrhs, k,
-                          merged ? done & 1 : -1,
+                          ringm ? done % kRing : (merged ? done & 1 : -1),
                           (unsigned long long)ctx->ws_digest);
             auto it = ctx->graphs.find(key);
             if (it == ctx->graphs.end()) {
@@ -942,6 +986,7 @@ static tm_status solve_block(tm_ctx* ctx, const tsm_solve_params* p, uint64_t se
         if (done >= kIterCap) break;
     }
     remember_chunk(ctx, ckey, nrhs);
+    if (ringm) flush(done);
     if (rel) {
         launch_rel_flush(st, a, x64, 1);
         res->x = x64;
@@ -1189,9 +1234,8 @@ static size_t ws_block(const Geom& g, const Geom& hg, const tsm_solve_params* p,
     if (p->solver == TM_SOLVER_CG_EO) {
         const int xprec = prec == P_F64 ? P_F64 : P_F32;
         const size_t fb = align256(field_bytes(hg, prec, nc));
-        const bool ring = !rel && prec != P_F64;
-        size_t b = ring ? align256(field_bytes(hg, prec, nc) * kEoRing) + align256(sizeof(double) * kMaxBlock * kEoRing)
-                        : fb;
+        const int ring = rel ? (half_storage(prec) ? kRelRing : 0) : (prec != P_F64 ? kEoRing : 0);
+        size_t b = ring ? align256(field_bytes(hg, prec, nc) * ring) + align256(sizeof(double) * kMaxBlock * ring) : fb;
         b += 3 * fb + align256(field_bytes(hg, xprec, nc)) + scal + (track ? fb : 0);
         b += align256(field_bytes(g, rel ? P_F64 : xprec, nc));
         b += align256(field_bytes(hg, rel ? P_F64 : prec, nc));  // etahat
@@ -1199,7 +1243,9 @@ static size_t ws_block(const Geom& g, const Geom& hg, const tsm_solve_params* p,
         return b;
     }
     const size_t fb = align256(field_bytes(g, prec, nc));
-    size_t b = 3 * fb + align256(field_bytes(g, prec == P_F64 ? P_F64 : P_F32, nc)) + scal + (track ? fb : 0);
+    const bool ring = !rel && half_storage(prec);
+    size_t b = 2 * fb + align256(field_bytes(g, prec == P_F64 ? P_F64 : P_F32, nc)) + scal + (track ? fb : 0);
+    b += ring ? align256(field_bytes(g, prec, nc) * kEoRing) + align256(sizeof(double) * kMaxBlock * kEoRing) : fb;
     b += rel ? 4 * align256(field_bytes(g, P_F64, nc)) : fb;
     return b;
 }

@@ -37,6 +37,10 @@ struct CgScal {
     int32_t stop;       // 0 normal-equation residual, 1 tracked true residual
     int32_t reliable;   // 1: reliable-update mode
     int32_t fell_back;  // flexible CG only: 1 if it fell back to plain CG
+    // reliable mode with kept directions: the first one not yet in x, and
+    // whether x32 holds anything
+    int32_t kf;
+    int32_t xacc;
     int32_t pad;
 };
 
