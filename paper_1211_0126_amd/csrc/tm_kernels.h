@@ -176,7 +176,6 @@ void launch_ring_rel_flush(hipStream_t st, const CgArgs& a, int prec, const void
                            int force);
 void launch_eo_xflush(hipStream_t st, const CgArgs& a, int prec, const void* dirs, size_t slot_bytes, int k0, int k1,
                       void* out = nullptr, int out_prec = P_F32);
-uint32_t eo_gated_blocks(const Geom& hg);
 void launch_eo_rel_resid(hipStream_t st, const CgArgs& a, const EoCg& e, const void* b64, const void* t64,
                          const void* y64, int nr, int prec = P_F32);
 // the same half-hops with the links of a tile of 64 half-sites staged in LDS

@@ -636,7 +636,7 @@ static tm_status solve_block_eo(tm_ctx* ctx, const tsm_solve_params* p, uint64_t
                     e3.gate = a.scal;
                     launch_eo_lin(st, e3, P_F64, nr64, EO_Y_DAG);
                     launch_eo_rel_resid(st, a, ec64, b64, t64, y64, nr64, prec);
-                    launch_rel_fin(st, a, eo_gated_blocks(hg));
+                    launch_rel_fin(st, a, a.npart);
                     prof_end(ctx, TM_KC_OTHER, 0.0);
                 }
                 prof_begin(ctx, TM_KC_BLAS, prof_tag(prec, 1, TM_SOLVER_CG_EO, 0, rel));
