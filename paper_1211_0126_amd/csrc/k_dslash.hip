@@ -74,40 +74,52 @@ __global__ TM_STENCIL_R(NR, R) void k_apply(Geom geo, const void* gauge, R kappa
 // CG kernels
 // ---------------------------------------------------------------------------
 
-// End of one CG step for one right-hand side (single thread).
-__device__ inline void cg_finish_step(CgScal& q, double rrn, double rhon) {
+// NaN or overflow in a step: breakdown
+__device__ __forceinline__ bool cg_broken(const CgScal& q, double rrn) {
+    return !(rrn == rrn) || !(q.alpha == q.alpha) || rrn > 1e300;
+}
+
+// Whether a plain CG step with |r|^2 = rrn and stop quantity rel2 is followed
+// by another (q: the state before the step)
+__device__ __forceinline__ bool cg_goes_on(const CgScal& q, double rrn, double rel2) {
+    return !cg_broken(q, rrn) && !(rel2 <= q.tol2) && !(q.maxit >= 0 && q.iters + 1 >= q.maxit);
+}
+
+// End of that step (single thread)
+__device__ __forceinline__ void cg_finish_plain(CgScal& q, double rrn, double rel2) {
+    const bool broken = cg_broken(q, rrn), go = cg_goes_on(q, rrn, rel2);
     q.iters += 1;
-    if (!(rrn == rrn) || !(q.alpha == q.alpha) || rrn > 1e300) {  // NaN or overflow: breakdown
-        q.status = 3;
+    if (!go) {
+        q.status = broken ? 3 : rel2 <= q.tol2 ? 1 : 2;
         q.active = 0;
-        q.rflag = 0;
-        return;
     }
-    if (q.stop == 1 && !q.reliable) q.rho2 = rhon;
-    if (q.reliable) {
-        if (rrn > q.maxrr) q.maxrr = rrn;
-        if (rrn * q.sigma * q.sigma <= q.tol2 * q.bb || rrn < q.delta2 * q.maxrr) {
-            q.rflag = 1;  // the reliable-update kernels finish this step
-            // the recomputed residual is stored at the source's scale
-            const double s = (rrn > 0 && q.bb > 0) ? q.sigma * sqrt(rrn / q.bb) : q.sigma;
-            q.sigma_next = (s > 0 && s < 1e300) ? exp2(rint(log2(s))) : q.sigma;
-            return;
-        }
-        q.beta = rrn / q.rr;
-        q.rr = rrn;
-        if (q.maxit >= 0 && q.iters >= q.maxit) {
-            q.status = 2;
-            q.active = 0;
-        }
+    if (broken) {
+        q.rflag = 0;
         return;
     }
     q.beta = rrn / q.rr;
     q.rr = rrn;
-    const double rel2 = (q.stop == 1) ? q.rho2 / q.ee : rrn / q.bb;
-    if (rel2 <= q.tol2) {
-        q.status = 1;
-        q.active = 0;
-    } else if (q.maxit >= 0 && q.iters >= q.maxit) {
+}
+
+// End of one CG step for one right-hand side (single thread).
+__device__ inline void cg_finish_step(CgScal& q, double rrn, double rhon) {
+    if (!q.reliable || cg_broken(q, rrn)) {
+        if (q.stop == 1 && !cg_broken(q, rrn)) q.rho2 = rhon;
+        cg_finish_plain(q, rrn, (q.stop == 1) ? q.rho2 / q.ee : rrn / q.bb);
+        return;
+    }
+    q.iters += 1;
+    if (rrn > q.maxrr) q.maxrr = rrn;
+    if (rrn * q.sigma * q.sigma <= q.tol2 * q.bb || rrn < q.delta2 * q.maxrr) {
+        q.rflag = 1;  // the reliable-update kernels finish this step
+        // the recomputed residual is stored at the source's scale
+        const double s = (rrn > 0 && q.bb > 0) ? q.sigma * sqrt(rrn / q.bb) : q.sigma;
+        q.sigma_next = (s > 0 && s < 1e300) ? exp2(rint(log2(s))) : q.sigma;
+        return;
+    }
+    q.beta = rrn / q.rr;
+    q.rr = rrn;
+    if (q.maxit >= 0 && q.iters >= q.maxit) {
         q.status = 2;
         q.active = 0;
     }
@@ -157,17 +169,34 @@ __global__ TM_STENCIL_R(NR, R) void k_cg_mp(CgArgs a) {
 }
 
 // Block partials of one right-hand side in a fixed order (the stencil
-// launch that wrote them has completed); valid in thread 0.
-__device__ __forceinline__ double sum_block_partials(const double* p, uint32_t n, double* sh) {
+// launch that wrote them has completed); valid in thread 0.  Blocks of kSumBlock
+// threads, eight loads in flight per thread: a chip-filling stencil leaves one
+// partial per 64 sites (5184 at 24^3 x 48: 12 us with 256 threads and one load
+// at a time, 6 us so).
+constexpr int kSumBlock = 1024;
+__device__ __forceinline__ double sum_block_partials(const double* p, uint32_t n, double* sh /*[kSumBlock / 64]*/) {
     if (n <= kOrderParts) return wave_partials(p, n);
     double v = 0;
-    for (uint32_t i = threadIdx.x; i < n; i += 256) v += p[i];
-    return block_sum256(v, sh);
+    for (uint32_t i = threadIdx.x; i < n; i += 8 * kSumBlock) {
+        double x[8];
+#pragma unroll
+        for (uint32_t j = 0; j < 8; j++) x[j] = p[min(i + kSumBlock * j, n - 1)];
+#pragma unroll
+        for (uint32_t j = 0; j < 8; j++) v += i + kSumBlock * j < n ? x[j] : 0.0;
+    }
+    v = wave_sum(v);
+    if ((threadIdx.x & 63u) == 0) sh[threadIdx.x >> 6] = v;
+    __syncthreads();
+    double r = 0;
+    if (threadIdx.x == 0)
+        for (int w = 0; w < kSumBlock / 64; w++) r += sh[w];
+    __syncthreads();
+    return r;
 }
 
 // after K1, one block per right-hand side: alpha = |r|^2 / |t|^2
-__global__ __launch_bounds__(256) void k_cg_alpha(CgArgs a, uint32_t nb) {
-    __shared__ double sh[4];
+__global__ __launch_bounds__(kSumBlock) void k_cg_alpha(CgArgs a, uint32_t nb) {
+    __shared__ double sh[kSumBlock / 64];
     const int r = blockIdx.x;
     if (!a.scal[r].active) return;
     const double tt = sum_block_partials(a.partials + (size_t)r * nb, nb, sh);
@@ -182,8 +211,8 @@ __global__ __launch_bounds__(256) void k_cg_alpha(CgArgs a, uint32_t nb) {
 // after K2, one block per right-hand side: |r|^2 (and |rho|^2), beta and the
 // stop test
 template <bool TRACK>
-__global__ __launch_bounds__(256) void k_cg_beta(CgArgs a, uint32_t nb) {
-    __shared__ double sh[4];
+__global__ __launch_bounds__(kSumBlock) void k_cg_beta(CgArgs a, uint32_t nb) {
+    __shared__ double sh[kSumBlock / 64];
     const int r = blockIdx.x;
     if (!a.scal[r].active) return;
     const double rrn = sum_block_partials(a.partials + (size_t)r * nb, nb, sh);
@@ -285,11 +314,23 @@ __global__ __launch_bounds__(256) void k_cg_p(CgArgs a) {
             load_spinor<S, R>(pp, a.geo.Vs, s, pv);
         }
         TM_MEM_FENCE();
-        CgScal q = a.scal[r];
-        if (q.active) cg_finish_step(q, wave_partials(a.partials2 + (size_t)r * a.npart, a.npart), 0.0);
-        if (s == 0) a.scal_next[r] = q;
-        if (!q.active) return;
-        b = q.beta;
+        // (every wave reads the few fields that it needs and one thread hands
+        // the state on: a copy of the struct per lane went through LDS and
+        // scratch, 12 us instead of 5 at 9x11x7x13)
+        const CgScal& q = a.scal[r];
+        CgScal& n = a.scal_next[r];
+        if (!q.active) {
+            if (s == 0) n = q;
+            return;
+        }
+        const double rrn = wave_partials(a.partials2 + (size_t)r * a.npart, a.npart);
+        b = rrn / q.rr;
+        const bool go = cg_goes_on(q, rrn, rrn / q.bb);
+        if (s == 0) {
+            n = q;
+            cg_finish_plain(n, rrn, rrn / q.bb);
+        }
+        if (!go) return;
     } else {
         const CgScal& q = a.scal[r];
         if (!q.active) return;
@@ -362,8 +403,8 @@ __device__ inline void cg_start(CgScal& q, double bb, double ee) {
 
 // one block per right-hand side; with_ee = 0: |eta|^2 = ee_z4 (12 per site
 // of a Z4 source on the whole lattice)
-__global__ __launch_bounds__(256) void k_cg_init_fin(CgArgs a, uint32_t nb, int with_ee, double ee_z4) {
-    __shared__ double sh[4];
+__global__ __launch_bounds__(kSumBlock) void k_cg_init_fin(CgArgs a, uint32_t nb, int with_ee, double ee_z4) {
+    __shared__ double sh[kSumBlock / 64];
     const int r = blockIdx.x;
     const double bb = sum_block_partials(a.partials + (size_t)r * nb, nb, sh);
     const double ee = with_ee ? sum_block_partials(a.partials2 + (size_t)r * nb, nb, sh) : ee_z4;
@@ -484,8 +525,8 @@ __global__ TM_STENCIL_R(1, double) void k_rel_resid(CgArgs a, const void* gauge6
 // one block per right-hand side with the reliable flag set: restart the
 // recursion from the recomputed residual, stop test on it (or on the FP64
 // true residual |eta - M x| when the solve stops on that)
-__global__ __launch_bounds__(256) void k_rel_fin(CgArgs a, uint32_t nb) {
-    __shared__ double sh[4];
+__global__ __launch_bounds__(kSumBlock) void k_rel_fin(CgArgs a, uint32_t nb) {
+    __shared__ double sh[kSumBlock / 64];
     const int r = blockIdx.x;
     if (!a.scal[r].rflag) return;
     const double rrn = sum_block_partials(a.partials + (size_t)r * nb, nb, sh);
@@ -549,8 +590,8 @@ __global__ TM_STENCIL_R(1, double) void k_true_resid(CgArgs a, const void* gauge
     if (threadIdx.x == 0) a.partials2[(size_t)r * nb + bm.sb] = w;
 }
 
-__global__ __launch_bounds__(256) void k_true_resid_fin(CgArgs a, uint32_t nb) {
-    __shared__ double sh[4];
+__global__ __launch_bounds__(kSumBlock) void k_true_resid_fin(CgArgs a, uint32_t nb) {
+    __shared__ double sh[kSumBlock / 64];
     const int r = blockIdx.x;
     const double rr = sum_block_partials(a.partials + (size_t)r * nb, nb, sh);
     const double ee = sum_block_partials(a.partials2 + (size_t)r * nb, nb, sh);
@@ -767,15 +808,15 @@ void launch_cg_upd(hipStream_t st, const CgArgs& a, int prec, int nr, bool track
 }
 
 void launch_cg_alpha(hipStream_t st, const CgArgs& a) {
-    hipLaunchKernelGGL(k_cg_alpha, dim3((unsigned)a.nrhs), dim3(256), 0, st, a, a.npart);
+    hipLaunchKernelGGL(k_cg_alpha, dim3((unsigned)a.nrhs), dim3(kSumBlock), 0, st, a, a.npart);
 }
 
 void launch_cg_beta(hipStream_t st, const CgArgs& a, bool track) {
     const uint32_t nb = a.npart;
     if (track)
-        hipLaunchKernelGGL(k_cg_beta<true>, dim3((unsigned)a.nrhs), dim3(256), 0, st, a, nb);
+        hipLaunchKernelGGL(k_cg_beta<true>, dim3((unsigned)a.nrhs), dim3(kSumBlock), 0, st, a, nb);
     else
-        hipLaunchKernelGGL(k_cg_beta<false>, dim3((unsigned)a.nrhs), dim3(256), 0, st, a, nb);
+        hipLaunchKernelGGL(k_cg_beta<false>, dim3((unsigned)a.nrhs), dim3(kSumBlock), 0, st, a, nb);
 }
 
 void launch_cg_p(hipStream_t st, const CgArgs& a, int prec) {
@@ -816,7 +857,7 @@ void launch_cg_init(hipStream_t st, const CgArgs& a, int prec, bool track, const
             hipLaunchKernelGGL((k_cg_init<float, SBF16, SF32, float, false>), grid, dim3(256), 0, st, a, eta);
         break;
     }
-    hipLaunchKernelGGL(k_cg_init_fin, dim3((unsigned)a.nrhs), dim3(256), 0, st, a, site_blocks(a.geo),
+    hipLaunchKernelGGL(k_cg_init_fin, dim3((unsigned)a.nrhs), dim3(kSumBlock), 0, st, a, site_blocks(a.geo),
                        ee_z4 > 0 ? 0 : 1, ee_z4);
 }
 
@@ -833,11 +874,11 @@ void launch_rel_init(hipStream_t st, const CgArgs& a, const void* b64, void* x64
     case P_BF16: hipLaunchKernelGGL(k_rel_init<SBF16>, grid, dim3(256), 0, st, a, b64, x64); break;
     default: hipLaunchKernelGGL(k_rel_init<SF32>, grid, dim3(256), 0, st, a, b64, x64); break;
     }
-    hipLaunchKernelGGL(k_cg_init_fin, dim3((unsigned)a.nrhs), dim3(256), 0, st, a, site_blocks(a.geo), 0,
+    hipLaunchKernelGGL(k_cg_init_fin, dim3((unsigned)a.nrhs), dim3(kSumBlock), 0, st, a, site_blocks(a.geo), 0,
                        ee_z4 > 0 ? ee_z4 : 12.0 * (double)a.geo.V);
 }
 void launch_rel_fin(hipStream_t st, const CgArgs& a, uint32_t nb) {
-    hipLaunchKernelGGL(k_rel_fin, dim3((unsigned)a.nrhs), dim3(256), 0, st, a, nb);
+    hipLaunchKernelGGL(k_rel_fin, dim3((unsigned)a.nrhs), dim3(kSumBlock), 0, st, a, nb);
 }
 void launch_rel_flush(hipStream_t st, const CgArgs& a, void* x64, int force) {
     hipLaunchKernelGGL(k_rel_flush, dim3(gated_blocks(a.geo), (unsigned)a.nrhs), dim3(256), 0, st, a, x64, force);
@@ -845,7 +886,7 @@ void launch_rel_flush(hipStream_t st, const CgArgs& a, void* x64, int force) {
 void launch_rel_resid(hipStream_t st, const CgArgs& a, const void* gauge64, const void* b64, const void* t64) {
     const uint32_t nb = gated_blocks(a.geo);
     hipLaunchKernelGGL(k_rel_resid, dim3(nb, (unsigned)a.nrhs), dim3(256), 0, st, a, gauge64, b64, t64);
-    hipLaunchKernelGGL(k_rel_fin, dim3((unsigned)a.nrhs), dim3(256), 0, st, a, nb);
+    hipLaunchKernelGGL(k_rel_fin, dim3((unsigned)a.nrhs), dim3(kSumBlock), 0, st, a, nb);
 }
 
 void launch_true_resid(hipStream_t st, const CgArgs& a, int xprec, const void* gauge64, uint64_t seed_mixed,
@@ -855,7 +896,7 @@ void launch_true_resid(hipStream_t st, const CgArgs& a, int xprec, const void* g
         hipLaunchKernelGGL((k_true_resid<SF64, double>), grid, dim3(256), 0, st, a, gauge64, seed_mixed, ids);
     else
         hipLaunchKernelGGL((k_true_resid<SF32, float>), grid, dim3(256), 0, st, a, gauge64, seed_mixed, ids);
-    hipLaunchKernelGGL(k_true_resid_fin, dim3((unsigned)a.nrhs), dim3(256), 0, st, a, site_blocks(a.geo));
+    hipLaunchKernelGGL(k_true_resid_fin, dim3((unsigned)a.nrhs), dim3(kSumBlock), 0, st, a, site_blocks(a.geo));
 }
 
 }  // namespace tmq

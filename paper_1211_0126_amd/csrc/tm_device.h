@@ -599,9 +599,9 @@ __device__ __forceinline__ double wave_partials(const double* p, uint32_t n) {
     for (uint32_t i = threadIdx.x & 63u; i < n; i += 512) {
         double x[8];
 #pragma unroll
-        for (uint32_t j = 0; j < 8; j++) x[j] = i + 64 * j < n ? p[i + 64 * j] : 0.0;
+        for (uint32_t j = 0; j < 8; j++) x[j] = p[min(i + 64 * j, n - 1)];
 #pragma unroll
-        for (uint32_t j = 0; j < 8; j++) v += x[j];
+        for (uint32_t j = 0; j < 8; j++) v += i + 64 * j < n ? x[j] : 0.0;
     }
     return wave_sum(v);
 }
