@@ -125,9 +125,9 @@ __device__ __forceinline__ void gather_tile(const PtArgs& a, uint32_t site0, uin
 // the current k-step, i.e. one (path, channel) and the spin pair 2(g&1),
 // 2(g&1)+1.  Each lane therefore transports a half spinor per k-step (18
 // complex multiply-adds as bfloat16 dot2 with FP32 accumulation); the link
-// comes from a bfloat16-pair copy of the gauge field.  The D layout gives
-// lane l the output channel g>>1 and the same spin pair, which it writes as
-// its half of the output spinor.  No LDS and no barriers.
+// comes from a bfloat16-pair copy of the gauge field, through the wave's part
+// of LDS.  The D layout gives lane l the output channel g>>1 and the same spin
+// pair, which it writes as its half of the output spinor.  No barriers.
 // K-steps: for two input channels step ks is path ks (lane channel g>>1); for
 // one channel step ks covers paths 2ks and 2ks+1 (lane path 2ks + (g>>1)),
 // the tenth "path" being zero padding.
@@ -179,165 +179,305 @@ struct SBH {
 };
 __device__ __forceinline__ uint32_t swap16(uint32_t x) { return __builtin_amdgcn_alignbit(x, x, 16); }
 
-// The lane's half spinor (components 6h .. 6h+5, spins 2h and 2h+1) of
-// channel b at site y, as bfloat16 (re, im) pairs.
-__device__ __forceinline__ void half_spinor(const void* f, uint32_t PB, int b, uint32_t y, int h, uint32_t q[6],
-                                            SBF16) {
-    // planes of 4 components: h = 0 -> plane 0 + low half of plane 1; h = 1 -> high half of plane 1 + plane 2
-    const uint32_t base = (y << 4) + (uint32_t)b * 3u * PB;
-    const uint4 full = ldv128(f, base + (h ? 2u * PB : 0u));
-    const uint2 half = ldv64(f, base + PB + (h ? 8u : 0u));
-    q[0] = h ? half.x : full.x;
-    q[1] = h ? half.y : full.y;
-    q[2] = h ? full.x : full.z;
-    q[3] = h ? full.y : full.w;
-    q[4] = h ? full.z : half.x;
-    q[5] = h ? full.w : half.y;
-}
-__device__ __forceinline__ void half_spinor(const void* f, uint32_t PB, int b, uint32_t y, int h, uint32_t q[6],
-                                            SBH) {
-    const uint32_t base = (y << 4) + (uint32_t)b * 3u * PB;
-    const uint4 full = ldv128(f, base + (uint32_t)h * PB);
-    const uint2 half = ldv64(f, base + 2u * PB + (uint32_t)h * 8u);
-    q[0] = full.x;
-    q[1] = full.y;
-    q[2] = full.z;
-    q[3] = full.w;
-    q[4] = half.x;
-    q[5] = half.y;
-}
-__device__ __forceinline__ void half_spinor(const void* f, uint32_t PB, int b, uint32_t y, int h, uint32_t q[6],
-                                            SF32) {
-    // planes of 2 components: planes 3h, 3h+1, 3h+2
-    const uint32_t base = (y << 4) + (uint32_t)b * 6u * PB + (uint32_t)h * 3u * PB;
-#pragma unroll
-    for (int j = 0; j < 3; j++) {
-        const float4 v = __builtin_bit_cast(float4, ldv128(f, base + (uint32_t)j * PB));
-        q[2 * j] = pack2_bf16(v.x, v.y);
-        q[2 * j + 1] = pack2_bf16(v.z, v.w);
+// The lane's half spinor (components 6h .. 6h+5, spins 2h and 2h+1) of channel
+// b at site y: the loads, and later its bfloat16 (re, im) pairs.
+template <class Si>
+struct HalfRaw {  // 16-bit: one plane and half of another
+    uint4 full;
+    uint2 half;
+    __device__ __forceinline__ void load(const void* f, uint32_t PB, int b, uint32_t y, int h) {
+        const uint32_t base = (y << 4) + (uint32_t)b * 3u * PB;
+        if constexpr (std::is_same<Si, SBH>::value) {
+            full = ldv128(f, base + (uint32_t)h * PB);
+            half = ldv64(f, base + 2u * PB + (uint32_t)h * 8u);
+        } else {
+            // planes of 4 components: h = 0 -> plane 0 + low half of plane 1; h = 1 -> high half of plane 1 + plane 2
+            full = ldv128(f, base + (h ? 2u * PB : 0u));
+            half = ldv64(f, base + PB + (h ? 8u : 0u));
+        }
     }
-}
+    __device__ __forceinline__ void pairs(int h, uint32_t q[6]) const {
+        if constexpr (std::is_same<Si, SBH>::value) h = 0;
+        q[0] = h ? half.x : full.x;
+        q[1] = h ? half.y : full.y;
+        q[2] = h ? full.x : full.z;
+        q[3] = h ? full.y : full.w;
+        q[4] = h ? full.z : half.x;
+        q[5] = h ? full.w : half.y;
+    }
+};
+template <>
+struct HalfRaw<SF32> {  // planes of 2 components: planes 3h, 3h+1, 3h+2
+    uint4 v[3];
+    __device__ __forceinline__ void load(const void* f, uint32_t PB, int b, uint32_t y, int h) {
+        const uint32_t base = (y << 4) + (uint32_t)b * 6u * PB + (uint32_t)h * 3u * PB;
+#pragma unroll
+        for (int j = 0; j < 3; j++) v[j] = ldv128(f, base + (uint32_t)j * PB);
+    }
+    __device__ __forceinline__ void pairs(int, uint32_t q[6]) const {
+#pragma unroll
+        for (int j = 0; j < 3; j++) {
+            const float4 w = __builtin_bit_cast(float4, v[j]);
+            q[2 * j] = pack2_bf16(w.x, w.y);
+            q[2 * j + 1] = pack2_bf16(w.z, w.w);
+        }
+    }
+};
 
 // Per-lane description of the (path, channel) of one k-step.
 struct LyPath {
     uint32_t y;      // neighbour site
-    uint32_t lsite;  // site of the link
-    uint32_t lplane; // byte offset of the link's first plane
-    uint32_t flip;   // 0x80008000 where the time-boundary sign applies
-    bool fwd, ident, pad;
+    uint32_t link;   // link of the path (0 ... 7: +-x, +-y, +-z, +-t)
+    bool ident, pad;
 };
 
 template <int P>
-__device__ __forceinline__ LyPath ly_path(const uint32_t ys[9], uint32_t s, uint32_t flip_f, uint32_t flip_b,
-                                          uint32_t PB) {
+__device__ __forceinline__ LyPath ly_path(const uint32_t ys[9]) {
     LyPath d;
     d.pad = P >= 9;
     d.ident = P == 0;
-    d.y = (P >= 1 && P <= 8) ? ys[P] : s;
-    d.fwd = (P & 1) != 0;
-    const int mu = (P >= 1 && P <= 8) ? (P - 1) >> 1 : 0;  // identity and padding read direction 0's link
-    d.lsite = d.fwd || P == 0 ? s : d.y;
-    d.lplane = (uint32_t)(mu * 3) * PB;
-    d.flip = (P == 7) ? flip_f : (P == 8) ? flip_b : 0u;
+    d.y = (P >= 1 && P <= 8) ? ys[P] : ys[0];
+    d.link = (P >= 1 && P <= 8) ? (uint32_t)(P - 1) : 0u;  // identity and padding read direction 0's link
     return d;
 }
 __device__ __forceinline__ LyPath ly_select(bool hi, const LyPath& a, const LyPath& b) {
     LyPath d;
     d.y = hi ? b.y : a.y;
-    d.lsite = hi ? b.lsite : a.lsite;
-    d.lplane = hi ? b.lplane : a.lplane;
-    d.flip = hi ? b.flip : a.flip;
-    d.fwd = hi ? b.fwd : a.fwd;
+    d.link = hi ? b.link : a.link;
     d.ident = hi ? b.ident : a.ident;
     d.pad = hi ? b.pad : a.pad;
     return d;
 }
 
-// The link of a k-step, oriented and as bfloat16 pairs: m[c][k] = U[c][k]
-// (forward) or U[k][c] (backward, to be used with the conjugating operand
-// signs below).
-__device__ __forceinline__ void ly_link(const PtArgs& a, uint32_t PB, const LyPath& d, uint32_t m[9]) {
-    const uint32_t lb = (d.lsite << 4) + d.lplane;
-    const uint4 u0 = ldv128(a.gaugebf, lb);
-    const uint4 u1 = ldv128(a.gaugebf, lb + PB);
-    const uint32_t u8 = ldv32(a.gaugebf, lb + 2u * PB);
-    const uint32_t u[9] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w, u8};
+// The eight links of a wave's 16 sites in LDS, [link][plane][site], each entry
+// V of the oriented link (U_mu(x), or U_mu(x - mu)^dag, with the time-boundary
+// sign) as the two bfloat16 pairs that a product with (re, im) takes:
+// dword e: (Re V, -Im V) for the real part, dword 9 + e: (Im V, Re V) for the
+// imaginary part, e = 3 c + k.  Lane 16 g + i prepares links g and 4 + g of
+// site i.
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+constexpr int LY_LP = 5;  // planes of 16 bytes per link (18 dwords)
+__device__ __forceinline__ void ly_stage_links(const PtArgs& a, uint32_t PB, const uint32_t ys[9], uint32_t flip_f,
+                                               uint32_t flip_b, int g, int i, v4u* sl) {
+    const bool bwd = (g & 1) != 0;  // (link l: mu = l >> 1, backward if odd)
+    const uint32_t mb = bwd ? ~0u : 0u;
+    uint4 u0[2], u1[2];
+    uint32_t u8[2];
 #pragma unroll
-    for (int c = 0; c < 3; c++)
+    for (int it = 0; it < 2; it++) {
+        const int l = 4 * it + g;
+        // (selections by mask: the compiler turns selected array elements into addresses in scratch)
+        const uint32_t yb = ys[4 + 4 * it] ^ ((ys[2 + 4 * it] ^ ys[4 + 4 * it]) & (g == 1 ? ~0u : 0u));
+        const uint32_t off = ((ys[0] ^ ((ys[0] ^ yb) & mb)) << 4) + (uint32_t)((l >> 1) * 3) * PB;
+        u0[it] = ldv128(a.gaugebf, off);
+        u1[it] = ldv128(a.gaugebf, off + PB);
+        u8[it] = ldv32(a.gaugebf, off + 2u * PB);
+    }
 #pragma unroll
-        for (int k = 0; k < 3; k++) m[3 * c + k] = d.fwd ? u[3 * c + k] : u[3 * k + c];
+    for (int it = 0; it < 2; it++) {
+        const uint32_t u[9] = {u0[it].x, u0[it].y, u0[it].z, u0[it].w, u1[it].x, u1[it].y, u1[it].z, u1[it].w, u8[it]};
+        const uint32_t flip = it == 0 ? 0u : g == 2 ? flip_f : g == 3 ? flip_b : 0u;
+        const uint32_t s1 = (bwd ? 0u : 0x80000000u) ^ flip, s2 = (bwd ? 0x8000u : 0u) ^ flip;
+        uint32_t w[4 * LY_LP];
+#pragma unroll
+        for (int c = 0; c < 3; c++)
+#pragma unroll
+            for (int k = 0; k < 3; k++) {
+                const uint32_t uf = u[3 * c + k], ub = u[3 * k + c], v = uf ^ ((uf ^ ub) & mb);
+                w[3 * c + k] = v ^ s1;
+                w[9 + 3 * c + k] = swap16(v) ^ s2;
+            }
+        w[18] = w[19] = 0u;
+#pragma unroll
+        for (int q = 0; q < LY_LP; q++)
+            sl[((4 * it + g) * LY_LP + q) * 16 + i] = (v4u){w[4 * q], w[4 * q + 1], w[4 * q + 2], w[4 * q + 3]};
+    }
+    // read by the same wave only: its LDS accesses stay in order
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The link of a k-step, prepared by ly_stage_links
+__device__ __forceinline__ void ly_link(const v4u* sl, int i, const LyPath& d, v4u m[LY_LP]) {
+    const v4u* p = sl + d.link * (16u * LY_LP) + (uint32_t)i;
+#pragma unroll
+    for (int q = 0; q < LY_LP; q++) m[q] = p[16 * q];
 }
 
 // B operand of one k-step and one right-hand side for the three colours: the
 // lane's two spins of the transported (or, for the identity path, the plain)
 // half spinor.
-//   forward:  Re t = (Re, -Im) psi . U,   Im t = (Im, Re) psi . U
-//   backward: Re t = psi . U^T,           Im t = (Im, -Re) psi . U^T
 template <class Si>
-__device__ __forceinline__ void ly_operand(const void* in, uint32_t PB, int h, int b, const LyPath& d,
-                                           const uint32_t m[9], uint32_t B[3][2]) {
-    uint32_t q[6];
-    half_spinor(in, PB, b, d.y, h, q, Si{});
-    const uint32_t s1 = d.fwd ? 0x80000000u : 0u, s2 = d.fwd ? 0u : 0x80000000u;
-    uint32_t a1[6], a2[6];
+__device__ __forceinline__ void ly_operand(const HalfRaw<Si>& raw, int h, const LyPath& d, const v4u mv[LY_LP],
+                                           uint32_t B[3][2]) {
+    uint32_t q[6], m[4 * LY_LP];
 #pragma unroll
-    for (int j = 0; j < 6; j++) {
-        a1[j] = q[j] ^ s1;
-        a2[j] = swap16(q[j]) ^ s2;
-    }
+    for (int e = 0; e < 4 * LY_LP; e++) m[e] = mv[e >> 2][e & 3];
+    raw.pairs(h, q);
 #pragma unroll
     for (int c = 0; c < 3; c++)
 #pragma unroll
         for (int t = 0; t < 2; t++) {
-            float tr = dot2_0(a1[3 * t], m[3 * c]), ti = dot2_0(a2[3 * t], m[3 * c]);
-            tr = dot2(a1[3 * t + 1], m[3 * c + 1], tr);
-            ti = dot2(a2[3 * t + 1], m[3 * c + 1], ti);
-            tr = dot2(a1[3 * t + 2], m[3 * c + 2], tr);
-            ti = dot2(a2[3 * t + 2], m[3 * c + 2], ti);
-            const uint32_t tv = pack2_bf16(tr, ti) ^ d.flip;
+            float tr = dot2_0(q[3 * t], m[3 * c]), ti = dot2_0(q[3 * t], m[9 + 3 * c]);
+            tr = dot2(q[3 * t + 1], m[3 * c + 1], tr);
+            ti = dot2(q[3 * t + 1], m[9 + 3 * c + 1], ti);
+            tr = dot2(q[3 * t + 2], m[3 * c + 2], tr);
+            ti = dot2(q[3 * t + 2], m[9 + 3 * c + 2], ti);
+            const uint32_t tv = pack2_bf16(tr, ti);
             B[c][t] = d.pad ? 0u : d.ident ? q[3 * t + c] : tv;
         }
 }
 
-// Right-hand sides are processed in chunks of LY_RC: each k-step's link is
-// loaded once and applied to all of the chunk's right-hand sides, whose MFMA
-// accumulators stay live.  A block handles TM_LY_CHUNKS_RC right-hand sides of
-// its tile, and the grid runs chunk-major, so the lattice is swept once per
-// group of right-hand sides and the time neighbours of a sweep stay in cache.
-// (Measured on 24^3 x 48 with 8 right-hand sides: chunks of 2 and 2 per block
-// are 5-15% faster than 1, 4 or all right-hand sides per block.)
-#ifndef TM_LY_RC
-#define TM_LY_RC 2
-#endif
-constexpr int LY_RC = TM_LY_RC;
-#ifndef TM_LY_CHUNKS_RC
-#define TM_LY_CHUNKS_RC 2
-#endif
+// Right-hand sides go through the wave two at a time (a link read from LDS
+// serves both, the MFMA accumulators of both stay live), and a block of 64
+// sites handles up to LY_PER of them.  What bounds the layer is the traffic
+// between L2 and the memory side: a lane reads nine half spinors and writes
+// one, and when a block handled two right-hand sides and every wave read its
+// links for itself, four times over, the links were half of the traffic and
+// every k-step waited for its loads.  Hence
+//   * the links of the 16 sites are staged in LDS once per block, already
+//     oriented, conjugated and signed for the two dot products of a complex
+//     multiply (per half spinor 36 dot2 and 6 conversions are left);
+//   * the half spinors of a k-step are loaded while the one before is computed;
+//   * four right-hand sides per block, sites in slab order.
+// 16 right-hand sides on 16^3 x 32: layer 2 -> 2 channels 254 -> 190 us,
+// 2 -> 1 240 -> 185 us, 1 -> 2 206 -> 135 us (2 right-hand sides per block:
+// 202 us for 2 -> 2; 8 and 16: 195; two k-steps ahead: 203; one right-hand
+// side at a time with four waves per SIMD: 195).
+constexpr uint32_t LY_PER = 4;
+
+template <int CIN, int KS>
+__device__ __forceinline__ LyPath ly_step(const uint32_t ys[9], bool hi) {
+    if constexpr (CIN == 2)
+        return ly_path<KS>(ys);
+    else
+        return ly_select(hi, ly_path<2 * KS>(ys), ly_path<2 * KS + 1>(ys));
+}
+
+// What one wave knows of its 16 sites
+struct LyWave {
+    uint32_t ys[9];   // the site and its neighbours
+    uint32_t sout;    // site to store (~0: past the lattice)
+    int g, i;         // lane = 16 g + i
+    const v4u* sl;    // links in LDS
+};
+
+template <class Si, int CIN, int KS, int NKS, int NRC>
+__device__ __forceinline__ void ly_loads(const PtArgs& a, const LyWave& w, uint32_t PB, uint32_t r0,
+                                         HalfRaw<Si> raw[2][NRC]) {
+    if constexpr (KS < NKS) {
+        const LyPath d = ly_step<CIN, KS>(w.ys, (w.g >> 1) != 0);
+#pragma unroll
+        for (int j = 0; j < NRC; j++)
+            raw[KS & 1][j].load(field_rhs<Si>(a.in, a.geo.Vs, (int)((r0 + j) * CIN)), PB,
+                                            CIN == 2 ? w.g >> 1 : 0, d.y, w.g & 1);
+        __builtin_amdgcn_sched_barrier(0);  // (the scheduler would sink the loads to their use)
+    }
+}
+
+// k-steps KS ... NKS - 1; raw[KS & 1] and m hold step KS
+template <class Si, int CIN, int KS, int NKS, int NRC>
+__device__ __forceinline__ void ly_steps(const PtArgs& a, const LyWave& w, uint32_t PB, uint32_t r0,
+                                         const v4s wf[NKS], HalfRaw<Si> raw[2][NRC],
+                                         const v4u m[LY_LP], v4f D[NRC][3]) {
+    v4u mn[LY_LP];
+    if constexpr (KS + 1 < NKS) ly_link(w.sl, w.i, ly_step<CIN, KS + 1>(w.ys, (w.g >> 1) != 0), mn);
+    ly_loads<Si, CIN, KS + 1, NKS, NRC>(a, w, PB, r0, raw);
+    const LyPath d = ly_step<CIN, KS>(w.ys, (w.g >> 1) != 0);
+#pragma unroll
+    for (int j = 0; j < NRC; j++) {
+        uint32_t B[3][2];
+        ly_operand<Si>(raw[KS & 1][j], w.g & 1, d, m, B);
+#pragma unroll
+        for (int c = 0; c < 3; c++) {
+            const v4s bo = __builtin_bit_cast(v4s, make_uint2(B[c][0], B[c][1]));
+            D[j][c] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(wf[KS], bo, D[j][c], 0, 0, 0);
+        }
+    }
+    if constexpr (KS + 1 < NKS) ly_steps<Si, CIN, KS + 1, NKS, NRC>(a, w, PB, r0, wf, raw, mn, D);
+}
+
+// NRC right-hand sides from r0 on
+template <class Si, class So, int CIN, int COUT, int NKS, int NRC>
+__device__ __forceinline__ void ly_chunk(const PtArgs& a, const LyWave& w, uint32_t PB, uint32_t r0,
+                                         const v4s wf[NKS]) {
+    const long Vs = a.geo.Vs;
+    const int g = w.g, h = g & 1;
+    const uint32_t s = w.sout;
+    v4f D[NRC][3];
+#pragma unroll
+    for (int j = 0; j < NRC; j++)
+#pragma unroll
+        for (int c = 0; c < 3; c++) D[j][c] = (v4f){0.f, 0.f, 0.f, 0.f};
+    HalfRaw<Si> raw[2][NRC];
+    ly_loads<Si, CIN, 0, NKS, NRC>(a, w, PB, r0, raw);
+    v4u m[LY_LP];
+    ly_link(w.sl, w.i, ly_step<CIN, 0>(w.ys, (g >> 1) != 0), m);
+    ly_steps<Si, CIN, 0, NKS, NRC>(a, w, PB, r0, wf, raw, m, D);
+    // lane holds channel g>>1, spins 2h and 2h+1: component 6h + 3t + c is
+    // (D[c][2t], D[c][2t + 1])
+    const int ch = g >> 1;
+    if (s == ~0u || ch >= COUT) return;
+#pragma unroll
+    for (int j = 0; j < NRC; j++) {
+        void* out = field_rhs<So>(a.out, Vs, (int)((r0 + j) * COUT));
+        float o[12];
+#pragma unroll
+        for (int t = 0; t < 2; t++)
+#pragma unroll
+            for (int c = 0; c < 3; c++) {
+                o[2 * (3 * t + c)] = D[j][c][2 * t];
+                o[2 * (3 * t + c) + 1] = D[j][c][2 * t + 1];
+            }
+        if constexpr (std::is_same<So, SBH>::value) {
+            uint32_t w[6];
+#pragma unroll
+            for (int q = 0; q < 6; q++) w[q] = pack2_bf16(o[2 * q], o[2 * q + 1]);
+            const uint32_t base = (s << 4) + (uint32_t)ch * 3u * PB;
+            stv128(out, base + (uint32_t)h * PB, make_uint4(w[0], w[1], w[2], w[3]));
+            stv64(out, base + 2u * PB + (uint32_t)h * 8u, make_uint2(w[4], w[5]));
+        } else if constexpr (std::is_same<So, SF32>::value) {
+            const uint32_t base = (s << 4) + (uint32_t)ch * 6u * PB + (uint32_t)h * 3u * PB;
+#pragma unroll
+            for (int q = 0; q < 3; q++)
+                stv128(out, base + (uint32_t)q * PB,
+                       make_uint4(__float_as_uint(o[4 * q]), __float_as_uint(o[4 * q + 1]),
+                                  __float_as_uint(o[4 * q + 2]), __float_as_uint(o[4 * q + 3])));
+        } else {
+            static_assert(std::is_same<So, SF32>::value || std::is_same<So, SBH>::value, "FP32 or SBH output");
+        }
+    }
+}
 
 template <class Si, class So, int CIN, int COUT>
-__global__ __launch_bounds__(LY_THREADS) void k_pt_layer(PtArgs a, uint32_t nrhs) {
+__global__ __launch_bounds__(LY_THREADS) __attribute__((amdgpu_waves_per_eu(std::is_same<Si, SF32>::value ? 2 : 3))) void k_pt_layer(PtArgs a, uint32_t nrhs,
+                                                                               uint32_t per) {
     constexpr int NKS = (9 * CIN + 1) / 2;  // k-steps of 16
     const Geom& geo = a.geo;
-    const long Vs = geo.Vs;
-    const uint32_t PB = (uint32_t)Vs * 16u;  // plane bytes
-    const int lane = threadIdx.x & 63, g = lane >> 4, h = g & 1;
+    const uint32_t PB = (uint32_t)geo.Vs * 16u;  // plane bytes
+    const int lane = threadIdx.x & 63, g = lane >> 4;
     // blocks: (right-hand-side chunk, site tile), chunk slowest
     const uint32_t ntile = (geo.V + LY_TS - 1) / LY_TS;
     const uint32_t L = xcd_block(blockIdx.x, gridDim.x);
     const uint32_t chunk = L / ntile, tile = L - chunk * ntile;
-    const uint32_t r_beg = chunk * (uint32_t)TM_LY_CHUNKS_RC;
-    const uint32_t r_end = r_beg + (uint32_t)TM_LY_CHUNKS_RC < nrhs ? r_beg + (uint32_t)TM_LY_CHUNKS_RC : nrhs;
-    if (a.gate) {  // flexible CG: nothing to do for converged or fallen-back right-hand sides
-        bool any = false;
-        for (uint32_t r = r_beg; r < r_end; r++) any |= a.gate[r].active != 0 && a.gate[r].fell == 0;
-        if (!any) return;
-    }
+    const uint32_t r_beg = chunk * per;
+    const uint32_t r_end = r_beg + per < nrhs ? r_beg + per : nrhs;
+    // flexible CG: nothing to do for converged or fallen-back right-hand sides
+    uint32_t live = 0;
+    for (uint32_t r = r_beg; r < r_end; r++)
+        live |= (!a.gate || (a.gate[r].active != 0 && a.gate[r].fell == 0)) ? 1u << (r - r_beg) : 0u;
+    if (!live) return;
     const uint32_t s0 = tile * LY_TS + (threadIdx.x >> 6) * 16 + (lane & 15);
     const bool valid = s0 < geo.V;
-    const uint32_t s = valid ? s0 : 0u;  // lanes past the lattice compute site 0 and store nothing
+    const uint32_t s = valid ? slab_order(geo, s0) : 0u;  // lanes past the lattice compute site 0 and store nothing
 
-    uint32_t ys[9];
+    LyWave w;
+    w.g = g;
+    w.i = lane & 15;
+    w.sout = valid ? s : ~0u;
     uint32_t flip_f = 0, flip_b = 0;
+    uint32_t* ys = w.ys;
     {
         const Site c = site_coords(geo, s);
         ys[0] = s;
@@ -351,91 +491,18 @@ __global__ __launch_bounds__(LY_THREADS) void k_pt_layer(PtArgs a, uint32_t nrhs
             flip_b = (c.t == 0) ? 0x80008000u : 0u;
         }
     }
+    __shared__ v4u links[LY_THREADS / 64][8 * LY_LP * 16];
+    v4u* sl = links[threadIdx.x >> 6];
+    ly_stage_links(a, PB, ys, flip_f, flip_b, g, lane & 15, sl);
+    w.sl = sl;
     v4s wf[NKS];
 #pragma unroll
     for (int ks = 0; ks < NKS; ks++) wf[ks] = ((const v4s*)a.wfrag)[ks * 64 + lane];
 
-    for (uint32_t r0 = r_beg; r0 < r_end; r0 += LY_RC) {
-        const uint32_t nrhs_left = r_end;
-        const uint32_t nr = nrhs_left - r0 < (uint32_t)LY_RC ? nrhs_left - r0 : (uint32_t)LY_RC;
-        v4f D[LY_RC][3];
-#pragma unroll
-        for (int j = 0; j < LY_RC; j++)
-#pragma unroll
-            for (int c = 0; c < 3; c++) D[j][c] = (v4f){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int ks = 0; ks < NKS; ks++) {
-            LyPath d;
-            int b;
-            if constexpr (CIN == 2) {
-                d = ks == 0 ? ly_path<0>(ys, s, flip_f, flip_b, PB)
-                  : ks == 1 ? ly_path<1>(ys, s, flip_f, flip_b, PB)
-                  : ks == 2 ? ly_path<2>(ys, s, flip_f, flip_b, PB)
-                  : ks == 3 ? ly_path<3>(ys, s, flip_f, flip_b, PB)
-                  : ks == 4 ? ly_path<4>(ys, s, flip_f, flip_b, PB)
-                  : ks == 5 ? ly_path<5>(ys, s, flip_f, flip_b, PB)
-                  : ks == 6 ? ly_path<6>(ys, s, flip_f, flip_b, PB)
-                  : ks == 7 ? ly_path<7>(ys, s, flip_f, flip_b, PB)
-                            : ly_path<8>(ys, s, flip_f, flip_b, PB);
-                b = g >> 1;
-            } else {
-                const bool hi = (g >> 1) != 0;
-                d = ks == 0 ? ly_select(hi, ly_path<0>(ys, s, flip_f, flip_b, PB), ly_path<1>(ys, s, flip_f, flip_b, PB))
-                  : ks == 1 ? ly_select(hi, ly_path<2>(ys, s, flip_f, flip_b, PB), ly_path<3>(ys, s, flip_f, flip_b, PB))
-                  : ks == 2 ? ly_select(hi, ly_path<4>(ys, s, flip_f, flip_b, PB), ly_path<5>(ys, s, flip_f, flip_b, PB))
-                  : ks == 3 ? ly_select(hi, ly_path<6>(ys, s, flip_f, flip_b, PB), ly_path<7>(ys, s, flip_f, flip_b, PB))
-                            : ly_select(hi, ly_path<8>(ys, s, flip_f, flip_b, PB), ly_path<9>(ys, s, flip_f, flip_b, PB));
-                b = 0;
-            }
-            uint32_t m[9];
-            ly_link(a, PB, d, m);
-#pragma unroll
-            for (int j = 0; j < LY_RC; j++) {
-                if ((uint32_t)j >= nr) break;
-                uint32_t B[3][2];
-                ly_operand<Si>(field_rhs<Si>(a.in, Vs, (int)((r0 + j) * CIN)), PB, h, b, d, m, B);
-#pragma unroll
-                for (int c = 0; c < 3; c++) {
-                    const v4s bo = __builtin_bit_cast(v4s, make_uint2(B[c][0], B[c][1]));
-                    D[j][c] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(wf[ks], bo, D[j][c], 0, 0, 0);
-                }
-            }
-        }
-        // lane holds channel g>>1, spins 2h and 2h+1: component 6h + 3t + c is
-        // (D[c][2t], D[c][2t + 1])
-        const int ch = g >> 1;
-        if (!valid || ch >= COUT) continue;
-#pragma unroll
-        for (int j = 0; j < LY_RC; j++) {
-            if ((uint32_t)j >= nr) break;
-            void* out = field_rhs<So>(a.out, Vs, (int)((r0 + j) * COUT));
-            float o[12];
-#pragma unroll
-            for (int t = 0; t < 2; t++)
-#pragma unroll
-                for (int c = 0; c < 3; c++) {
-                    o[2 * (3 * t + c)] = D[j][c][2 * t];
-                    o[2 * (3 * t + c) + 1] = D[j][c][2 * t + 1];
-                }
-            if constexpr (std::is_same<So, SBH>::value) {
-                uint32_t w[6];
-#pragma unroll
-                for (int q = 0; q < 6; q++) w[q] = pack2_bf16(o[2 * q], o[2 * q + 1]);
-                const uint32_t base = (s << 4) + (uint32_t)ch * 3u * PB;
-                stv128(out, base + (uint32_t)h * PB, make_uint4(w[0], w[1], w[2], w[3]));
-                stv64(out, base + 2u * PB + (uint32_t)h * 8u, make_uint2(w[4], w[5]));
-            } else if constexpr (std::is_same<So, SF32>::value) {
-                const uint32_t base = (s << 4) + (uint32_t)ch * 6u * PB + (uint32_t)h * 3u * PB;
-#pragma unroll
-                for (int q = 0; q < 3; q++)
-                    stv128(out, base + (uint32_t)q * PB,
-                           make_uint4(__float_as_uint(o[4 * q]), __float_as_uint(o[4 * q + 1]),
-                                      __float_as_uint(o[4 * q + 2]), __float_as_uint(o[4 * q + 3])));
-            } else {
-                static_assert(std::is_same<So, SF32>::value || std::is_same<So, SBH>::value, "FP32 or SBH output");
-            }
-        }
-    }
+    uint32_t r0 = r_beg;
+    for (; r0 + 2 <= r_end; r0 += 2, live >>= 2)
+        if (live & 3u) ly_chunk<Si, So, CIN, COUT, NKS, 2>(a, w, PB, r0, wf);
+    if (live & 1u) ly_chunk<Si, So, CIN, COUT, NKS, 1>(a, w, PB, r0, wf);
 }
 
 // Weight gradient of one layer for one right-hand side: block partials of
@@ -555,13 +622,18 @@ __global__ __launch_bounds__(256) void k_pt_loss_fin(const double* partials, uin
 
 template <class Si, class So>
 static void launch_pt_layer_t(hipStream_t st, const PtArgs& a, int nrhs) {
-    const unsigned nchunk = (unsigned)((nrhs + TM_LY_CHUNKS_RC - 1) / TM_LY_CHUNKS_RC);
-    const dim3 grid((unsigned)((a.geo.V + LY_TS - 1) / LY_TS) * nchunk), blk(LY_THREADS);
+    // small lattices: fewer right-hand sides per block while the launch holds
+    // less than three blocks per CU
+    const unsigned ntile = (unsigned)((a.geo.V + LY_TS - 1) / LY_TS);
+    uint32_t per = LY_PER;
+    auto nchunk = [&] { return ((unsigned)nrhs + per - 1) / per; };
+    while (per > 1 && ntile * nchunk() < 768u) per >>= 1;
+    const dim3 grid(ntile * nchunk()), blk(LY_THREADS);
     const uint32_t n = (uint32_t)nrhs;
-    if (a.cin == 1 && a.cout == 1) hipLaunchKernelGGL((k_pt_layer<Si, So, 1, 1>), grid, blk, 0, st, a, n);
-    else if (a.cin == 1) hipLaunchKernelGGL((k_pt_layer<Si, So, 1, 2>), grid, blk, 0, st, a, n);
-    else if (a.cout == 1) hipLaunchKernelGGL((k_pt_layer<Si, So, 2, 1>), grid, blk, 0, st, a, n);
-    else hipLaunchKernelGGL((k_pt_layer<Si, So, 2, 2>), grid, blk, 0, st, a, n);
+    if (a.cin == 1 && a.cout == 1) hipLaunchKernelGGL((k_pt_layer<Si, So, 1, 1>), grid, blk, 0, st, a, n, per);
+    else if (a.cin == 1) hipLaunchKernelGGL((k_pt_layer<Si, So, 1, 2>), grid, blk, 0, st, a, n, per);
+    else if (a.cout == 1) hipLaunchKernelGGL((k_pt_layer<Si, So, 2, 1>), grid, blk, 0, st, a, n, per);
+    else hipLaunchKernelGGL((k_pt_layer<Si, So, 2, 2>), grid, blk, 0, st, a, n, per);
 }
 
 void launch_pt_layer(hipStream_t st, const PtArgs& a, int in_prec, int out_prec, int nrhs) {

@@ -119,3 +119,22 @@ def test_small_and_large_launches_agree(orc, solver, prec):
             ref, _ = f(dims, -1, KAPPA, MU, U, orc.noise_z4(dims, 29, 7), 0.0, 3)
             assert np.linalg.norm(x[7].cpu().numpy() - ref) < 1e-12 * np.linalg.norm(ref)
     ctx.close()
+
+
+@pytest.mark.parametrize("dims,nrhs", [((10, 14, 18, 20), 7), ((8, 10, 12, 10), 7), ((16, 16, 10, 6), 7)])
+@pytest.mark.parametrize("adjoint", [False, True])
+def test_network_right_hand_sides_per_block(orc, dims, nrhs, adjoint):
+    """Transport layers with 4, 1 and 2 right-hand sides per block (ragged last
+    tiles, pairs and a single one): each field as when it is given alone."""
+    import torch
+    import paper_1211_0126_amd as tq
+    ctx, U = _ctx(dims)
+    widths = [1, 2, 2, 1]
+    rng = np.random.default_rng(3)
+    n = orc.net_weight_count(widths)
+    tq.tm_precond_set(ctx, widths, 0.3 * (rng.standard_normal(n) + 1j * rng.standard_normal(n)))
+    x = torch.from_numpy(random_spinor(dims, 5, nrhs)).cuda()
+    y = tq.tm_precond_apply(ctx, x, adjoint=adjoint)
+    for r in range(nrhs):
+        assert torch.equal(y[r], tq.tm_precond_apply(ctx, x[r:r + 1].contiguous(), adjoint=adjoint)[0]), r
+    ctx.close()
