@@ -74,33 +74,6 @@ __global__ TM_STENCIL_R(NR, R) void k_apply(Geom geo, const void* gauge, R kappa
 // CG kernels
 // ---------------------------------------------------------------------------
 
-// NaN or overflow in a step: breakdown
-__device__ __forceinline__ bool cg_broken(const CgScal& q, double rrn) {
-    return !(rrn == rrn) || !(q.alpha == q.alpha) || rrn > 1e300;
-}
-
-// Whether a plain CG step with |r|^2 = rrn and stop quantity rel2 is followed
-// by another (q: the state before the step)
-__device__ __forceinline__ bool cg_goes_on(const CgScal& q, double rrn, double rel2) {
-    return !cg_broken(q, rrn) && !(rel2 <= q.tol2) && !(q.maxit >= 0 && q.iters + 1 >= q.maxit);
-}
-
-// End of that step (single thread)
-__device__ __forceinline__ void cg_finish_plain(CgScal& q, double rrn, double rel2) {
-    const bool broken = cg_broken(q, rrn), go = cg_goes_on(q, rrn, rel2);
-    q.iters += 1;
-    if (!go) {
-        q.status = broken ? 3 : rel2 <= q.tol2 ? 1 : 2;
-        q.active = 0;
-    }
-    if (broken) {
-        q.rflag = 0;
-        return;
-    }
-    q.beta = rrn / q.rr;
-    q.rr = rrn;
-}
-
 // End of one CG step for one right-hand side (single thread).
 __device__ inline void cg_finish_step(CgScal& q, double rrn, double rhon) {
     if (!q.reliable || cg_broken(q, rrn)) {
@@ -308,29 +281,23 @@ __global__ __launch_bounds__(256) void k_cg_p(CgArgs a) {
     void* pp = field_rhs<S>(a.p, a.geo.Vs, r);
     cx<R> rv[12], pv[12];
     double b;
-    if (a.scal_next) {  // merged reductions: finish the step here (the fields are loaded meanwhile)
+    if (a.scal_next) {
+        // Merged reductions: finish the step here.  Every wave reads the few
+        // fields and the partials first, loads its part of r and p while they
+        // are on the way, and one wave hands the state on.  (9x11x7x13, FP32:
+        // 5 us; with a copy of the state per lane, through LDS and scratch, 12.)
+        StepEnd e;
+        const double* parts = a.partials2 + (size_t)r * a.npart;
+        e.begin(a.scal + r, parts, a.npart);
+        TM_MEM_FENCE();
         if (on) {
             load_spinor<S, R>(field_rhs<S>(a.r, a.geo.Vs, r), a.geo.Vs, s, rv);
             load_spinor<S, R>(pp, a.geo.Vs, s, pv);
         }
         TM_MEM_FENCE();
-        // (every wave reads the few fields that it needs and one thread hands
-        // the state on: a copy of the struct per lane went through LDS and
-        // scratch, 12 us instead of 5 at 9x11x7x13)
-        const CgScal& q = a.scal[r];
-        CgScal& n = a.scal_next[r];
-        if (!q.active) {
-            if (s == 0) n = q;
-            return;
-        }
-        const double rrn = wave_partials(a.partials2 + (size_t)r * a.npart, a.npart);
-        b = rrn / q.rr;
-        const bool go = cg_goes_on(q, rrn, rrn / q.bb);
-        if (s == 0) {
-            n = q;
-            cg_finish_plain(n, rrn, rrn / q.bb);
-        }
-        if (!go) return;
+        b = e.end(parts, a.npart);
+        if (s < 64) e.write(a.scal_next + r, b);
+        if (!e.go) return;
     } else {
         const CgScal& q = a.scal[r];
         if (!q.active) return;

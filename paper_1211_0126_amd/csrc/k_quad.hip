@@ -328,6 +328,108 @@ __global__ __launch_bounds__(256) void k_quad_mp(CgArgs a, EoCg e) {
     norm_partial<R>(sh, on, a.partials + (size_t)q.r * q.nws + q.ws);
 }
 
+// K1 with the step before finished in it (whole lattice, FP64 and FP32):
+// p' = r + beta p is formed where the hops and the operator read it and written
+// to the other direction buffer pn, so k_cg_p and its launch go: each wave sums
+// |r|^2 from the partials of the last K2 (scal_next not null), forms beta and
+// the stop test and the first thread hands the state on; the fields and links
+// are loaded meanwhile.  The launch is a chain of latencies.  4^4, FP64: an
+// iteration of three launches (5.9 + 6.9 + 4.8 us) -> two (7.0 + 6.1 us); a
+// solve of 12 sources 390 -> 359 us.
+template <int MU, typename R, class S, class G, class B>
+__device__ __forceinline__ void dir_hops_fold(const Geom& geo, const void* links, const void* pin, const void* rin,
+                                              uint32_t s, cx<R>* sh, B&& beta) {
+    const uint32_t lane = threadIdx.x & 63u;
+    const long Vs = geo.Vs;
+    const Site c = site_coords(geo, s);
+    const uint32_t yf = nb_fwd(geo, s, c, MU), yb = nb_bwd(geo, s, c, MU);
+    cx<R> pf[12], rf[12], pb[12], rb[12], U[3][3], Ub[3][3], f[6], b[6], h[6];
+    load_spinor<S, R>(pin, Vs, yf, pf);
+    load_spinor<S, R>(rin, Vs, yf, rf);
+    load_spinor<S, R>(pin, Vs, yb, pb);
+    load_spinor<S, R>(rin, Vs, yb, rb);
+    load_link<G, R>(links, Vs, MU, s, U);
+    load_link<G, R>(links, Vs, MU, yb, Ub);
+    const R be = beta();
+#pragma unroll
+    for (int k = 0; k < 12; k++) {
+        pf[k] = rf[k] + be * pf[k];
+        pb[k] = rb[k] + be * pb[k];
+    }
+    proj<MU, 1>(pf, h);
+    if (MU == 3 && c.t + 1 == geo.L[3] && geo.t_bc < 0) negate6(h);
+    su3_mul(U, h, f);
+    proj<MU, -1>(pb, h);
+    if (MU == 3 && c.t == 0 && geo.t_bc < 0) negate6(h);
+    su3_dag_mul(Ub, h, b);
+#pragma unroll
+    for (int k = 0; k < 6; k++) {
+        sh[((2 * MU) * 6 + k) * 64 + lane] = f[k];
+        sh[((2 * MU + 1) * 6 + k) * 64 + lane] = b[k];
+    }
+}
+
+template <typename R, class S, class G>
+__global__ __launch_bounds__(256) void k_quad_mp_fold(CgArgs a) {
+    __shared__ cx<R> sh[8 * 6 * 64];
+    const Geom& geo = a.geo;
+    const QuadSite q = quad_site<false>(geo, a.nrhs);
+    const long Vs = geo.Vs;
+    const bool on = q.s < (uint32_t)geo.V;
+    const uint32_t s = on ? q.s : 0u;  // lanes past the lattice compute site 0 and store nothing
+    const void *pin = field_rhs<S>(a.p, Vs, q.r), *rin = field_rhs<S>(a.r, Vs, q.r);
+    StepEnd e;
+    const double* parts = a.partials2 + (size_t)q.r * a.npart;
+    e.begin(a.scal + q.r, parts, a.npart);
+    const double bst = a.scal[q.r].beta;
+    TM_MEM_FENCE();
+    constexpr int N = part_comps<S>();
+    cx<R> o[N], rv[N];
+    if (q.w < part_waves<S>()) {
+        load_part<S, R, N>(pin, Vs, s, q.w, o);
+        load_part<S, R, N>(rin, Vs, s, q.w, rv);
+    }
+    bool act = e.c.active != 0;
+    double bd = bst;
+    auto beta = [&]() {
+        TM_MEM_FENCE();  // (the fields are loaded before the sum is waited for)
+        if (a.scal_next) {
+            bd = e.end(parts, a.npart);
+            act = e.go;
+        }
+        return (R)bd;
+    };
+    switch (q.w) {
+    case 0: dir_hops_fold<0, R, S, G>(geo, a.gauge, pin, rin, s, sh, beta); break;
+    case 1: dir_hops_fold<1, R, S, G>(geo, a.gauge, pin, rin, s, sh, beta); break;
+    case 2: dir_hops_fold<2, R, S, G>(geo, a.gauge, pin, rin, s, sh, beta); break;
+    default: dir_hops_fold<3, R, S, G>(geo, a.gauge, pin, rin, s, sh, beta); break;
+    }
+    const R tw = (R)a.twist, kap = (R)a.kappa, be = (R)bd;
+    if (a.scal_next && q.ws == 0 && q.w == 3) e.write(a.scal_next + q.r, bd);
+    __syncthreads();
+    if (!act) return;  // uniform over the block: every wave summed the same partials
+    if (on)
+        for_part<S>(q.w, [&](auto W) {
+            constexpr int K0 = W.value * N;
+#pragma unroll
+            for (int c = 0; c < N; c++) o[c] = rv[c] + be * o[c];
+            store_part<S, R, N>(field_rhs<S>(a.pn, Vs, q.r), Vs, q.s, W.value, o);
+            o[0] = op_comp<false, false, K0>(o[0], sh, kap, tw);
+            o[1] = op_comp<false, false, K0 + 1>(o[1], sh, kap, tw);
+            o[2] = op_comp<false, false, K0 + 2>(o[2], sh, kap, tw);
+            if constexpr (N == 4) o[3] = op_comp<false, false, K0 + 3>(o[3], sh, kap, tw);
+            settle<N>(o);
+            store_part<S, R, N>(field_rhs<S>(a.t, Vs, q.r), Vs, q.s, W.value, o);
+        });
+    __syncthreads();  // (every wave has read the hops)
+    if (q.w < part_waves<S>())
+#pragma unroll
+        for (int c = 0; c < N; c++) sh[(q.w * N + c) * 64 + (threadIdx.x & 63u)] = o[c];
+    __syncthreads();
+    norm_partial<R>(sh, on, a.partials + (size_t)q.r * q.nws + q.ws);
+}
+
 // K2: q = M^dag t (EO: D^dag t - kappa^2 H_oe^dag y), r -= alpha q, |r|^2, and
 // unless XFREE x += alpha p
 template <bool EO, typename R, class S, class G, class X, typename RX, bool XFREE>
@@ -335,7 +437,10 @@ __global__ __launch_bounds__(256) void k_quad_upd(CgArgs a, EoCg e) {
     __shared__ cx<R> sh[8 * 6 * 64];
     const Geom& geo = a.geo;
     const QuadSite q = quad_site<EO>(geo, a.nrhs);
-    const bool act = a.scal[q.r].active != 0;
+    StepAlpha sa;
+    sa.begin(a, q.r);
+    TM_MEM_FENCE();  // (the fields are loaded while the partials are on the way)
+    const bool act = sa.active != 0;
     const long Vs = geo.Vs;
     const bool on = q.s < (uint32_t)geo.V;
     const void* gout = EO ? e.godd : a.gauge;
@@ -343,13 +448,21 @@ __global__ __launch_bounds__(256) void k_quad_upd(CgArgs a, EoCg e) {
     if (on) quad_hops<EO, true, R, S, G>(geo, gout, gin, field_rhs<S>(EO ? e.y : a.t, Vs, q.r), q.s, 1, q.w, sh);
     const R tw = (R)(-a.twist), kap = EO ? (R)(-a.kappa * a.kappa) : (R)a.kappa;
     constexpr int N = part_comps<S>();
-    cx<R> o[N], rv[N];
+    cx<R> o[N], rv[N], pv[N];
+    cx<RX> xv[N];
     void* rp = field_rhs<S>(a.r, Vs, q.r);
+    void* xp = XFREE ? nullptr : field_rhs<X>(a.x, Vs, q.r);
     if (on && q.w < part_waves<S>()) {
         load_part<S, R, N>(field_rhs<S>(a.t, Vs, q.r), Vs, q.s, q.w, o);
         load_part<S, R, N>(rp, Vs, q.s, q.w, rv);
+        if constexpr (!XFREE) {
+            static_assert(part_comps<X>() == N, "x in parts of the same components");
+            load_part<S, R, N>(field_rhs<S>(a.p, Vs, q.r), Vs, q.s, q.w, pv);
+            load_part<X, RX, N>(xp, Vs, q.s, q.w, xv);
+        }
     }
-    const double alpha = step_alpha(a, q.r, q.ws == 0 && threadIdx.x == 0);
+    TM_MEM_FENCE();
+    const double alpha = sa.end(a, q.r, q.ws == 0 && threadIdx.x == 0);
     const R al = (R)alpha;
     __syncthreads();
     if (!act) return;  // uniform over the block
@@ -366,12 +479,6 @@ __global__ __launch_bounds__(256) void k_quad_upd(CgArgs a, EoCg e) {
             round_part<S, R, N>(rv);
             store_part<S, R, N>(rp, Vs, q.s, W.value, rv);
             if constexpr (!XFREE) {
-                static_assert(part_comps<X>() == N, "x in parts of the same components");
-                cx<RX> xv[N];
-                cx<R> pv[N];
-                void* xp = field_rhs<X>(a.x, Vs, q.r);
-                load_part<S, R, N>(field_rhs<S>(a.p, Vs, q.r), Vs, q.s, W.value, pv);
-                load_part<X, RX, N>(xp, Vs, q.s, W.value, xv);
                 const RX alx = (RX)alpha;
 #pragma unroll
                 for (int c = 0; c < N; c++)
@@ -395,6 +502,16 @@ __global__ __launch_bounds__(256) void k_quad_upd(CgArgs a, EoCg e) {
 // 466 / 441; FP32 whole lattice 12^3 x 24, 1 (648) 517 / 482, 16^3 x 32, 1
 // (2048) 971 / 989)
 bool use_quad(int64_t V, int nrhs) { return (V + 63) / 64 * nrhs <= 1536; }
+
+// launches whose K1 finishes the step before (k_quad_mp_fold): those whose
+// blocks are all resident at once, one per CU in FP64 and two in FP32.  LP
+// solves without / with: FP64 10x12x8x14, 1 source (210 blocks) 434 / 394 us,
+// 8^4, 4 (256) 437 / 396, 10x12x8x14, 2 (420) 523 / 537, 12^3 x 24, 1 (648)
+// 680 / 775; FP32 9x11x7x13, 1 (141) 795 / 758, 10x12x8x14, 2 (420) 414 / 393,
+// 12^3 x 24, 1 (648) 455 / 454, 2 (1296) 614 / 668.
+bool use_quad_fold(int64_t V, int nrhs, int prec) {
+    return (V + 63) / 64 * nrhs <= (prec == P_F64 ? 256 : prec == P_F32 ? 512 : 0);
+}
 
 static dim3 quad_grid(const Geom& g, int nrhs) { return dim3((unsigned)((g.V + 63) / 64 * nrhs)); }
 
@@ -446,6 +563,14 @@ void launch_quad_mp(hipStream_t st, const CgArgs& a, const EoCg* e, int prec) {
         e ? quad_mp_typed<true, float, SBF16, GF32>(st, a, *e) : quad_mp_typed<false, float, SBF16, GF32>(st, a, none);
         break;
     }
+}
+// prec: FP64 or FP32
+void launch_quad_mp_fold(hipStream_t st, const CgArgs& a, int prec) {
+    const dim3 grid = quad_grid(a.geo, a.nrhs);
+    if (prec == P_F64)
+        hipLaunchKernelGGL((k_quad_mp_fold<double, SF64, GF64>), grid, dim3(256), 0, st, a);
+    else
+        hipLaunchKernelGGL((k_quad_mp_fold<float, SF32, GF32>), grid, dim3(256), 0, st, a);
 }
 void launch_quad_upd(hipStream_t st, const CgArgs& a, const EoCg* e, int prec, bool xfree) {
     const EoCg none = {};

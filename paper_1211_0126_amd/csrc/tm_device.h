@@ -3,6 +3,8 @@
 // reductions.  Included only by the .hip translation units.
 #pragma once
 
+#include <cstddef>
+
 #include <hip/hip_runtime.h>
 #include <type_traits>
 #include <stdint.h>
@@ -594,9 +596,22 @@ __device__ __forceinline__ double wave_sum(double v) {
 
 // Sum of n partials by one wave, in every lane (lane l adds l, l + 64, ... in
 // order; eight loads in flight).
-__device__ __forceinline__ double wave_partials(const double* p, uint32_t n) {
+// (partials_begin only issues the loads of the first 512, so that a kernel can
+// load its fields before it waits for them in partials_end)
+struct PartLoads {
+    double x[8];
+};
+__device__ __forceinline__ PartLoads partials_begin(const double* p, uint32_t n) {
+    PartLoads l;
+#pragma unroll
+    for (uint32_t j = 0; j < 8; j++) l.x[j] = p[min((threadIdx.x & 63u) + 64 * j, n - 1)];
+    return l;
+}
+__device__ __forceinline__ double partials_end(const PartLoads& l, const double* p, uint32_t n) {
     double v = 0;
-    for (uint32_t i = threadIdx.x & 63u; i < n; i += 512) {
+#pragma unroll
+    for (uint32_t j = 0; j < 8; j++) v += (threadIdx.x & 63u) + 64 * j < n ? l.x[j] : 0.0;
+    for (uint32_t i = (threadIdx.x & 63u) + 512; i < n; i += 512) {
         double x[8];
 #pragma unroll
         for (uint32_t j = 0; j < 8; j++) x[j] = p[min(i + 64 * j, n - 1)];
@@ -604,6 +619,9 @@ __device__ __forceinline__ double wave_partials(const double* p, uint32_t n) {
         for (uint32_t j = 0; j < 8; j++) v += i + 64 * j < n ? x[j] : 0.0;
     }
     return wave_sum(v);
+}
+__device__ __forceinline__ double wave_partials(const double* p, uint32_t n) {
+    return partials_end(partials_begin(p, n), p, n);
 }
 
 // Sum of v over a 256-thread block; result valid in thread 0.
@@ -638,18 +656,119 @@ struct StencilOcc {
 // Step length of right-hand side r for K2: alpha as k_cg_alpha left it, or with
 // merged reductions formed by every wave from K1's partials (and recorded by
 // the lane that says it is first)
+struct StepAlpha {
+    PartLoads l;
+    double rr, alpha;
+    int active, iters;
+    template <class Args>
+    __device__ __forceinline__ void begin(const Args& a, int r) {
+        const CgScal& q = a.scal[r];
+        active = q.active;
+        if (a.scal_next) {
+            l = partials_begin(a.partials + (size_t)r * a.npart, a.npart);
+            rr = q.rr;
+            iters = q.iters;
+        } else
+            alpha = q.alpha;
+    }
+    template <class Args>
+    __device__ __forceinline__ double end(const Args& a, int r, bool first) {
+        if (!a.scal_next) return alpha;
+        const double tt = partials_end(l, a.partials + (size_t)r * a.npart, a.npart);
+        alpha = tt > 0 ? rr / tt : 0.0;
+        if (first && active) {
+            a.scal[r].tt = tt;
+            a.scal[r].alpha = alpha;
+            if (a.ahist) a.ahist[(size_t)r * a.ring + (iters % a.ring)] = alpha;
+        }
+        return alpha;
+    }
+};
 template <class Args>
 __device__ __forceinline__ double step_alpha(const Args& a, int r, bool first) {
-    if (!a.scal_next) return a.scal[r].alpha;
-    const double tt = wave_partials(a.partials + (size_t)r * a.npart, a.npart);
-    const double alpha = tt > 0 ? a.scal[r].rr / tt : 0.0;
-    if (first && a.scal[r].active) {
-        a.scal[r].tt = tt;
-        a.scal[r].alpha = alpha;
-        if (a.ahist) a.ahist[(size_t)r * a.ring + (a.scal[r].iters % a.ring)] = alpha;
-    }
-    return alpha;
+    StepAlpha s;
+    s.begin(a, r);
+    return s.end(a, r, first);
 }
+
+// NaN or overflow in a step: breakdown
+__device__ __forceinline__ bool cg_broken(const CgScal& q, double rrn) {
+    return !(rrn == rrn) || !(q.alpha == q.alpha) || rrn > 1e300;
+}
+
+// Whether a plain CG step with |r|^2 = rrn and stop quantity rel2 is followed
+// by another (q: the state before the step)
+__device__ __forceinline__ bool cg_goes_on(const CgScal& q, double rrn, double rel2) {
+    return !cg_broken(q, rrn) && !(rel2 <= q.tol2) && !(q.maxit >= 0 && q.iters + 1 >= q.maxit);
+}
+
+// End of that step (single thread)
+__device__ __forceinline__ void cg_finish_plain(CgScal& q, double rrn, double rel2) {
+    const bool broken = cg_broken(q, rrn), go = cg_goes_on(q, rrn, rel2);
+    q.iters += 1;
+    if (!go) {
+        q.status = broken ? 3 : rel2 <= q.tol2 ? 1 : 2;
+        q.active = 0;
+    }
+    if (broken) {
+        q.rflag = 0;
+        return;
+    }
+    q.beta = rrn / q.rr;
+    q.rr = rrn;
+}
+
+// The plain step of a right-hand side finished by a kernel that goes on with it:
+// the fields every wave needs (loaded by begin, before the kernel's own loads)
+// and the state handed on by one wave, a word per lane.
+struct StepEnd {
+    CgScal c;  // rr, bb, alpha, tol2, maxit, iters, active of the state before
+    PartLoads l;
+    uint64_t word;
+    double rrn;
+    bool go;
+    static constexpr uint32_t kWords = sizeof(CgScal) / 8;
+
+    __device__ __forceinline__ void begin(const CgScal* q, const double* p, uint32_t n) {
+        l = partials_begin(p, n);
+        c.rr = q->rr;
+        c.bb = q->bb;
+        c.alpha = q->alpha;
+        c.tol2 = q->tol2;
+        c.maxit = q->maxit;
+        c.iters = q->iters;
+        c.active = q->active;
+        word = ((const uint64_t*)q)[min(threadIdx.x & 63u, kWords - 1)];
+    }
+    // beta; go: another step follows
+    __device__ __forceinline__ double end(const double* p, uint32_t n) {
+        rrn = partials_end(l, p, n);
+        go = c.active && cg_goes_on(c, rrn, rrn / c.bb);
+        return rrn / c.rr;
+    }
+    // (whole wave) the state after the step, as cg_finish_plain leaves it
+    __device__ __forceinline__ void write(CgScal* next, double beta) const {
+        constexpr uint32_t W_RR = offsetof(CgScal, rr) / 8, W_BETA = offsetof(CgScal, beta) / 8,
+                           W_IT = offsetof(CgScal, maxit) / 8, W_ACT = offsetof(CgScal, active) / 8,
+                           W_FLAG = offsetof(CgScal, rflag) / 8;
+        static_assert(offsetof(CgScal, iters) == 8 * W_IT + 4 && offsetof(CgScal, active) == 8 * W_ACT &&
+                          offsetof(CgScal, status) == 8 * W_ACT + 4 && offsetof(CgScal, rflag) == 8 * W_FLAG &&
+                          sizeof(CgScal) == 8 * kWords,
+                      "words of the state");
+        const uint32_t lane = threadIdx.x & 63u;
+        uint64_t w = word;
+        if (c.active) {
+            const bool broken = cg_broken(c, rrn);
+            const uint32_t status = broken ? 3u : rrn / c.bb <= c.tol2 ? 1u : 2u;
+            if (lane == W_RR && !broken) w = __builtin_bit_cast(uint64_t, rrn);
+            if (lane == W_BETA && !broken) w = __builtin_bit_cast(uint64_t, beta);
+            if (lane == W_IT) w = (w & 0xFFFFFFFFu) | ((uint64_t)(uint32_t)(c.iters + 1) << 32);
+            if (lane == W_ACT && !go) w = (uint64_t)status << 32;
+            if (lane == W_FLAG && broken) w &= ~(uint64_t)0xFFFFFFFFu;
+        }
+        if (lane < kWords) ((uint64_t*)next)[lane] = w;
+    }
+};
 
 }  // namespace tmq
 

@@ -152,8 +152,12 @@ struct EoCg {
 };
 // small launches: a direction per wave (k_quad.hip); e null for the whole lattice
 bool use_quad(int64_t V, int nrhs);
+bool use_quad_fold(int64_t V, int nrhs, int prec);
 void launch_quad_lin(hipStream_t st, const EoArgs& a, int prec, bool dag);
 void launch_quad_mp(hipStream_t st, const CgArgs& a, const EoCg* e, int prec);
+// K1 with the step before finished in it: reads p, writes pn = r + beta p (FP64
+// and FP32, whole lattice)
+void launch_quad_mp_fold(hipStream_t st, const CgArgs& a, int prec);
 void launch_quad_upd(hipStream_t st, const CgArgs& a, const EoCg* e, int prec, bool xfree);
 // kinds of launch_eo_lin: out = POST(PRE(b) + c H in)
 enum { EO_Y = 0, EO_Y_DAG = 1, EO_T = 2, EO_T_DAG = 3, EO_SRC = 4, EO_REC = 5 };

@@ -870,6 +870,12 @@ static tm_status solve_block(tm_ctx* ctx, const tsm_solve_params* p, uint64_t se
     // merged reductions (as in solve_block_eo)
     const bool merged = !rel && !track && a.tseg == 0 && merge_parts(a.npart, nrhs);
     const bool quad = a.tseg == 0 && use_quad(g.V, nrhs);
+    // small launches in FP64 and FP32 also form p in K1, alternating between two
+    // buffers (the sources are not needed any more); the last step of a chunk is
+    // finished by a launch of its own
+    const bool fold = merged && quad && use_quad_fold(g.V, nrhs, prec);
+    int tr = 0;  // states written by K1 so far
+    void* const pbuf[2] = {a.p, eta};
     auto state = [&](int k) { return scal0 + (merged && (k & 1) ? kMaxBlock : 0); };
     const CgArgs a0 = a;
     const int vtag = prof_tag(prec, prec == P_F64 ? 1 : nr, TM_SOLVER_CG, a.tseg);
@@ -899,7 +905,30 @@ static tm_status solve_block(tm_ctx* ctx, const tsm_solve_params* p, uint64_t se
             k = std::min(k, kRing - 1 - (done - k0));
         }
         const CgBytes by = cg_bytes(g, prec, n_active, ringm, track);
+        auto fold_steps = [&](int n) {
+            CgArgs a = a0;
+            for (int i = 0; i < n; i++) {
+                a.p = pbuf[(done + i) & 1];
+                a.pn = pbuf[(done + i + 1) & 1];
+                a.scal = state(i ? tr + i - 1 : tr);
+                a.scal_next = i ? state(tr + i) : nullptr;
+                prof_begin(ctx, TM_KC_DSLASH, vtag);
+                launch_quad_mp_fold(st, a, prec);
+                prof_end(ctx, TM_KC_DSLASH, by.k1 + by.k3);
+                a.p = a.pn;
+                a.scal = a.scal_next = state(tr + i);  // (K2 only looks whether scal_next is there)
+                prof_begin(ctx, TM_KC_DSLASH_UPD, vtag);
+                launch_quad_upd(st, a, nullptr, prec, false);
+                prof_end(ctx, TM_KC_DSLASH_UPD, by.k2);
+            }
+            a.scal_next = nullptr;
+            a.partials = a.partials2;
+            prof_begin(ctx, TM_KC_OTHER);
+            launch_cg_beta(st, a, false);
+            prof_end(ctx, TM_KC_OTHER, 0.0);
+        };
         auto steps = [&](int n) {
+            if (fold) return fold_steps(n);
             for (int i = 0; i < n; i++) {
                 CgArgs a = a0;
                 if (ringm) {
@@ -956,7 +985,7 @@ static tm_status solve_block(tm_ctx* ctx, const tsm_solve_params* p, uint64_t se
             std::snprintf(key, sizeof(key), "cg|%p|%p|%p|%p|%p|%p|%p|%p|%p|%p|%p|%p|%d|%d|%d|%d|%d|%d|%d|%d|%llx", a0.p,
                           a0.t, a0.r, a0.x, a0.rho, (void*)a0.scal, (void*)a0.partials, (void*)a0.partials2, x64, t64,
                           b64, (void*)a0.eta64, prec, nr, a0.tseg, (int)track, (int)rel, nrhs, k,
-                          ringm ? done % kRing : (merged ? done & 1 : -1),
+                          ringm ? done % kRing : (fold ? 2 + 2 * (done & 1) + (tr & 1) : merged ? done & 1 : -1),
                           (unsigned long long)ctx->ws_digest);
             auto it = ctx->graphs.find(key);
             if (it == ctx->graphs.end()) {
@@ -978,7 +1007,8 @@ static tm_status solve_block(tm_ctx* ctx, const tsm_solve_params* p, uint64_t se
         }
         TM_HIP(hipGetLastError());
         done += k;
-        a.scal = state(done);
+        tr += k - 1;
+        a.scal = state(fold ? tr : done);
         TM_HIP(hipMemcpyAsync(ctx->scal_host, a.scal, sizeof(CgScal) * nrhs, hipMemcpyDeviceToHost, st));
         TM_HIP(hipStreamSynchronize(st));
         n_active = active_count(ctx, nrhs);

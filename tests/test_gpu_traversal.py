@@ -138,3 +138,31 @@ def test_network_right_hand_sides_per_block(orc, dims, nrhs, adjoint):
     for r in range(nrhs):
         assert torch.equal(y[r], tq.tm_precond_apply(ctx, x[r:r + 1].contiguous(), adjoint=adjoint)[0]), r
     ctx.close()
+
+
+@pytest.mark.parametrize("graphs", [False, True])
+@pytest.mark.parametrize("maxit", [1, 2, 8, 9, 21])
+def test_cg_steps_finished_in_the_next_launch(orc, maxit, graphs):
+    """Lattices of few waves (the last one ragged): the direction and the stop
+    test of a step are formed by the next one's first stencil, the last step of
+    a chunk by a launch of its own.  Truncated inside and at the ends of chunks,
+    repeated, eager and captured: FP64 iterates against the oracle (1e-12) and
+    FP32 ones against FP64 (2e-5: FP32 rounding over 21 steps)."""
+    import torch
+    import paper_1211_0126_amd as tq
+    dims = (3, 5, 4, 6)
+    U = make_gauge(dims, 0.25, 17)
+    stream = torch.cuda.Stream()  # (graphs need a stream of their own)
+    with torch.cuda.stream(stream):
+        ctx = tq.tm_create(dims, KAPPA, MU, -1, stream=stream)
+        tq.tm_gauge_load(ctx, U)
+        n0 = tq.tm_set_graphs(ctx, graphs)
+        ref, _ = orc.cgnr(dims, -1, KAPPA, MU, U, orc.noise_z4(dims, 29, 7), 0.0, maxit)
+        for prec, tol in ((tq.PREC_F64, 1e-12), (tq.PREC_F32, 2e-5)):
+            p = tq.solve_params(prec=prec, tol=0.0, max_iter=maxit, rhs_block=4, true_resid=0)
+            for _ in range(3):
+                x, st, _ = tq.tsm_solve_batch(ctx, p, 29, [7, 8])
+                assert st[0]["iters"] == maxit
+                assert np.linalg.norm(x[0].cpu().numpy() - ref) < tol * np.linalg.norm(ref)
+        assert (tq.tm_set_graphs(ctx) > n0) == graphs
+        ctx.close()
