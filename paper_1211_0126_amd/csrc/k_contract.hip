@@ -281,7 +281,7 @@ __device__ __forceinline__ cx<A> z4_unit(uint32_t nb, uint32_t flip) {
 }
 
 // One-derivative loops, stage A: one lane per (x, z, t) row, spin half h
-// and direction mu (grid z); the A slice of (source r, direction mu) is
+// and direction mu; the A slice of (source r, direction mu) is
 // r * 4 + mu.  With f = U s(x+mu) - U^dag s(x-mu) and g the same of eta, the
 // source-side transport moved onto the solution and the terms of the backward
 // hop shifted by mu, the loop of a link is
@@ -296,10 +296,13 @@ __device__ __forceinline__ cx<A> z4_unit(uint32_t nb, uint32_t flip) {
 // about 1e-6 relative); an FP64 one FP64 throughout.
 // Bound by FP64 arithmetic and the latency of a row site's loads (about 700
 // vector instructions per row site and lane, two waves per SIMD): four sources
-// at 24^3 x 48 from canonical solutions 0.86 ms, against 1.41 with the four
-// transports.
+// at 24^3 x 48 from canonical solutions 0.74 ms, against 1.41 with the four
+// transports and 0.85 with the blocks of a row dealt to all XCDs, where 4.4 GB
+// came from behind L2 instead of 2.0 (directions fastest: 0.82; row blocks in
+// groups of 4 or 16 per direction: 0.75; blocks of four waves: 0.75).
+constexpr int kDerivBlock = 64;
 template <class S>
-__global__ __launch_bounds__(256) void k_contract_d(ContractArgs a) {
+__global__ __launch_bounds__(kDerivBlock) void k_contract_d(ContractArgs a) {
     constexpr bool F64 = S::NV == 12;
     using A = typename std::conditional<F64, double, float>::type;
     using GL = typename std::conditional<F64, GF64, GF32>::type;
@@ -307,11 +310,12 @@ __global__ __launch_bounds__(256) void k_contract_d(ContractArgs a) {
     const Geom& g = a.geo;
     const int Lx = g.L[0], Ly = g.L[1], Lz = g.L[2], Lt = g.L[3];
     const long nrow = (long)Lx * Lz * Lt;
-    // the source is the fastest grid index: the blocks of all sources on
-    // the same rows run together and share the links through L2
-    const long tid = (long)blockIdx.y * 256 + threadIdx.x;
-    const int r = blockIdx.x;
-    const int mu = blockIdx.z;
+    // an XCD takes one range of rows: the sources of a row block next to each
+    // other (they share the links through its L2), then its four directions
+    // (they share the solution)
+    const uint32_t L = xcd_block(blockIdx.x, gridDim.x), Lr = L / (uint32_t)a.nrhs;
+    const int r = (int)(L - Lr * (uint32_t)a.nrhs), mu = (int)(Lr & 3u);
+    const long tid = (long)(Lr >> 2) * kDerivBlock + threadIdx.x;
     if (tid >= 2 * nrow) return;
     long row;
     int h;
@@ -477,13 +481,13 @@ void launch_contract(hipStream_t st, const ContractArgs& a0, int xprec, bool can
     ContractArgs a = a0;
     a.nrhs = a0.nrhs * a0.nmu;
     if (a0.est == 3) {
-        dim3 gd(ga.y, ga.x, 4);
+        const dim3 gd((unsigned)((nrow + kDerivBlock - 1) / kDerivBlock) * (unsigned)a0.nrhs * 4u);
         if (canon)
-            hipLaunchKernelGGL((k_contract_d<Canon<SF64>>), gd, dim3(256), 0, st, a0);
+            hipLaunchKernelGGL((k_contract_d<Canon<SF64>>), gd, dim3(kDerivBlock), 0, st, a0);
         else if (xprec == P_F64)
-            hipLaunchKernelGGL((k_contract_d<SF64>), gd, dim3(256), 0, st, a0);
+            hipLaunchKernelGGL((k_contract_d<SF64>), gd, dim3(kDerivBlock), 0, st, a0);
         else
-            hipLaunchKernelGGL((k_contract_d<SF32>), gd, dim3(256), 0, st, a0);
+            hipLaunchKernelGGL((k_contract_d<SF32>), gd, dim3(kDerivBlock), 0, st, a0);
     }
     auto run_a = [&](auto est) {
         constexpr int E = decltype(est)::value;
