@@ -166,3 +166,31 @@ def test_cg_steps_finished_in_the_next_launch(orc, maxit, graphs):
                 assert np.linalg.norm(x[0].cpu().numpy() - ref) < tol * np.linalg.norm(ref)
         assert (tq.tm_set_graphs(ctx) > n0) == graphs
         ctx.close()
+
+
+@pytest.mark.parametrize("solver,kw,bound", [
+    # M^dag M >= (2 kappa mu)^2 and |M| < 2.4: two solutions with true residuals
+    # below 1e-10 differ by less than 2e-10 * 2.4 / (2 kappa mu) = 3.7e-7
+    (2, dict(tol=1e-10, max_iter=-1, reliable=1, delta=0.1), 4e-7),
+    # the same directions and step lengths, FP32 sums of five terms
+    (0, dict(tol=0.0, max_iter=5), 1e-5)])
+def test_kept_directions_only_where_the_workspace_has_room(solver, kw, bound):
+    """16-bit solves that keep their directions in a ring where the workspace has
+    room, and where it lacks a MiB for that update x in every iteration."""
+    import paper_1211_0126_amd as tq
+    dims = (8, 8, 8, 8)
+    U = make_gauge(dims, 0.25, 17)
+    p = tq.solve_params(prec=tq.PREC_F16, rhs_block=8, solver=solver, **kw)
+    x, size = [], None
+    for _ in range(2):
+        ctx = tq.tm_create(dims, KAPPA, MU, -1, workspace_bytes=size)
+        tq.tm_gauge_load(ctx, U)
+        for _ in range(2):
+            y, st, _ = tq.tsm_solve_batch(ctx, p, 29, list(range(8)))
+            assert all(s["converged"] for s in st) or kw["tol"] == 0.0
+            x.append(y.cpu())
+        use = ctx.workspace_usage()
+        size = use["persistent"] + use["peak_scratch"] - (1 << 20)
+        ctx.close()
+    assert (x[0] == x[1]).all() and (x[2] == x[3]).all()
+    assert (x[0] - x[2]).norm() < bound * x[0].norm()
