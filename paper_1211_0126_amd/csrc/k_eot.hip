@@ -240,7 +240,7 @@ __global__ TM_EOT(NR) void k_eot_mp(CgArgs a, EoCg e, const void* cin, void* cou
                 for (int k = 0; k < 12; k++) t[k] = t[k] + k2 * acc[r][k];
                 round_storage<S, float>(t);
                 store_spinor_cp<S, float, TM_CP_K1T>(field_rhs<S>(cout, Vs, r0 + r), Vs, T.h, t);
-                part[r] = spinor_norm2(t);
+                part[r] = norm2_own(t);
             }
         }
 #pragma unroll
@@ -297,7 +297,7 @@ __global__ TM_EOT(NR) void k_eot_upd(CgArgs a, EoCg e) {
                 for (int k = 0; k < 12; k++) rv[k] = rv[k] - al * q[k];
                 round_storage<S, float>(rv);
                 store_spinor_cp<S, float, TM_CP_K2>(rp, Vs, T.h, rv);
-                prr[r] = spinor_norm2(rv);
+                prr[r] = norm2_own(rv);
                 load_spinor_cp<S, float, TM_CP_K2>(field_rhs<S>(a.p, Vs, r0 + r), Vs, T.h, pv);
                 cx<float> xv[12];
                 void* xp = field_rhs<X>(a.x, Vs, r0 + r);
@@ -313,7 +313,7 @@ __global__ TM_EOT(NR) void k_eot_upd(CgArgs a, EoCg e) {
                     for (int k = 0; k < 12; k++) rh[k] = rh[k] - al * tc[k];
                     round_storage<S, float>(rh);
                     store_spinor_cp<S, float, TM_CP_K2>(hp, Vs, T.h, rh);
-                    prho[r] = spinor_norm2(rh);
+                    prho[r] = norm2_own(rh);
                 }
             }
         }

@@ -170,7 +170,7 @@ __global__ TM_MARCH_R(NR, R) void k_tm_mp(CgArgs a) {
                                           round_storage<S, R>(out[r]);
                                           store_spinor_cp<S, R, TM_CP_K1T>(field_rhs<S>(a.t, Vs, r0 + r), Vs, s,
                                                                            out[r]);
-                                          part[r] += spinor_norm2(out[r]);
+                                          part[r] += norm2_own(out[r]);
                                       }
                                   });
     }
@@ -228,7 +228,7 @@ __global__ TM_MARCH_R(NR, R) void k_tm_upd(CgArgs a) {
                     for (int k = 0; k < 12; k++) rv[k] = rv[k] - al[r] * q[r][k];
                     round_storage<S, R>(rv);
                     store_spinor_cp<S, R, TM_CP_K2>(rp, Vs, s, rv);
-                    prr[r] += spinor_norm2(rv);
+                    prr[r] += norm2_own(rv);
                     if (!XFREE) {
                         cx<R> pv[12];
                         load_spinor_cp<S, R, TM_CP_K2>(field_rhs<S>(a.p, Vs, r0 + r), Vs, s, pv);
@@ -249,7 +249,7 @@ __global__ TM_MARCH_R(NR, R) void k_tm_upd(CgArgs a) {
                         for (int k = 0; k < 12; k++) rh[k] = rh[k] - al[r] * tc[k];
                         round_storage<S, R>(rh);
                         store_spinor_cp<S, R, TM_CP_K2>(hp, Vs, s, rh);
-                        prho[r] += spinor_norm2(rh);
+                        prho[r] += norm2_own(rh);
                     }
                 }
             });
@@ -301,7 +301,7 @@ __global__ TM_MARCH_R(NR, float) void k_fcg_tm_mp(FcgArgs a, int tseg, uint32_t 
                                                  if (!act[r]) continue;
                                                  round_storage<S, float>(out[r]);
                                                  store_spinor<S, float>(field_rhs<S>(a.t, Vs, r0 + r), Vs, s, out[r]);
-                                                 part[r] += spinor_norm2(out[r]);
+                                                 part[r] += norm2_own(out[r]);
                                              }
                                          });
     }
@@ -351,7 +351,7 @@ __global__ TM_MARCH_R(NR, float) void k_fcg_tm_upd(FcgArgs a, int tseg, uint32_t
 #pragma unroll
                     for (int k = 0; k < 12; k++) rv[k] = rv[k] - al[r] * q[r][k];
                     store_spinor_cp<SF32, float, TM_CP_K2>(rp, Vs, s, rv);
-                    prr[r] += spinor_norm2(rv);
+                    prr[r] += norm2_own(rv);
                     void* xp = field_rhs<SF32>(a.x, Vs, r0 + r);
                     cx<float> pv[12], xv[12];
                     load_spinor_cp<S, float, TM_CP_K2>(field_rhs<S>(a.p, Vs, r0 + r), Vs, s, pv);

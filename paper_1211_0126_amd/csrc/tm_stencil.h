@@ -245,7 +245,21 @@ __device__ __forceinline__ void settle(cx<R>* v) {
     for (int k = 0; k < N; k++) asm("" : "+v"(v[k].re), "+v"(v[k].im));
 }
 
-// (explicit FMAs: the same sum in every kernel)
+// |v|^2 where only one kernel forms it, contracted as the compiler likes.  (How
+// it is written also moves which components of an FP16 field the compiler
+// rounds within the last multiply-add: with the explicit FMAs below the
+// time-marching and tile kernels round others, and FP16 solves then differ by
+// 1e-4 of their norm.)
+template <typename R>
+__device__ __forceinline__ double norm2_own(const cx<R> v[12]) {
+    double s = 0;
+#pragma unroll
+    for (int k = 0; k < 12; k++) s += (double)v[k].re * (double)v[k].re + (double)v[k].im * (double)v[k].im;
+    return s;
+}
+
+// |v|^2 of the kernels that have a direction-per-wave form (explicit FMAs: the
+// same sum in both)
 template <typename R>
 __device__ __forceinline__ double spinor_norm2(const cx<R> v[12]) {
     double s = 0;
