@@ -243,8 +243,8 @@ size_t tm_workspace_bytes(const tm_lattice* lat, const tm_caps* caps);
    from its top, the scratch of each call from its bottom (released when the
    next call begins).  The library allocates no device memory after
    tm_create; a call whose buffers do not fit returns TM_ENOMEM before it
-   enqueues work (16-bit solves that lack room only for the directions they
-   keep start over without keeping them).  dev_ws NULL: tm_create allocates ws_bytes itself (once;
+   enqueues work (16-bit solves keep their directions where the workspace has
+   room for them beside the fields, and do without otherwise).  dev_ws NULL: tm_create allocates ws_bytes itself (once;
    tm_destroy releases it).  tm_create zeroes the workspace and allocates a
    small pinned host buffer (and the first result of 4 MiB or more that goes to
    the host a staging buffer of 8 MiB, kept until tm_destroy).  hip_stream is a hipStream_t (NULL: the null

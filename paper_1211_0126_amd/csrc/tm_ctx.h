@@ -57,10 +57,6 @@ struct tm_ctx {
     // the keys of captured graphs, which hold buffer addresses)
     uint64_t ws_digest = 0;
 
-    // whether solves may keep directions in rings that they can do without
-    // (with_rings), and whether one did in the current call
-    bool rings = true, ring_used = false;
-
     // pinned staging of large results (copy_out; allocated by the first one,
     // kept until tm_destroy)
     char* out_stage = nullptr;

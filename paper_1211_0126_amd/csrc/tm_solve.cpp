@@ -361,12 +361,13 @@ static EoBytes eo_bytes(const Geom& hg, int prec, int nrhs, bool track, bool xfr
 // half-hops per iteration), then x_e = D^{-1} (eta_e + kappa H_eo x_o) and
 // the full native solution in res.  Reliable updates recompute
 // r = b - Mhat^dag Mhat x in FP64 on the half lattice.
+// rings: the workspace has room for the directions (ring_room)
 // halves: the caller can take the solution as its two halves (the standard
 // loop's contraction), FP32, or FP16 for an FP16 solve, which saves writing
 // the full native field
 static tm_status solve_block_eo(tm_ctx* ctx, const tsm_solve_params* p, uint64_t seed_mixed,
                                 const uint64_t* ids_dev, int nrhs, int nr, const std::string& tag,
-                                BlockResult* res, bool halves) {
+                                BlockResult* res, bool rings, bool halves) {
     const Geom& g = ctx->geo;
     const Geom& hg = ctx->hgeo;
     hipStream_t st = ctx->stream;
@@ -397,8 +398,7 @@ static tm_status solve_block_eo(tm_ctx* ctx, const tsm_solve_params* p, uint64_t
     // search directions in a ring (CgArgs::pn): without reliable updates, on
     // the lane-per-site kernels; x is formed from the step lengths every
     // kRing - 1 iterations and at the end
-    const bool ringm = !tiles && (rel ? half_storage(prec) && ctx->rings : prec != P_F64);
-    ctx->ring_used |= ringm && rel;
+    const bool ringm = !tiles && (rel ? half_storage(prec) && rings : prec != P_F64);
     const int kRing = rel ? kRelRing : kEoRing;
     void* dirs = nullptr;
     if (ringm) {
@@ -777,40 +777,15 @@ static tm_status solve_block_eo(tm_ctx* ctx, const tsm_solve_params* p, uint64_t
     return TM_OK;
 }
 
-// A call that solves.  Reliable-update solves and 16-bit solves on the whole
-// lattice keep their directions in rings where the workspace has room (24^3 x
-// 48, 16 sources: 84 -> 76 ms with reliable updates, 30 -> 26.6 ms without).
-// A call that runs out of workspace with one starts over without, updating x in
-// every iteration, so that a workspace that holds the fields alone is enough.
-template <class F>
-static tm_status with_rings(tm_ctx* ctx, F&& call) {
-    if (!ctx || !ctx->rings) return call();
-    const size_t sp = ctx->arena.sp;
-    const auto ws = ctx->ws;
-    const auto cap = ctx->ws_cap;
-    const uint64_t digest = ctx->ws_digest;
-    ctx->ring_used = false;
-    tm_status s = call();
-    if (s == TM_ENOMEM && ctx->ring_used) {
-        // (inside another call its buffers stay; nothing of the first try does)
-        ctx->arena.sp = sp;
-        ctx->ws = ws;
-        ctx->ws_cap = cap;
-        ctx->ws_digest = digest;
-        ctx->rings = false;
-        s = call();
-        ctx->rings = true;
-    }
-    return s;
-}
-
 // Solve nrhs sources (ids on the device) with the given settings.  On
 // return the stream is synchronised, ctx->scal_host[0..nrhs) holds the final
-// per-source state and res the native solutions.
+// per-source state and res the native solutions.  rings: reliable-update solves
+// and 16-bit solves on the whole lattice may keep their directions.
 static tm_status solve_block(tm_ctx* ctx, const tsm_solve_params* p, uint64_t seed_mixed, const uint64_t* ids_dev,
-                             int nrhs, int nr, const std::string& tag, BlockResult* res, bool halves = false) {
+                             int nrhs, int nr, const std::string& tag, BlockResult* res, bool rings,
+                             bool halves = false) {
     if (p->solver == TM_SOLVER_FCG_LEARNED) return solve_block_fcg(ctx, p, seed_mixed, ids_dev, nrhs, nr, tag, res);
-    if (p->solver == TM_SOLVER_CG_EO) return solve_block_eo(ctx, p, seed_mixed, ids_dev, nrhs, nr, tag, res, halves);
+    if (p->solver == TM_SOLVER_CG_EO) return solve_block_eo(ctx, p, seed_mixed, ids_dev, nrhs, nr, tag, res, rings, halves);
     const Geom& g = ctx->geo;
     hipStream_t st = ctx->stream;
     tm_status s = TM_OK;
@@ -838,8 +813,7 @@ static tm_status solve_block(tm_ctx* ctx, const tsm_solve_params* p, uint64_t se
     a.npart = a.tseg > 0 ? march_partials(g, a.tseg) : (uint32_t)((g.V + 63) / 64);
     const size_t npart_max = partials_per_rhs(g, ctx->hgeo, ctx->eo_ok);
     // directions in a ring, as in solve_block_eo
-    const bool ringm = !rel && half_storage(prec) && ctx->rings;
-    ctx->ring_used |= ringm;
+    const bool ringm = !rel && half_storage(prec) && rings;
     const int kRing = kEoRing;
     void* dirs = nullptr;
     if (ringm) {
@@ -1281,7 +1255,7 @@ static tm_status contract_all_momenta(tm_ctx* ctx, uint64_t seed, int32_t nsrc, 
 // buffers of the solver path, each rounded to 256 B.  The partial arrays
 // shared by every solve of a call are counted by ws_partials.
 // rings: with the rings of reliable solves and of the whole lattice, which a
-// solve can do without (with_rings)
+// solve can do without (ring_room)
 static size_t ws_block(const Geom& g, const Geom& hg, const tsm_solve_params* p, int nc, bool rings) {
     const size_t scal = align256(sizeof(CgScal) * 2 * kMaxBlock);
     const int prec = p->prec;
@@ -1314,6 +1288,21 @@ static size_t ws_block(const Geom& g, const Geom& hg, const tsm_solve_params* p,
 static size_t ws_partials(const Geom& g, const Geom& hg, bool eo_ok, bool fcg) {
     const size_t n = partials_per_rhs(g, hg, eo_ok) * kMaxBlock;
     return 2 * align256(sizeof(double) * n) + (fcg ? align256(sizeof(double) * n * 4) : 0);
+}
+
+static size_t solve_bytes(const tm_ctx* ctx, const tsm_solve_params* p, int nc, bool rings) {
+    return ws_block(ctx->geo, ctx->hgeo, p, nc, rings);
+}
+
+// Whether the rest of the workspace holds a solve of nc sources with its
+// directions kept, beside `other` bytes that the call still carves.  Asked before
+// the call enqueues any work: without the room a solve updates x in every
+// iteration instead, so that a workspace that holds the fields alone is enough
+// (24^3 x 48, 16 sources: 84 instead of 76 ms with reliable updates, 30 instead
+// of 26.6 ms on the whole lattice).
+static bool ring_room(const tm_ctx* ctx, const tsm_solve_params* p, int nc, size_t other) {
+    other += ws_partials(ctx->geo, ctx->hgeo, ctx->eo_ok, false);
+    return solve_bytes(ctx, p, nc, true) + other <= ctx->arena.top - ctx->arena.sp;
 }
 
 // setup_contract for maxr sources: phase tables, momentum indices, the two
@@ -1411,8 +1400,8 @@ using namespace tmq;
 
 extern "C" {
 
-static tm_status solve_batch_once(tm_ctx* ctx, const tsm_solve_params* params, uint64_t seed, int32_t nsrc,
-                                  const uint64_t* ids_host, void* sol_dev, tsm_solve_stats* stats_host) {
+tm_status tsm_solve_batch(tm_ctx* ctx, const tsm_solve_params* params, uint64_t seed, int32_t nsrc,
+                          const uint64_t* ids_host, void* sol_dev, tsm_solve_stats* stats_host) {
     if (!ctx) return TM_EINVAL;
     if (ctx->sticky) return set_error(ctx, TM_EDEVICE, "context has a sticky device error");
     WsScope scope(ctx);
@@ -1438,11 +1427,12 @@ static tm_status solve_batch_once(tm_ctx* ctx, const tsm_solve_params* params, u
     TM_COPY(ids_dev, ids.data(), sizeof(uint64_t) * npad, hipMemcpyHostToDevice);
     const uint64_t sm = seed_mix(seed);
     bool warn = false;
+    const bool rings = ring_room(ctx, params, (std::min(blk, nsrc) + nr - 1) / nr * nr, 0);
     for (int j0 = 0; j0 < nsrc; j0 += blk) {
         const int nb = std::min(blk, nsrc - j0);
         const int nbp = (nb + nr - 1) / nr * nr;
         BlockResult res;
-        s = solve_block(ctx, params, sm, ids_dev + j0, nbp, nr, "sb", &res);
+        s = solve_block(ctx, params, sm, ids_dev + j0, nbp, nr, "sb", &res, rings);
         if (s != TM_OK) return s;
         for (int r = 0; r < nb; r++) {
             fill_stats(ctx->scal_host[r], stats_host + j0 + r);
@@ -1515,8 +1505,8 @@ tm_status tsm_contract_est(tm_ctx* ctx, int32_t estimator, uint64_t seed, int32_
     return copy_out(ctx, loops_host, out, sizeof(double) * 2 * nl * nsrc);
 }
 
-static tm_status loops_once(tm_ctx* ctx, const tsm_params* P, double* loops_host, double* err_host, double* per_source_host,
-                            tsm_solve_stats* stats_host, tsm_run_stats* run_stats) {
+tm_status tsm_loops(tm_ctx* ctx, const tsm_params* P, double* loops_host, double* err_host, double* per_source_host,
+                    tsm_solve_stats* stats_host, tsm_run_stats* run_stats) {
     using clk = std::chrono::steady_clock;
     if (!ctx) return TM_EINVAL;
     if (ctx->sticky) return set_error(ctx, TM_EDEVICE, "context has a sticky device error");
@@ -1591,6 +1581,15 @@ static tm_status loops_once(tm_ctx* ctx, const tsm_params* P, double* loops_host
 
     // the standard loop takes the LP solutions as their two halves
     const bool halves = P->estimator == TM_LOOP_STANDARD;
+    // directions kept where both solves have room beside each other, those of
+    // the longer (HP) solves before those of the LP solves
+    const int nc_lp = ctx->ws_cap["lp"], nc_hp = P->n_hp > 0 ? ctx->ws_cap["hp"] : 0;
+    const size_t fcg = ws_partials(g, ctx->hgeo, ctx->eo_ok, true) - ws_partials(g, ctx->hgeo, ctx->eo_ok, false);
+    auto bytes = [&](const tsm_solve_params* p, int nc, bool rings) {
+        return nc == 0 ? 0 : solve_bytes(ctx, p, nc, rings) + (p->solver == TM_SOLVER_FCG_LEARNED ? fcg : 0);
+    };
+    const bool rings_hp = nc_hp > 0 && ring_room(ctx, &P->hp, nc_hp, bytes(&P->lp, nc_lp, false));
+    const bool rings_lp = ring_room(ctx, &P->lp, nc_lp, bytes(&P->hp, nc_hp, rings_hp));
     auto t0 = clk::now();
     // HP set: LP and HP solves of ids 0..n_hp-1
     const int bh = std::min(blp, bhp);
@@ -1598,11 +1597,11 @@ static tm_status loops_once(tm_ctx* ctx, const tsm_params* P, double* loops_host
         const int nb = std::min(bh, P->n_hp - j0);
         BlockResult res;
         const int nbl = (nb + nr_lp - 1) / nr_lp * nr_lp;
-        if ((s = solve_block(ctx, &P->lp, sm, ids_dev + j0, nbl, nr_lp, "lp", &res, halves)) != TM_OK) return s;
+        if ((s = solve_block(ctx, &P->lp, sm, ids_dev + j0, nbl, nr_lp, "lp", &res, rings_lp, halves)) != TM_OK) return s;
         record(j0, nb, 0, false);
         contract_block(ctx, &c, ids_dev + j0, res.x, res.xprec, nb, (double2*)ps, slots_dev + j0, nl, res.xe);
         const int nbh = (nb + nr_hp - 1) / nr_hp * nr_hp;
-        if ((s = solve_block(ctx, &P->hp, sm, ids_dev + j0, nbh, nr_hp, "hp", &res)) != TM_OK) return s;
+        if ((s = solve_block(ctx, &P->hp, sm, ids_dev + j0, nbh, nr_hp, "hp", &res, rings_hp)) != TM_OK) return s;
         record(j0, nb, 1, true);
         contract_block(ctx, &c, ids_dev + j0, res.x, res.xprec, nb, (double2*)ps, slots_dev + Npad + j0, nl);
         TM_HIP(hipGetLastError());
@@ -1614,7 +1613,7 @@ static tm_status loops_once(tm_ctx* ctx, const tsm_params* P, double* loops_host
         const int nb = std::min(blp, N - j0);
         const int nbl = (nb + nr_lp - 1) / nr_lp * nr_lp;
         BlockResult res;
-        if ((s = solve_block(ctx, &P->lp, sm, ids_dev + j0, nbl, nr_lp, "lp", &res, halves)) != TM_OK) return s;
+        if ((s = solve_block(ctx, &P->lp, sm, ids_dev + j0, nbl, nr_lp, "lp", &res, rings_lp, halves)) != TM_OK) return s;
         record(j0, nb, 0, false);
         contract_block(ctx, &c, ids_dev + j0, res.x, res.xprec, nb, (double2*)ps, slots_dev + j0, nl, res.xe);
         TM_HIP(hipGetLastError());
@@ -1634,8 +1633,8 @@ static tm_status loops_once(tm_ctx* ctx, const tsm_params* P, double* loops_host
     return warn ? TM_WARN_NOT_CONVERGED : TM_OK;
 }
 
-static tm_status autotune_cg_once(tm_ctx* ctx, int32_t prec, int32_t nrhs, int32_t* best_nr, int32_t* best_tseg,
-                                  double* ms_host) {
+tm_status tm_autotune_cg(tm_ctx* ctx, int32_t prec, int32_t nrhs, int32_t* best_nr, int32_t* best_tseg,
+                         double* ms_host) {
     if (!ctx || prec < 0 || prec > 3 || nrhs < 1 || nrhs > kMaxBlock || !best_nr || !best_tseg)
         return ctx ? set_error(ctx, TM_EINVAL, "tm_autotune_cg: bad argument") : TM_EINVAL;
     if (ctx->sticky) return set_error(ctx, TM_EDEVICE, "context has a sticky device error");
@@ -1658,6 +1657,7 @@ static tm_status autotune_cg_once(tm_ctx* ctx, int32_t prec, int32_t nrhs, int32
     p.true_resid = 0;
     double best = 1e300;
     int bnr = 1, bts = 0;
+    const bool rings = ring_room(ctx, &p, nrhs, 0);
     for (int c = 0; c < kTuneCandidates; c++) {
         const int nr = kTuneNr[c], ts = kTuneTseg[c];
         if (ms_host) ms_host[c] = -1.0;
@@ -1673,7 +1673,7 @@ static tm_status autotune_cg_once(tm_ctx* ctx, int32_t prec, int32_t nrhs, int32
                 p.max_iter = j == 0 ? 2 : 10;
                 BlockResult res;
                 const auto t0 = std::chrono::steady_clock::now();
-                s = solve_block(ctx, &p, seed_mix(12345), ids, nrhs, nr, "tune", &res);
+                s = solve_block(ctx, &p, seed_mix(12345), ids, nrhs, nr, "tune", &res, rings);
                 const auto t1 = std::chrono::steady_clock::now();
                 if (s != TM_OK) break;
                 t[j] = std::chrono::duration<double, std::milli>(t1 - t0).count();
@@ -1743,7 +1743,7 @@ tm_status tm_autotune_eo(tm_ctx* ctx, int32_t prec, int32_t nrhs, int32_t* best_
                 p.max_iter = j == 0 ? 2 : 8;
                 BlockResult res;
                 const auto t0 = std::chrono::steady_clock::now();
-                s = solve_block(ctx, &p, seed_mix(12345), ids, nrhs, nr, "tune", &res);
+                s = solve_block(ctx, &p, seed_mix(12345), ids, nrhs, nr, "tune", &res, false);
                 const auto t1 = std::chrono::steady_clock::now();
                 if (s != TM_OK) break;
                 t[j] = std::chrono::duration<double, std::milli>(t1 - t0).count();
@@ -1810,21 +1810,6 @@ size_t tm_workspace_bytes(const tm_lattice* lat, const tm_caps* caps) {
     const uint32_t est = caps->estimators ? caps->estimators : (1u << TM_LOOP_STANDARD);
     return ws_bound(lat, g, hg, eo_ok, sv, caps->max_sources, max_mom, nd, est, caps->all_mom_sources,
                     std::max(caps->field_rhs, 1), caps->train_pairs, caps->train_sources, caps->loss_pairs);
-}
-
-tm_status tsm_solve_batch(tm_ctx* ctx, const tsm_solve_params* params, uint64_t seed, int32_t nsrc,
-                          const uint64_t* ids_host, void* sol_dev, tsm_solve_stats* stats_host) {
-    return with_rings(ctx, [&] { return solve_batch_once(ctx, params, seed, nsrc, ids_host, sol_dev, stats_host); });
-}
-
-tm_status tsm_loops(tm_ctx* ctx, const tsm_params* P, double* loops_host, double* err_host, double* per_source_host,
-                    tsm_solve_stats* stats_host, tsm_run_stats* run_stats) {
-    return with_rings(ctx, [&] { return loops_once(ctx, P, loops_host, err_host, per_source_host, stats_host, run_stats); });
-}
-
-tm_status tm_autotune_cg(tm_ctx* ctx, int32_t prec, int32_t nrhs, int32_t* best_nr, int32_t* best_tseg,
-                         double* ms_host) {
-    return with_rings(ctx, [&] { return autotune_cg_once(ctx, prec, nrhs, best_nr, best_tseg, ms_host); });
 }
 
 }  // extern "C"

@@ -1,0 +1,44 @@
+"""Host code of the library on the CPU (see standin.py): what a call launches,
+where it stops and what it leaves behind."""
+
+from standin import run
+
+# FP16 LP solves in blocks of 16, HP solves in blocks of 8 that keep their
+# directions where they have room
+SOLVES = """
+tq = s.tq
+dims = (8, 8, 8, 8)
+lp = tq.solve_params(prec=tq.PREC_F16, tol=1e-2, rhs_block=16, solver=tq.SOLVER_CG_EO, true_resid=0)
+hp = tq.solve_params(prec=tq.PREC_F16, tol=1e-10, rhs_block=8, solver=tq.SOLVER_CG_EO, reliable=1, delta=3e-3)
+whole = tq.solve_params(prec=tq.PREC_F16, tol=1e-2, rhs_block=16, solver=tq.SOLVER_CG, true_resid=0)
+
+def named(launches, *parts):
+    return [n for n, _ in launches if all(p in n for p in parts)]
+
+def used(c):
+    u = c.workspace_usage()
+    return u["persistent"] + u["peak_scratch"]
+"""
+
+
+def test_a_call_without_room_for_directions_does_its_work_once(tmp_path):
+    """The workspace that a call used with its directions kept, and 1 MiB less:
+    each block of sources is prepared and solved once, in the first call and in
+    the second, and without the room x is updated in every iteration."""
+    run(tmp_path, SOLVES + """
+calls = [(lambda c: tq.tsm_loops(c, 7, 8, 24, lp, hp, [[0, 0, 0]]), 4, "k_ring_rel_flush"),
+         (lambda c: tq.tsm_solve_batch(c, hp, 7, list(range(8)), want_solutions=False), 1, "k_ring_rel_flush"),
+         (lambda c: tq.tsm_solve_batch(c, whole, 7, list(range(16)), want_solutions=False), 1, "k_eo_xflush")]
+for call, blocks, kept in calls:
+    size = 1 << 30
+    for room in (True, True, False):
+        c = s.context(dims, size)
+        for _ in range(2):
+            call(c)
+            got = s.launches()
+            assert len(named(got, "k_scal_init")) == blocks, (kept, room, len(named(got, "k_scal_init")))
+            hp_kept = [n for n in named(got, kept) if "SF16" in n]
+            assert bool(hp_kept) == room, (kept, room)
+        size = used(c) if room and size == 1 << 30 else used(c) - (1 << 20)
+        c.close()
+""")
