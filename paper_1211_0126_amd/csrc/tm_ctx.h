@@ -201,6 +201,23 @@ struct WsScope {
     WsScope& operator=(const WsScope&) = delete;
 };
 
+// The scratch of the current call as it is here: back() gives up what was carved
+// since (dead: its last use is enqueued before the work of what is carved next).
+// The digest goes back too, so that the same buffers carved again have the same
+// graphs.
+struct WsMark {
+    tm_ctx* c;
+    size_t sp;
+    uint64_t digest;
+    std::map<std::string, tm_ctx::Buf> ws;
+    explicit WsMark(tm_ctx* ctx) : c(ctx), sp(ctx->arena.sp), digest(ctx->ws_digest), ws(ctx->ws) {}
+    void back() const {
+        c->arena.sp = sp;
+        c->ws_digest = digest;
+        c->ws = ws;
+    }
+};
+
 #define TM_HIP(call)                                             \
     do {                                                         \
         hipError_t e_ = (call);                                  \

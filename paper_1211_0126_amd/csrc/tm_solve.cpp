@@ -812,7 +812,9 @@ static tm_status solve_block(tm_ctx* ctx, const tsm_solve_params* p, uint64_t se
     a.tseg = march_tseg(ctx, p, nr);
     a.npart = a.tseg > 0 ? march_partials(g, a.tseg) : (uint32_t)((g.V + 63) / 64);
     const size_t npart_max = partials_per_rhs(g, ctx->hgeo, ctx->eo_ok);
-    // directions in a ring, as in solve_block_eo
+    // directions in a ring, as in solve_block_eo; the source is read by the CG
+    // start only and takes the slot of the last direction (two such blocks without
+    // the ring are then as large as one with it)
     const bool ringm = !rel && half_storage(prec) && rings;
     const int kRing = kEoRing;
     void* dirs = nullptr;
@@ -843,7 +845,7 @@ static tm_status solve_block(tm_ctx* ctx, const tsm_solve_params* p, uint64_t se
         x64 = ws_get(ctx, tag + "_x64", f64, &s);
         t64 = ws_get(ctx, tag + "_t64", f64, &s);
     } else {
-        eta = ws_get(ctx, tag + "_eta", fb, &s);
+        eta = ringm ? slot(kRing - 1) : ws_get(ctx, tag + "_eta", fb, &s);
     }
     if (s != TM_OK) return s;
     if ((s = ensure_scal_host(ctx, nrhs)) != TM_OK) return s;
@@ -1281,7 +1283,7 @@ static size_t ws_block(const Geom& g, const Geom& hg, const tsm_solve_params* p,
     const bool ring = !rel && half_storage(prec) && rings;
     size_t b = 2 * fb + align256(field_bytes(g, prec == P_F64 ? P_F64 : P_F32, nc)) + scal + (track ? fb : 0);
     b += ring ? align256(field_bytes(g, prec, nc) * kEoRing) + align256(sizeof(double) * kMaxBlock * kEoRing) : fb;
-    b += rel ? 4 * align256(field_bytes(g, P_F64, nc)) : fb;
+    b += rel ? 4 * align256(field_bytes(g, P_F64, nc)) : (ring ? 0 : fb);
     return b;
 }
 
@@ -1290,19 +1292,15 @@ static size_t ws_partials(const Geom& g, const Geom& hg, bool eo_ok, bool fcg) {
     return 2 * align256(sizeof(double) * n) + (fcg ? align256(sizeof(double) * n * 4) : 0);
 }
 
-static size_t solve_bytes(const tm_ctx* ctx, const tsm_solve_params* p, int nc, bool rings) {
-    return ws_block(ctx->geo, ctx->hgeo, p, nc, rings);
-}
-
 // Whether the rest of the workspace holds a solve of nc sources with its
-// directions kept, beside `other` bytes that the call still carves.  Asked before
-// the call enqueues any work: without the room a solve updates x in every
-// iteration instead, so that a workspace that holds the fields alone is enough
-// (24^3 x 48, 16 sources: 84 instead of 76 ms with reliable updates, 30 instead
-// of 26.6 ms on the whole lattice).
-static bool ring_room(const tm_ctx* ctx, const tsm_solve_params* p, int nc, size_t other) {
-    other += ws_partials(ctx->geo, ctx->hgeo, ctx->eo_ok, false);
-    return solve_bytes(ctx, p, nc, true) + other <= ctx->arena.top - ctx->arena.sp;
+// directions kept.  Asked before the call enqueues any work: without the room a
+// solve updates x in every iteration instead, so that a workspace that holds the
+// fields alone is enough (24^3 x 48, 16 sources: 84 instead of 76 ms with
+// reliable updates, 30 instead of 26.6 ms on the whole lattice).
+static bool ring_room(const tm_ctx* ctx, const tsm_solve_params* p, int nc) {
+    const size_t need =
+        ws_block(ctx->geo, ctx->hgeo, p, nc, true) + ws_partials(ctx->geo, ctx->hgeo, ctx->eo_ok, false);
+    return need <= ctx->arena.top - ctx->arena.sp;
 }
 
 // setup_contract for maxr sources: phase tables, momentum indices, the two
@@ -1318,10 +1316,10 @@ static size_t ws_contract_setup(const Geom& g, int n_mom, int nd, int maxr, uint
     return b;
 }
 
-static size_t ws_bound_rings(const tm_lattice* lat, const Geom& g, const Geom& hg, bool eo_ok,
-                             const std::vector<tsm_solve_params>& sv, int max_sources, int max_mom, int nd,
-                             uint32_t est_mask, int all_mom, int field_rhs, int train_pairs, int train_sources,
-                             int loss_pairs, bool rings) {
+static size_t ws_bound(const tm_lattice* lat, const Geom& g, const Geom& hg, bool eo_ok,
+                       const std::vector<tsm_solve_params>& sv, int max_sources, int max_mom, int nd,
+                       uint32_t est_mask, int all_mom, int field_rhs, int train_pairs, int train_sources,
+                       int loss_pairs) {
     (void)lat;
     const int N = std::max(max_sources, 1);
     const int nmu = (est_mask & (1u << TM_LOOP_DERIVATIVE)) ? 4 : 1;
@@ -1337,7 +1335,7 @@ static size_t ws_bound_rings(const tm_lattice* lat, const Geom& g, const Geom& h
     size_t best = ws_abi_scratch(g, field_rhs, bmax);
     // tsm_solve_batch
     for (size_t i = 0; i < sv.size(); i++)
-        best = std::max(best, align256(sizeof(uint64_t) * (N + 4)) + ws_block(g, hg, &sv[i], blk[i], rings) + parts);
+        best = std::max(best, align256(sizeof(uint64_t) * (N + 4)) + ws_block(g, hg, &sv[i], blk[i], false) + parts);
     // autotuners: a truncated solve at each listed precision and block
     for (size_t i = 0; i < sv.size(); i++) {
         tsm_solve_params t = sv[i];
@@ -1345,10 +1343,10 @@ static size_t ws_bound_rings(const tm_lattice* lat, const Geom& g, const Geom& h
         t.stop = TM_STOP_NORMAL;
         const size_t ids = align256(sizeof(uint64_t) * blk[i]);
         t.solver = TM_SOLVER_CG;
-        best = std::max(best, ids + ws_block(g, hg, &t, blk[i], rings) + parts);
+        best = std::max(best, ids + ws_block(g, hg, &t, blk[i], false) + parts);
         if (eo_ok) {
             t.solver = TM_SOLVER_CG_EO;
-            best = std::max(best, ids + ws_block(g, hg, &t, blk[i], rings) + parts);
+            best = std::max(best, ids + ws_block(g, hg, &t, blk[i], false) + parts);
         }
     }
     // tsm_contract / tsm_contract_est at max_mom
@@ -1368,7 +1366,9 @@ static size_t ws_bound_rings(const tm_lattice* lat, const Geom& g, const Geom& h
                                   align256(field_bytes(g, P_F64, b)) +
                                   align256(sizeof(double) * 2 * 16 * (size_t)g.V * all_mom));
     }
-    // tsm_loops: any two listed settings as lp and hp
+    // tsm_loops: any two listed settings as lp and hp.  The two solves take turns
+    // in one stretch of scratch; the second block is room for the directions that
+    // a solve keeps where it can (they come to less than its other fields)
     if (!sv.empty()) {
         const size_t nl = (size_t)16 * nmu * max_mom * g.L[3];
         const size_t fixed = ws_contract_setup(g, max_mom, nd, bmax + 4, est_mask) +
@@ -1377,7 +1377,7 @@ static size_t ws_bound_rings(const tm_lattice* lat, const Geom& g, const Geom& h
         size_t pair = 0;
         for (size_t i = 0; i < sv.size(); i++)
             for (size_t j = 0; j < sv.size(); j++)
-                pair = std::max(pair, ws_block(g, hg, &sv[i], blk[i], rings) + ws_block(g, hg, &sv[j], blk[j], rings));
+                pair = std::max(pair, ws_block(g, hg, &sv[i], blk[i], false) + ws_block(g, hg, &sv[j], blk[j], false));
         best = std::max(best, fixed + pair);
     }
     // network calls
@@ -1385,13 +1385,6 @@ static size_t ws_bound_rings(const tm_lattice* lat, const Geom& g, const Geom& h
     if (loss_pairs > 0) best = std::max(best, ws_loss_grad(g, loss_pairs));
     if (train_pairs > 0) best = std::max(best, ws_train(g, hg, eo_ok, train_pairs, std::max(train_sources, 1)));
     return ws_persistent(g, hg, eo_ok) + best + (size_t(1) << 20);
-}
-
-// The rings a solve can do without are counted up to 240 GiB in all, so that no
-// call that fits a card of 288 GB without them needs a larger one.
-template <class... A>
-static size_t ws_bound(const A&... args) {
-    return std::max(ws_bound_rings(args..., false), std::min(ws_bound_rings(args..., true), (size_t)240 << 30));
 }
 
 }  // namespace tmq
@@ -1427,7 +1420,7 @@ tm_status tsm_solve_batch(tm_ctx* ctx, const tsm_solve_params* params, uint64_t 
     TM_COPY(ids_dev, ids.data(), sizeof(uint64_t) * npad, hipMemcpyHostToDevice);
     const uint64_t sm = seed_mix(seed);
     bool warn = false;
-    const bool rings = ring_room(ctx, params, (std::min(blk, nsrc) + nr - 1) / nr * nr, 0);
+    const bool rings = ring_room(ctx, params, (std::min(blk, nsrc) + nr - 1) / nr * nr);
     for (int j0 = 0; j0 < nsrc; j0 += blk) {
         const int nb = std::min(blk, nsrc - j0);
         const int nbp = (nb + nr - 1) / nr * nr;
@@ -1581,15 +1574,16 @@ tm_status tsm_loops(tm_ctx* ctx, const tsm_params* P, double* loops_host, double
 
     // the standard loop takes the LP solutions as their two halves
     const bool halves = P->estimator == TM_LOOP_STANDARD;
-    // directions kept where both solves have room beside each other, those of
-    // the longer (HP) solves before those of the LP solves
-    const int nc_lp = ctx->ws_cap["lp"], nc_hp = P->n_hp > 0 ? ctx->ws_cap["hp"] : 0;
-    const size_t fcg = ws_partials(g, ctx->hgeo, ctx->eo_ok, true) - ws_partials(g, ctx->hgeo, ctx->eo_ok, false);
-    auto bytes = [&](const tsm_solve_params* p, int nc, bool rings) {
-        return nc == 0 ? 0 : solve_bytes(ctx, p, nc, rings) + (p->solver == TM_SOLVER_FCG_LEARNED ? fcg : 0);
+    // The solves take turns in the same scratch: the loops of one are contracted
+    // before the next begins.
+    const WsMark solves(ctx);
+    const bool rings_lp = ring_room(ctx, &P->lp, ctx->ws_cap["lp"]);
+    const bool rings_hp = ring_room(ctx, &P->hp, ctx->ws_cap["hp"]);
+    auto solve = [&](bool hp, const uint64_t* ids, int n, BlockResult* res) {
+        solves.back();
+        return hp ? solve_block(ctx, &P->hp, sm, ids, n, nr_hp, "hp", res, rings_hp)
+                  : solve_block(ctx, &P->lp, sm, ids, n, nr_lp, "lp", res, rings_lp, halves);
     };
-    const bool rings_hp = nc_hp > 0 && ring_room(ctx, &P->hp, nc_hp, bytes(&P->lp, nc_lp, false));
-    const bool rings_lp = ring_room(ctx, &P->lp, nc_lp, bytes(&P->hp, nc_hp, rings_hp));
     auto t0 = clk::now();
     // HP set: LP and HP solves of ids 0..n_hp-1
     const int bh = std::min(blp, bhp);
@@ -1597,11 +1591,11 @@ tm_status tsm_loops(tm_ctx* ctx, const tsm_params* P, double* loops_host, double
         const int nb = std::min(bh, P->n_hp - j0);
         BlockResult res;
         const int nbl = (nb + nr_lp - 1) / nr_lp * nr_lp;
-        if ((s = solve_block(ctx, &P->lp, sm, ids_dev + j0, nbl, nr_lp, "lp", &res, rings_lp, halves)) != TM_OK) return s;
+        if ((s = solve(false, ids_dev + j0, nbl, &res)) != TM_OK) return s;
         record(j0, nb, 0, false);
         contract_block(ctx, &c, ids_dev + j0, res.x, res.xprec, nb, (double2*)ps, slots_dev + j0, nl, res.xe);
         const int nbh = (nb + nr_hp - 1) / nr_hp * nr_hp;
-        if ((s = solve_block(ctx, &P->hp, sm, ids_dev + j0, nbh, nr_hp, "hp", &res, rings_hp)) != TM_OK) return s;
+        if ((s = solve(true, ids_dev + j0, nbh, &res)) != TM_OK) return s;
         record(j0, nb, 1, true);
         contract_block(ctx, &c, ids_dev + j0, res.x, res.xprec, nb, (double2*)ps, slots_dev + Npad + j0, nl);
         TM_HIP(hipGetLastError());
@@ -1613,7 +1607,7 @@ tm_status tsm_loops(tm_ctx* ctx, const tsm_params* P, double* loops_host, double
         const int nb = std::min(blp, N - j0);
         const int nbl = (nb + nr_lp - 1) / nr_lp * nr_lp;
         BlockResult res;
-        if ((s = solve_block(ctx, &P->lp, sm, ids_dev + j0, nbl, nr_lp, "lp", &res, rings_lp, halves)) != TM_OK) return s;
+        if ((s = solve(false, ids_dev + j0, nbl, &res)) != TM_OK) return s;
         record(j0, nb, 0, false);
         contract_block(ctx, &c, ids_dev + j0, res.x, res.xprec, nb, (double2*)ps, slots_dev + j0, nl, res.xe);
         TM_HIP(hipGetLastError());
@@ -1657,7 +1651,7 @@ tm_status tm_autotune_cg(tm_ctx* ctx, int32_t prec, int32_t nrhs, int32_t* best_
     p.true_resid = 0;
     double best = 1e300;
     int bnr = 1, bts = 0;
-    const bool rings = ring_room(ctx, &p, nrhs, 0);
+    const bool rings = ring_room(ctx, &p, nrhs);
     for (int c = 0; c < kTuneCandidates; c++) {
         const int nr = kTuneNr[c], ts = kTuneTseg[c];
         if (ms_host) ms_host[c] = -1.0;

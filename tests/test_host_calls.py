@@ -42,3 +42,29 @@ for call, blocks, kept in calls:
         size = used(c) if room and size == 1 << 30 else used(c) - (1 << 20)
         c.close()
 """)
+
+
+def test_directions_fit_the_workspace_of_the_fields(tmp_path):
+    """tm_workspace_bytes asks for no room for directions (FP16 fields with
+    reliable updates are smaller than FP32 ones, and so is their workspace, at
+    every size), and yet the solves that it was asked for keep theirs in it."""
+    run(tmp_path, SOLVES + """
+import copy
+for d in ((4, 4, 4, 4), dims, (32, 32, 32, 64)):
+    for p in (hp, whole):
+        wide = copy.copy(p)
+        wide.prec = tq.PREC_F32
+        a, b = (tq.tm_workspace_bytes(d, caps_=tq.caps([q], max_sources=32, max_mom=1)) for q in (p, wide))
+        assert a < b, (d, a, b)
+for d in (dims, (8, 16, 12, 4)):
+    for call, solves, kept in [
+            (lambda c: tq.tsm_loops(c, 7, 8, 24, lp, hp, [[0, 0, 0]]), [lp, hp], "k_ring_rel_flush"),
+            (lambda c: tq.tsm_loops(c, 7, 8, 24, whole, hp, [[0, 0, 0]]), [whole, hp], "k_ring_rel_flush"),
+            (lambda c: tq.tsm_loops(c, 7, 0, 24, whole, whole, [[0, 0, 0]]), [whole], "k_eo_xflush"),
+            (lambda c: tq.tsm_solve_batch(c, hp, 7, list(range(8)), want_solutions=False), [hp], "k_ring_rel_flush"),
+            (lambda c: tq.tsm_solve_batch(c, whole, 7, list(range(32)), want_solutions=False), [whole], "k_eo_xflush")]:
+        c = s.context(d, tq.tm_workspace_bytes(d, caps_=tq.caps(solves, max_sources=32, max_mom=1)))
+        call(c)
+        assert named(s.launches(), kept), (d, kept)
+        c.close()
+""")
