@@ -124,6 +124,19 @@ tm_status copy_sync(tm_ctx* ctx, void* dst, const void* src, size_t bytes, hipMe
     return TM_OK;
 }
 
+// The device of a context current in this thread for a while
+struct DeviceScope {
+    int before = -1, dev;
+    explicit DeviceScope(int d) : dev(d) {
+        if (hipGetDevice(&before) == hipSuccess && before != dev) (void)hipSetDevice(dev);
+    }
+    ~DeviceScope() {
+        if (before >= 0 && before != dev) (void)hipSetDevice(before);
+    }
+    DeviceScope(const DeviceScope&) = delete;
+    DeviceScope& operator=(const DeviceScope&) = delete;
+};
+
 // A copy to pageable memory runs at 10 GB/s and less where its pages are not yet
 // there (a fresh result array: 13 ms for 134 MB), bound by one thread's page
 // faults and copies.  Large results go through pinned slots instead: a few
@@ -134,6 +147,9 @@ constexpr int kOutThreads = 4;
 constexpr size_t kOutPiece = size_t(1) << 20;
 tm_status copy_out(tm_ctx* ctx, void* dst_host, const void* src_dev, size_t bytes) {
     constexpr size_t kFrom = size_t(4) << 20;  // (below, threads cost what they save)
+    // (events belong to the device they are made on, and the caller may have
+    // another one current than the context's)
+    const DeviceScope device(ctx->device);
     if (bytes >= kFrom && !ctx->out_stage) {
         if (hipHostMalloc((void**)&ctx->out_stage, kOutPiece * 2 * kOutThreads) != hipSuccess) {
             (void)hipGetLastError();
@@ -149,8 +165,8 @@ tm_status copy_out(tm_ctx* ctx, void* dst_host, const void* src_dev, size_t byte
     for (; nev < 2 * kOutThreads; nev++)
         if (hipEventCreateWithFlags(&ev[nev], hipEventDisableTiming) != hipSuccess) break;
     // thread w moves pieces w, w + kOutThreads, ... through its two slots
-    auto work = [&](int w) {
-        hipError_t e = hipSetDevice(ctx->device);
+    auto work = [&](int w) {  // (w = 0 in the caller's thread)
+        hipError_t e = w ? hipSetDevice(ctx->device) : hipSuccess;
         auto issue = [&](size_t i, int slot) {
             char* s = ctx->out_stage + (size_t)(2 * w + slot) * kOutPiece;
             if (e == hipSuccess)

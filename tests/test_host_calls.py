@@ -68,3 +68,25 @@ for d in (dims, (8, 16, 12, 4)):
         assert named(s.launches(), kept), (d, kept)
         c.close()
 """)
+
+
+def test_large_results_with_another_device_current(tmp_path):
+    """A context on device 1 called with device 0 current: a result of 4 MiB
+    reaches the host, and the caller's device is left as it was."""
+    run(tmp_path, """
+import ctypes
+import numpy as np
+tq = s.tq
+dims = (8, 8, 8, 32)
+c = s.context(dims, tq.tm_workspace_bytes(dims, caps_=tq.caps([], max_sources=1, all_mom_sources=1)), device=1)
+s.hip.hipSetDevice(0)
+sol = np.zeros(c.V * 24)
+out = np.ones((1, 16, c.V), dtype=np.complex128)
+ids = np.zeros(1, dtype=np.uint64)
+rc = s.lib.tsm_contract(c.h, 31, 1, ids.ctypes.data_as(ctypes.c_void_p), sol.ctypes.data_as(ctypes.c_void_p),
+                        tq.binding.ALL_MOMENTA, None, out.ctypes.data_as(ctypes.c_void_p))
+assert rc == 0, s.lib.tm_last_error(c.h)
+assert out.nbytes == 4 << 20 and not out.any()
+assert s.hip.standin_device() == 0
+c.close()
+""")
