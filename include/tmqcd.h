@@ -495,7 +495,10 @@ tm_status tm_autotune_eo(tm_ctx* ctx, int32_t prec, int32_t nrhs, int32_t* best_
                          double* ms_host);
 
 /* Set (nr = 1, 2 or 4) or reset to the built-in choice (nr = 0) the
-   right-hand sides per lane used by solves in storage precision prec. */
+   right-hand sides per lane used by solves in storage precision prec.
+   Solves of few sites and sources, whose CG kernels give each direction a
+   wave, have one right-hand side per lane whatever is set; the autotuners
+   report one time for all widths there and keep 1. */
 tm_status tm_set_lane_rhs(tm_ctx* ctx, int32_t prec, int32_t nr);
 
 /* Stencil traversal of the CG kernels in storage precision prec: tseg = 0

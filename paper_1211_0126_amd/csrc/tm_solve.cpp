@@ -99,6 +99,20 @@ static int march_tseg(const tm_ctx* ctx, const tsm_solve_params* p, int nr) {
     return std::min(t, ctx->geo.L[3]);
 }
 
+// Whether the CG steps of n sources take the direction-per-wave kernels, which
+// have one source per lane whatever width is set (nr decides only whether the
+// solve marches in time): such a block is not filled up to the width, its other
+// launches have one source per lane too, and to a tuner all widths are the same.
+static bool quad_solve(const tm_ctx* ctx, const tsm_solve_params* p, int nr, int n) {
+    if (p->solver == TM_SOLVER_CG_EO)
+        return (p->prec == TM_PREC_F64 || !ctx->eo_tiles[p->prec]) && use_quad(ctx->hgeo.V, n);
+    return p->solver == TM_SOLVER_CG && march_tseg(ctx, p, nr) == 0 && use_quad(ctx->geo.V, n);
+}
+// sources that a block of n is solved with
+static int lane_pad(const tm_ctx* ctx, const tsm_solve_params* p, int nr, int n) {
+    return quad_solve(ctx, p, nr, n) ? n : (n + nr - 1) / nr * nr;
+}
+
 // the pinned mirror (allocated by tm_create) holds a block's scalars
 static tm_status ensure_scal_host(tm_ctx* ctx, int n) {
     if (ctx->scal_host_n >= n) return TM_OK;
@@ -388,6 +402,8 @@ static tm_status solve_block_eo(tm_ctx* ctx, const tsm_solve_params* p, uint64_t
     // FP32 arithmetic runs the tile kernels (links staged in LDS, shared by
     // the block's right-hand sides); FP64 the lane-per-site kernels
     const bool tiles = prec != P_F64 && ctx->eo_tiles[prec] != 0;
+    const bool quad = quad_solve(ctx, p, nr, nrhs);
+    if (quad) nr = 1;
     CgArgs a;
     std::memset(&a, 0, sizeof(a));
     a.geo = hg;
@@ -524,7 +540,6 @@ static tm_status solve_block_eo(tm_ctx* ctx, const tsm_solve_params* p, uint64_t
     // merged reductions: the state alternates between two arrays, iteration k
     // reads array k % 2
     const bool merged = !rel && !track && !tiles && merge_parts(a.npart, nrhs);
-    const bool quad = !tiles && use_quad(hg.V, nrhs);
     auto state = [&](int k) { return scal0 + (merged && (k & 1) ? kMaxBlock : 0); };
     const CgArgs a0 = a;
     const int vtag = prof_tag(prec, prec == P_F64 ? 1 : nr, TM_SOLVER_CG_EO, 0, rel);
@@ -810,6 +825,8 @@ static tm_status solve_block(tm_ctx* ctx, const tsm_solve_params* p, uint64_t se
     a.nrhs = nrhs;
     // time-marching K1 / K2 when a segment length is set for this precision
     a.tseg = march_tseg(ctx, p, nr);
+    const bool quad = quad_solve(ctx, p, nr, nrhs);
+    if (quad) nr = 1;
     a.npart = a.tseg > 0 ? march_partials(g, a.tseg) : (uint32_t)((g.V + 63) / 64);
     const size_t npart_max = partials_per_rhs(g, ctx->hgeo, ctx->eo_ok);
     // directions in a ring, as in solve_block_eo; the source is read by the CG
@@ -874,7 +891,6 @@ static tm_status solve_block(tm_ctx* ctx, const tsm_solve_params* p, uint64_t se
 
     // merged reductions (as in solve_block_eo)
     const bool merged = !rel && !track && a.tseg == 0 && merge_parts(a.npart, nrhs);
-    const bool quad = a.tseg == 0 && use_quad(g.V, nrhs);
     // small launches in FP64 and FP32 also form p in K1, alternating between two
     // buffers (the sources are not needed any more); the last step of a chunk is
     // finished by a launch of its own
@@ -1423,7 +1439,7 @@ tm_status tsm_solve_batch(tm_ctx* ctx, const tsm_solve_params* params, uint64_t 
     const bool rings = ring_room(ctx, params, (std::min(blk, nsrc) + nr - 1) / nr * nr);
     for (int j0 = 0; j0 < nsrc; j0 += blk) {
         const int nb = std::min(blk, nsrc - j0);
-        const int nbp = (nb + nr - 1) / nr * nr;
+        const int nbp = lane_pad(ctx, params, nr, nb);
         BlockResult res;
         s = solve_block(ctx, params, sm, ids_dev + j0, nbp, nr, "sb", &res, rings);
         if (s != TM_OK) return s;
@@ -1590,11 +1606,11 @@ tm_status tsm_loops(tm_ctx* ctx, const tsm_params* P, double* loops_host, double
     for (int j0 = 0; j0 < P->n_hp; j0 += bh) {
         const int nb = std::min(bh, P->n_hp - j0);
         BlockResult res;
-        const int nbl = (nb + nr_lp - 1) / nr_lp * nr_lp;
+        const int nbl = lane_pad(ctx, &P->lp, nr_lp, nb);
         if ((s = solve(false, ids_dev + j0, nbl, &res)) != TM_OK) return s;
         record(j0, nb, 0, false);
         contract_block(ctx, &c, ids_dev + j0, res.x, res.xprec, nb, (double2*)ps, slots_dev + j0, nl, res.xe);
-        const int nbh = (nb + nr_hp - 1) / nr_hp * nr_hp;
+        const int nbh = lane_pad(ctx, &P->hp, nr_hp, nb);
         if ((s = solve(true, ids_dev + j0, nbh, &res)) != TM_OK) return s;
         record(j0, nb, 1, true);
         contract_block(ctx, &c, ids_dev + j0, res.x, res.xprec, nb, (double2*)ps, slots_dev + Npad + j0, nl);
@@ -1605,7 +1621,7 @@ tm_status tsm_loops(tm_ctx* ctx, const tsm_params* P, double* loops_host, double
     // LP set: ids n_hp..N-1
     for (int j0 = P->n_hp; j0 < N; j0 += blp) {
         const int nb = std::min(blp, N - j0);
-        const int nbl = (nb + nr_lp - 1) / nr_lp * nr_lp;
+        const int nbl = lane_pad(ctx, &P->lp, nr_lp, nb);
         BlockResult res;
         if ((s = solve(false, ids_dev + j0, nbl, &res)) != TM_OK) return s;
         record(j0, nb, 0, false);
@@ -1649,7 +1665,7 @@ tm_status tm_autotune_cg(tm_ctx* ctx, int32_t prec, int32_t nrhs, int32_t* best_
     p.stop = TM_STOP_NORMAL;
     p.rhs_block = nrhs;
     p.true_resid = 0;
-    double best = 1e300;
+    double best = 1e300, quad_ms = 1e300;
     int bnr = 1, bts = 0;
     const bool rings = ring_room(ctx, &p, nrhs);
     for (int c = 0; c < kTuneCandidates; c++) {
@@ -1660,8 +1676,9 @@ tm_status tm_autotune_cg(tm_ctx* ctx, int32_t prec, int32_t nrhs, int32_t* best_
         ctx->march[prec] = ts;
         // per-iteration time: difference of a long and a short truncated
         // solve (initialisation cancels), best of two
-        double per = 1e300;
-        for (int rep = 0; rep < 3; rep++) {
+        const bool quad = quad_solve(ctx, &p, nr, nrhs);
+        double per = quad ? quad_ms : 1e300;
+        for (int rep = per < 1e300 ? 3 : 0; rep < 3; rep++) {
             double t[2];
             for (int j = 0; j < 2; j++) {
                 p.max_iter = j == 0 ? 2 : 10;
@@ -1676,6 +1693,7 @@ tm_status tm_autotune_cg(tm_ctx* ctx, int32_t prec, int32_t nrhs, int32_t* best_
             if (rep > 0) per = std::min(per, (t[1] - t[0]) / 8.0);  // the first pass warms up
         }
         if (s != TM_OK) break;
+        if (quad) quad_ms = per;  // (the other widths run the same kernels)
         if (ms_host) ms_host[c] = per;
         if (per < best) {
             best = per;
@@ -1720,7 +1738,7 @@ tm_status tm_autotune_eo(tm_ctx* ctx, int32_t prec, int32_t nrhs, int32_t* best_
     p.true_resid = 0;
     constexpr int kNrEo[6] = {1, 2, 4, 1, 2, 4};
     constexpr int kTilesEo[6] = {0, 0, 0, 1, 1, 1};
-    double best = 1e300;
+    double best = 1e300, quad_ms = 1e300;
     int bnr = 1, bt = 0;
     for (int c = 0; c < 6; c++) {
         const int nr = kNrEo[c], tl = kTilesEo[c];
@@ -1730,8 +1748,9 @@ tm_status tm_autotune_eo(tm_ctx* ctx, int32_t prec, int32_t nrhs, int32_t* best_
         ctx->eo_tiles[prec] = tl;
         // per-iteration time: difference of a long and a short truncated
         // solve (set-up and reconstruction cancel), best of two after a warm-up
-        double per = 1e300;
-        for (int rep = 0; rep < 3; rep++) {
+        const bool quad = quad_solve(ctx, &p, nr, nrhs);
+        double per = quad ? quad_ms : 1e300;
+        for (int rep = per < 1e300 ? 3 : 0; rep < 3; rep++) {
             double t[2];
             for (int j = 0; j < 2; j++) {
                 p.max_iter = j == 0 ? 2 : 8;
@@ -1746,6 +1765,7 @@ tm_status tm_autotune_eo(tm_ctx* ctx, int32_t prec, int32_t nrhs, int32_t* best_
             if (rep > 0) per = std::min(per, (t[1] - t[0]) / 6.0);
         }
         if (s != TM_OK) break;
+        if (quad) quad_ms = per;  // (the other widths run the same kernels)
         if (ms_host) ms_host[c] = per;
         if (per < best) {
             best = per;

@@ -90,3 +90,38 @@ assert out.nbytes == 4 << 20 and not out.any()
 assert s.hip.standin_device() == 0
 c.close()
 """)
+
+
+def test_small_solves_take_one_source_per_lane(tmp_path):
+    """Where the CG steps give each direction a wave, a lane width that is set
+    neither fills a block up with further sources nor is timed by the tuners
+    again (each candidate is 3 x 2 solves); tiles and marching keep theirs."""
+    run(tmp_path, """
+tq = s.tq
+dims = (8, 8, 8, 8)
+c = s.context(dims, 1 << 30)
+groups = {tq.SOLVER_CG: 64, tq.SOLVER_CG_EO: 32}
+for solver in groups:
+    for prec in (tq.PREC_F32, tq.PREC_F16):
+        tq.tm_set_lane_rhs(c, prec, 4)
+        p = tq.solve_params(prec=prec, tol=1e-2, rhs_block=4, solver=solver, true_resid=0)
+        for n in (1, 3, 4, 5):
+            tq.tsm_solve_batch(c, p, 7, list(range(n)), want_solutions=False)
+            grids = {g[0] for k, g in s.launches() if "k_quad_mp" in k}
+            want = {groups[solver] * (1 if n == 1 else min(n, 4))} | ({groups[solver]} if n == 5 else set())
+            assert grids == want, (solver, prec, n, grids)
+tq.tm_set_eo_tiles(c, tq.PREC_F16, 1)
+tq.tm_set_march(c, tq.PREC_F32, 4)
+tq.tm_set_lane_rhs(c, tq.PREC_F32, 2)
+tq.tm_set_lane_rhs(c, tq.PREC_F16, 2)
+for prec, solver, kernel in ((tq.PREC_F16, tq.SOLVER_CG_EO, "k_eot_mp<false, tmq::SF16, 2>"),
+                             (tq.PREC_F32, tq.SOLVER_CG, "k_tm_mp<float, tmq::SF32, tmq::GF32, 2>")):
+    p = tq.solve_params(prec=prec, tol=1e-2, rhs_block=4, solver=solver, true_resid=0)
+    tq.tsm_solve_batch(c, p, 7, [0], want_solutions=False)
+    assert any(kernel in k for k, _ in s.launches()), kernel
+tq.tm_autotune_cg(c, tq.PREC_BF16, 8)
+assert sum("k_scal_init" in k for k, _ in s.launches()) == 6 * 6
+tq.binding_tuning.tm_autotune_eo(c, tq.PREC_BF16, 8)
+assert sum("k_scal_init" in k for k, _ in s.launches()) == 4 * 6
+c.close()
+""")
