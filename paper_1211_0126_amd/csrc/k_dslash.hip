@@ -127,8 +127,7 @@ __global__ TM_STENCIL_R(NR, R) void k_cg_mp(CgArgs a) {
             if (!act[r]) continue;
             cx<R> pc[12], t[12];
             load_spinor<S, R>(field_rhs<S>(p0, Vs, r), Vs, s, pc);
-            diag_combine(pc, acc[r], (R)a.kappa, (R)a.twist, t);
-            settle<12>(t);
+            diag_combine_towards<S, R>(pc, acc[r], (R)a.kappa, (R)a.twist, t);
             round_storage<S, R>(t);
             store_spinor_cp<S, R, TM_CP_K1T>(field_rhs<S>(a.t, Vs, r0 + r), Vs, s, t);
             part[r] = spinor_norm2(t);
@@ -233,8 +232,7 @@ __global__ TM_STENCIL_R(NR, R) void k_cg_upd(CgArgs a) {
             load_spinor_cp<S, R, TM_CP_K2>(rp, Vs, s, rv);
             const R al = (R)alpha;
 #pragma unroll
-            for (int k = 0; k < 12; k++) rv[k] = rv[k] - al * q[k];
-            settle<12>(rv);
+            for (int k = 0; k < 12; k++) rv[k] = sub_towards<S, R>(rv[k], al, q[k]);
             round_storage<S, R>(rv);
             store_spinor_cp<S, R, TM_CP_K2>(rp, Vs, s, rv);
             prr[r] = spinor_norm2(rv);

@@ -276,18 +276,17 @@ __global__ __launch_bounds__(256) void k_quad_lin(EoArgs a) {
 }
 
 // part W of the operator: EO D v + k2 hops (k2 = -kappa^2), else v - kappa hops
-// + i tw g5 v (the expressions of mul_diag and diag_combine)
-template <bool EO, bool DAG, int K, typename R>
+// + i tw g5 v (the expressions of mul_diag and diag_combine; K1 of the whole
+// lattice towards its storage, ST = S)
+template <bool EO, bool DAG, int K, class ST, typename R>
 __device__ __forceinline__ cx<R> op_comp(cx<R> v, const cx<R>* sh, R kap, R tw) {
     const cx<R> h = hop_comp<K, DAG, R>(sh);
     if constexpr (EO) {
         const R sg = K < 6 ? tw : -tw;
         const cx<R> d = {v.re - sg * v.im, v.im + sg * v.re};
         return d + kap * h;
-    } else if constexpr (K < 6) {
-        return {v.re - kap * h.re - tw * v.im, v.im - kap * h.im + tw * v.re};
     } else {
-        return {v.re - kap * h.re + tw * v.im, v.im - kap * h.im - tw * v.re};
+        return diag_towards<ST, K, R>(v, h, kap, tw);
     }
 }
 
@@ -312,11 +311,10 @@ __global__ __launch_bounds__(256) void k_quad_mp(CgArgs a, EoCg e) {
     if (on)
         for_part<S>(q.w, [&](auto W) {
             constexpr int K0 = W.value * N;
-            o[0] = op_comp<EO, false, K0>(o[0], sh, kap, tw);
-            o[1] = op_comp<EO, false, K0 + 1>(o[1], sh, kap, tw);
-            o[2] = op_comp<EO, false, K0 + 2>(o[2], sh, kap, tw);
-            if constexpr (N == 4) o[3] = op_comp<EO, false, K0 + 3>(o[3], sh, kap, tw);
-            if constexpr (!EO) settle<N>(o);
+            o[0] = op_comp<EO, false, K0, S>(o[0], sh, kap, tw);
+            o[1] = op_comp<EO, false, K0 + 1, S>(o[1], sh, kap, tw);
+            o[2] = op_comp<EO, false, K0 + 2, S>(o[2], sh, kap, tw);
+            if constexpr (N == 4) o[3] = op_comp<EO, false, K0 + 3, S>(o[3], sh, kap, tw);
             round_part<S, R, N>(o);
             store_part<S, R, N>(field_rhs<S>(a.t, Vs, q.r), Vs, q.s, W.value, o);
         });
@@ -415,11 +413,10 @@ __global__ __launch_bounds__(256) void k_quad_mp_fold(CgArgs a) {
 #pragma unroll
             for (int c = 0; c < N; c++) o[c] = rv[c] + be * o[c];
             store_part<S, R, N>(field_rhs<S>(a.pn, Vs, q.r), Vs, q.s, W.value, o);
-            o[0] = op_comp<false, false, K0>(o[0], sh, kap, tw);
-            o[1] = op_comp<false, false, K0 + 1>(o[1], sh, kap, tw);
-            o[2] = op_comp<false, false, K0 + 2>(o[2], sh, kap, tw);
-            if constexpr (N == 4) o[3] = op_comp<false, false, K0 + 3>(o[3], sh, kap, tw);
-            settle<N>(o);
+            o[0] = op_comp<false, false, K0, S>(o[0], sh, kap, tw);
+            o[1] = op_comp<false, false, K0 + 1, S>(o[1], sh, kap, tw);
+            o[2] = op_comp<false, false, K0 + 2, S>(o[2], sh, kap, tw);
+            if constexpr (N == 4) o[3] = op_comp<false, false, K0 + 3, S>(o[3], sh, kap, tw);
             store_part<S, R, N>(field_rhs<S>(a.t, Vs, q.r), Vs, q.s, W.value, o);
         });
     __syncthreads();  // (every wave has read the hops)
@@ -469,13 +466,16 @@ __global__ __launch_bounds__(256) void k_quad_upd(CgArgs a, EoCg e) {
     if (on)
         for_part<S>(q.w, [&](auto W) {
             constexpr int K0 = W.value * N;
-            o[0] = op_comp<EO, true, K0>(o[0], sh, kap, tw);
-            o[1] = op_comp<EO, true, K0 + 1>(o[1], sh, kap, tw);
-            o[2] = op_comp<EO, true, K0 + 2>(o[2], sh, kap, tw);
-            if constexpr (N == 4) o[3] = op_comp<EO, true, K0 + 3>(o[3], sh, kap, tw);
+            o[0] = op_comp<EO, true, K0, SF32>(o[0], sh, kap, tw);
+            o[1] = op_comp<EO, true, K0 + 1, SF32>(o[1], sh, kap, tw);
+            o[2] = op_comp<EO, true, K0 + 2, SF32>(o[2], sh, kap, tw);
+            if constexpr (N == 4) o[3] = op_comp<EO, true, K0 + 3, SF32>(o[3], sh, kap, tw);
 #pragma unroll
-            for (int c = 0; c < N; c++) rv[c] = rv[c] - al * o[c];
-            if constexpr (!EO) settle<N>(rv);
+            for (int c = 0; c < N; c++)
+                if constexpr (EO)
+                    rv[c] = rv[c] - al * o[c];
+                else
+                    rv[c] = sub_towards<S, R>(rv[c], al, o[c]);
             round_part<S, R, N>(rv);
             store_part<S, R, N>(rp, Vs, q.s, W.value, rv);
             if constexpr (!XFREE) {

@@ -235,14 +235,48 @@ __device__ __forceinline__ void diag_combine(const cx<R> p[12], const cx<R> acc[
         out[k] = {p[k].re - kappa * acc[k].re + tw * p[k].im, p[k].im - kappa * acc[k].im - tw * p[k].re};
 }
 
-// The values as they are here, in FP32 or FP64: a following rounding to FP16 is
-// then a rounding of them (the compiler may otherwise round to FP16 within the
-// last multiply-add, of some components and not of others, which the kernels of
-// different lane widths do not share).
-template <int N, typename R>
-__device__ __forceinline__ void settle(cx<R>* v) {
-#pragma unroll
-    for (int k = 0; k < N; k++) asm("" : "+v"(v[k].re), "+v"(v[k].im));
+// FP16 fields of the whole-lattice CG are rounded within the last multiply-add
+// of a component, as FP16 values a b + c (one rounding), in every kernel that
+// forms them: written out, because the compiler does so for some components and
+// not for others, and not alike at different lane widths.
+__device__ __forceinline__ float fma_f16(float a, float b, float c) {
+    uint32_t d;
+    asm("v_fma_mixlo_f16 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+    return f16_to_f32(d & 0xFFFFu);
+}
+// a b + c towards storage S
+template <class S, typename R>
+__device__ __forceinline__ R fma_towards(R a, R b, R c) {
+    if constexpr (std::is_same<S, SF16>::value)
+        return fma_f16(a, b, c);
+    else
+        return fma(a, b, c);
+}
+// component K of diag_combine towards storage S (K1; in FP16 the last component
+// alone is formed in FP32 and then rounded)
+template <class S, int K, typename R>
+__device__ __forceinline__ cx<R> diag_towards(const cx<R>& p, const cx<R>& h, R kappa, R tw) {
+    const R g = K < 6 ? -tw : tw;
+    const R re = fma(-kappa, h.re, p.re), im = fma(-kappa, h.im, p.im);
+    if constexpr (std::is_same<S, SF16>::value && K == 11) {
+        cx<R> o = {fma(g, p.im, re), fma(-g, p.re, im)};
+        asm("" : "+v"(o.re), "+v"(o.im));
+        return o;
+    }
+    return {fma_towards<S, R>(g, p.im, re), fma_towards<S, R>(-g, p.re, im)};
+}
+template <class S, typename R, int K = 0>
+__device__ __forceinline__ void diag_combine_towards(const cx<R> p[12], const cx<R> acc[12], R kappa, R tw,
+                                                     cx<R> out[12]) {
+    if constexpr (K < 12) {
+        out[K] = diag_towards<S, K, R>(p[K], acc[K], kappa, tw);
+        diag_combine_towards<S, R, K + 1>(p, acc, kappa, tw, out);
+    }
+}
+// r - al q towards storage S (K2)
+template <class S, typename R>
+__device__ __forceinline__ cx<R> sub_towards(const cx<R>& r, R al, const cx<R>& q) {
+    return {fma_towards<S, R>(-al, q.re, r.re), fma_towards<S, R>(-al, q.im, r.im)};
 }
 
 // |v|^2 where only one kernel forms it, contracted as the compiler likes.  (How
