@@ -228,37 +228,39 @@ struct HalfRaw<SF32> {  // planes of 2 components: planes 3h, 3h+1, 3h+2
 struct LyPath {
     uint32_t y;      // neighbour site
     uint32_t link;   // link of the path (0 ... 7: +-x, +-y, +-z, +-t)
+    uint32_t flip;   // 0x80008000 where the time-boundary sign applies
     bool ident, pad;
 };
 
 template <int P>
-__device__ __forceinline__ LyPath ly_path(const uint32_t ys[9]) {
+__device__ __forceinline__ LyPath ly_path(const uint32_t ys[9], uint32_t flip_f, uint32_t flip_b) {
     LyPath d;
     d.pad = P >= 9;
     d.ident = P == 0;
     d.y = (P >= 1 && P <= 8) ? ys[P] : ys[0];
     d.link = (P >= 1 && P <= 8) ? (uint32_t)(P - 1) : 0u;  // identity and padding read direction 0's link
+    d.flip = P == 7 ? flip_f : P == 8 ? flip_b : 0u;
     return d;
 }
 __device__ __forceinline__ LyPath ly_select(bool hi, const LyPath& a, const LyPath& b) {
     LyPath d;
     d.y = hi ? b.y : a.y;
     d.link = hi ? b.link : a.link;
+    d.flip = hi ? b.flip : a.flip;
     d.ident = hi ? b.ident : a.ident;
     d.pad = hi ? b.pad : a.pad;
     return d;
 }
 
 // The eight links of a wave's 16 sites in LDS, [link][plane][site], each entry
-// V of the oriented link (U_mu(x), or U_mu(x - mu)^dag, with the time-boundary
-// sign) as the two bfloat16 pairs that a product with (re, im) takes:
-// dword e: (Re V, -Im V) for the real part, dword 9 + e: (Im V, Re V) for the
-// imaginary part, e = 3 c + k.  Lane 16 g + i prepares links g and 4 + g of
-// site i.
+// V of the oriented link (U_mu(x), or U_mu(x - mu)^dag) as the two bfloat16
+// pairs that a product with (re, im) takes: dword e: (Re V, -Im V) for the real
+// part, dword 9 + e: (Im V, Re V) for the imaginary part, e = 3 c + k.  Lane
+// 16 g + i prepares links g and 4 + g of site i.
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 constexpr int LY_LP = 5;  // planes of 16 bytes per link (18 dwords)
-__device__ __forceinline__ void ly_stage_links(const PtArgs& a, uint32_t PB, const uint32_t ys[9], uint32_t flip_f,
-                                               uint32_t flip_b, int g, int i, v4u* sl) {
+__device__ __forceinline__ void ly_stage_links(const PtArgs& a, uint32_t PB, const uint32_t ys[9], int g, int i,
+                                               v4u* sl) {
     const bool bwd = (g & 1) != 0;  // (link l: mu = l >> 1, backward if odd)
     const uint32_t mb = bwd ? ~0u : 0u;
     uint4 u0[2], u1[2];
@@ -276,8 +278,7 @@ __device__ __forceinline__ void ly_stage_links(const PtArgs& a, uint32_t PB, con
 #pragma unroll
     for (int it = 0; it < 2; it++) {
         const uint32_t u[9] = {u0[it].x, u0[it].y, u0[it].z, u0[it].w, u1[it].x, u1[it].y, u1[it].z, u1[it].w, u8[it]};
-        const uint32_t flip = it == 0 ? 0u : g == 2 ? flip_f : g == 3 ? flip_b : 0u;
-        const uint32_t s1 = (bwd ? 0u : 0x80000000u) ^ flip, s2 = (bwd ? 0x8000u : 0u) ^ flip;
+        const uint32_t s1 = bwd ? 0u : 0x80000000u, s2 = bwd ? 0x8000u : 0u;
         uint32_t w[4 * LY_LP];
 #pragma unroll
         for (int c = 0; c < 3; c++)
@@ -324,7 +325,9 @@ __device__ __forceinline__ void ly_operand(const HalfRaw<Si>& raw, int h, const 
             ti = dot2(q[3 * t + 1], m[9 + 3 * c + 1], ti);
             tr = dot2(q[3 * t + 2], m[3 * c + 2], tr);
             ti = dot2(q[3 * t + 2], m[9 + 3 * c + 2], ti);
-            const uint32_t tv = pack2_bf16(tr, ti);
+            // (the time-boundary sign here, not in the link: a dot2 of negated
+            // products is not always the negative of the dot2)
+            const uint32_t tv = pack2_bf16(tr, ti) ^ d.flip;
             B[c][t] = d.pad ? 0u : d.ident ? q[3 * t + c] : tv;
         }
 }
@@ -347,27 +350,29 @@ __device__ __forceinline__ void ly_operand(const HalfRaw<Si>& raw, int h, const 
 // side at a time with four waves per SIMD: 195).
 constexpr uint32_t LY_PER = 4;
 
-template <int CIN, int KS>
-__device__ __forceinline__ LyPath ly_step(const uint32_t ys[9], bool hi) {
-    if constexpr (CIN == 2)
-        return ly_path<KS>(ys);
-    else
-        return ly_select(hi, ly_path<2 * KS>(ys), ly_path<2 * KS + 1>(ys));
-}
-
 // What one wave knows of its 16 sites
 struct LyWave {
     uint32_t ys[9];   // the site and its neighbours
     uint32_t sout;    // site to store (~0: past the lattice)
+    uint32_t flip_f, flip_b;  // time-boundary sign of its forward and backward time hop
     int g, i;         // lane = 16 g + i
     const v4u* sl;    // links in LDS
 };
+
+template <int CIN, int KS>
+__device__ __forceinline__ LyPath ly_step(const LyWave& w) {
+    if constexpr (CIN == 2)
+        return ly_path<KS>(w.ys, w.flip_f, w.flip_b);
+    else
+        return ly_select((w.g >> 1) != 0, ly_path<2 * KS>(w.ys, w.flip_f, w.flip_b),
+                         ly_path<2 * KS + 1>(w.ys, w.flip_f, w.flip_b));
+}
 
 template <class Si, int CIN, int KS, int NKS, int NRC>
 __device__ __forceinline__ void ly_loads(const PtArgs& a, const LyWave& w, uint32_t PB, uint32_t r0,
                                          HalfRaw<Si> raw[2][NRC]) {
     if constexpr (KS < NKS) {
-        const LyPath d = ly_step<CIN, KS>(w.ys, (w.g >> 1) != 0);
+        const LyPath d = ly_step<CIN, KS>(w);
 #pragma unroll
         for (int j = 0; j < NRC; j++)
             raw[KS & 1][j].load(field_rhs<Si>(a.in, a.geo.Vs, (int)((r0 + j) * CIN)), PB,
@@ -382,9 +387,9 @@ __device__ __forceinline__ void ly_steps(const PtArgs& a, const LyWave& w, uint3
                                          const v4s wf[NKS], HalfRaw<Si> raw[2][NRC],
                                          const v4u m[LY_LP], v4f D[NRC][3]) {
     v4u mn[LY_LP];
-    if constexpr (KS + 1 < NKS) ly_link(w.sl, w.i, ly_step<CIN, KS + 1>(w.ys, (w.g >> 1) != 0), mn);
+    if constexpr (KS + 1 < NKS) ly_link(w.sl, w.i, ly_step<CIN, KS + 1>(w), mn);
     ly_loads<Si, CIN, KS + 1, NKS, NRC>(a, w, PB, r0, raw);
-    const LyPath d = ly_step<CIN, KS>(w.ys, (w.g >> 1) != 0);
+    const LyPath d = ly_step<CIN, KS>(w);
 #pragma unroll
     for (int j = 0; j < NRC; j++) {
         uint32_t B[3][2];
@@ -413,7 +418,7 @@ __device__ __forceinline__ void ly_chunk(const PtArgs& a, const LyWave& w, uint3
     HalfRaw<Si> raw[2][NRC];
     ly_loads<Si, CIN, 0, NKS, NRC>(a, w, PB, r0, raw);
     v4u m[LY_LP];
-    ly_link(w.sl, w.i, ly_step<CIN, 0>(w.ys, (g >> 1) != 0), m);
+    ly_link(w.sl, w.i, ly_step<CIN, 0>(w), m);
     ly_steps<Si, CIN, 0, NKS, NRC>(a, w, PB, r0, wf, raw, m, D);
     // lane holds channel g>>1, spins 2h and 2h+1: component 6h + 3t + c is
     // (D[c][2t], D[c][2t + 1])
@@ -476,7 +481,7 @@ __global__ __launch_bounds__(LY_THREADS) __attribute__((amdgpu_waves_per_eu(std:
     w.g = g;
     w.i = lane & 15;
     w.sout = valid ? s : ~0u;
-    uint32_t flip_f = 0, flip_b = 0;
+    w.flip_f = w.flip_b = 0;
     uint32_t* ys = w.ys;
     {
         const Site c = site_coords(geo, s);
@@ -487,13 +492,13 @@ __global__ __launch_bounds__(LY_THREADS) __attribute__((amdgpu_waves_per_eu(std:
             ys[2 + 2 * mu] = nb_bwd(geo, s, c, mu);
         }
         if (geo.t_bc < 0) {
-            flip_f = (c.t + 1 == geo.L[3]) ? 0x80008000u : 0u;
-            flip_b = (c.t == 0) ? 0x80008000u : 0u;
+            w.flip_f = (c.t + 1 == geo.L[3]) ? 0x80008000u : 0u;
+            w.flip_b = (c.t == 0) ? 0x80008000u : 0u;
         }
     }
     __shared__ v4u links[LY_THREADS / 64][8 * LY_LP * 16];
     v4u* sl = links[threadIdx.x >> 6];
-    ly_stage_links(a, PB, ys, flip_f, flip_b, g, lane & 15, sl);
+    ly_stage_links(a, PB, ys, g, lane & 15, sl);
     w.sl = sl;
     v4s wf[NKS];
 #pragma unroll
