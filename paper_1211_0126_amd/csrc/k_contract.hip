@@ -292,8 +292,12 @@ __device__ __forceinline__ cx<A> z4_unit(uint32_t nb, uint32_t flip) {
 // so two transports and two products with the noise per link instead of four.
 // w(x+mu) / w(x) is one phase for a spatial mu and the next time slice for mu
 // = 3; stage C applies it.  Every product with the noise is a Z4 permutation.
-// An FP32 solution takes FP32 links and FP32 arithmetic (its y sums too,
-// about 1e-6 relative); an FP64 one FP64 throughout.
+// An FP32 solution takes FP32 links and arithmetic, an FP64 one FP64; the y sums
+// are FP64 for both: the rounding of D counts twice in the sum over x and x + mu,
+// and with FP32 sums the loops of FP32 solutions were 7.6e-8 (8^3 x 16) and
+// 4.6e-8 (16^3 x 32) off the FP64 ones against 6.9e-8 and 3.9e-8 with four
+// transports; with FP64 sums 5.8e-8 and 2.8e-8 (16 sources at 24^3 x 48: 2.05
+// -> 2.51 ms, with four transports 3.33).
 // Bound by FP64 arithmetic and the latency of a row site's loads (about 700
 // vector instructions per row site and lane, two waves per SIMD): four sources
 // at 24^3 x 48 from canonical solutions 0.74 ms, against 1.41 with the four
@@ -328,11 +332,11 @@ __global__ __launch_bounds__(kDerivBlock) void k_contract_d(ContractArgs a) {
     const void* sol = field_rhs<S>(a.sol, field_stride<S>(g), r);
     const uint64_t id = a.ids[r];
     const uint64_t V = (uint64_t)g.V;
-    cx<A> acc[3][8];
+    cx<double> acc[3][8];
 #pragma unroll
     for (int i = 0; i < 3; i++)
 #pragma unroll
-        for (int e = 0; e < 8; e++) acc[i][e] = {(A)0, (A)0};
+        for (int e = 0; e < 8; e++) acc[i][e] = {0.0, 0.0};
     // the neighbour's coordinates by selects (a coordinate array indexed by mu
     // would live in scratch memory)
     const int cmu = mu == 0 ? x : (mu == 2 ? z : t), Lmu = mu == 0 ? Lx : (mu == 2 ? Lz : Lt);
@@ -378,9 +382,9 @@ __global__ __launch_bounds__(kDerivBlock) void k_contract_d(ContractArgs a) {
         for (int i = 0; i < 3; i++) {
             if (i < npy) {
                 const double2 ph = a.phy[i * Ly + y];
-                const cx<A> w = {(A)(0.25 * ph.x), (A)(0.25 * ph.y)};
+                const cx<double> w = {0.25 * ph.x, 0.25 * ph.y};
 #pragma unroll
-                for (int e = 0; e < 8; e++) cmac_f(acc[i][e], w, S8[e]);
+                for (int e = 0; e < 8; e++) cmac_f(acc[i][e], w, cx<double>{(double)S8[e].re, (double)S8[e].im});
             }
         }
     }
@@ -390,7 +394,7 @@ __global__ __launch_bounds__(kDerivBlock) void k_contract_d(ContractArgs a) {
         if (i < npy) {
             double2* o = a.A + (((((size_t)rs * Lt + t) * Lz + z) * npy + i) * Lx + x) * 16 + 8 * h;
 #pragma unroll
-            for (int e = 0; e < 8; e++) o[e] = make_double2((double)acc[i][e].re, (double)acc[i][e].im);
+            for (int e = 0; e < 8; e++) o[e] = make_double2(acc[i][e].re, acc[i][e].im);
         }
     }
 }
