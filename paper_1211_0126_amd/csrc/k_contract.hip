@@ -418,6 +418,8 @@ struct CarrySum {
     __device__ __forceinline__ cx<double> value() const { return s + c; }
 };
 
+// DERIV: the one-derivative loops (nmu 4)
+template <bool DERIV>
 __global__ __launch_bounds__(256) void k_contract_b(ContractArgs a) {
     const Geom& g = a.geo;
     const int Lx = g.L[0], Lz = g.L[2], Lt = g.L[3];
@@ -437,7 +439,7 @@ __global__ __launch_bounds__(256) void k_contract_b(ContractArgs a) {
     for (int i = 0; i < 3; i++) acc[i] = {0.0, 0.0};
     // the 16 lanes of one (iy, z, t) read the 16 entries of an x together
     const double2* in = a.A + ((((size_t)r * Lt + t) * Lz + z) * npy + iy) * Lx * 16 + e;
-    if (a.nmu == 4) {
+    if constexpr (DERIV) {
         CarrySum sum[3];
         for (int x = 0; x < Lx; x++) {
             const double2 v = in[(size_t)x * 16];
@@ -471,6 +473,7 @@ __global__ __launch_bounds__(256) void k_contract_b(ContractArgs a) {
                 make_double2(acc[i].re, acc[i].im);
 }
 
+template <bool DERIV>
 __global__ __launch_bounds__(256) void k_contract_c(ContractArgs a) {
     const Geom& g = a.geo;
     const int Lz = g.L[2], Lt = g.L[3];
@@ -485,9 +488,9 @@ __global__ __launch_bounds__(256) void k_contract_c(ContractArgs a) {
     const int t = (int)(q / a.n_mom);
     const int ix = a.mom_idx[3 * m], iy = a.mom_idx[3 * m + 1], iz = a.mom_idx[3 * m + 2];
     cx<double> acc = {0.0, 0.0};
-    // one-derivative loops (nmu 4): the link sums D at x and at x + mu, the
-    // second the previous time slice's for mu = 3, else a phase
-    const int mu = a.nmu == 4 ? r % 4 : -1;
+    // one-derivative loops: the link sums D at x and at x + mu, the second the
+    // previous time slice's for mu = 3, else a phase
+    const int mu = DERIV ? r % 4 : -1;
     CarrySum sum;
     for (int zz = 0; zz < (mu == 3 ? 2 * Lz : Lz); zz++) {
         const int z = zz < Lz ? zz : zz - Lz, tz = zz < Lz ? t : (t == 0 ? Lt - 1 : t - 1);
@@ -501,12 +504,12 @@ __global__ __launch_bounds__(256) void k_contract_c(ContractArgs a) {
             tr = tr + ph * cx<double>{v.x, v.y};
         }
         const double2 pz = a.phz[iz * Lz + z];
-        if (mu >= 0)
+        if constexpr (DERIV)
             sum.add(cmul_f(cx<double>{pz.x, pz.y}, tr));
         else
             acc = acc + cx<double>{pz.x, pz.y} * tr;
     }
-    if (mu >= 0) acc = sum.value();
+    if constexpr (DERIV) acc = sum.value();
     if (mu >= 0 && mu < 3) {
         const double2 pm = mu == 0 ? a.phx[ix * g.L[0] + 1] : (mu == 1 ? a.phy[iy * g.L[1] + 1] : a.phz[iz * Lz + 1]);
         acc = cx<double>{1.0 + pm.x, pm.y} * acc;
@@ -553,9 +556,11 @@ void launch_contract(hipStream_t st, const ContractArgs& a0, int xprec, bool can
     else if (a.est == 0)
         run_a(std::integral_constant<int, 0>{});
     const long nb = 16L * a.npy * g.L[2] * g.L[3];
-    hipLaunchKernelGGL(k_contract_b, dim3((unsigned)((nb + 255) / 256), (unsigned)a.nrhs), dim3(256), 0, st, a);
+    auto kb = a0.est == 3 ? k_contract_b<true> : k_contract_b<false>;
+    hipLaunchKernelGGL(kb, dim3((unsigned)((nb + 255) / 256), (unsigned)a.nrhs), dim3(256), 0, st, a);
     const long nc = 16L * a.n_mom * g.L[3];
-    hipLaunchKernelGGL(k_contract_c, dim3((unsigned)((nc + 255) / 256), (unsigned)a.nrhs), dim3(256), 0, st, a);
+    auto kc = a0.est == 3 ? k_contract_c<true> : k_contract_c<false>;
+    hipLaunchKernelGGL(kc, dim3((unsigned)((nc + 255) / 256), (unsigned)a.nrhs), dim3(256), 0, st, a);
 }
 
 // ---------------------------------------------------------------------------
