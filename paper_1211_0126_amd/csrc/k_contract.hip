@@ -26,7 +26,8 @@
 // The sums are in FP64, except stage A of the standard loop of an FP32
 // solution: its products with the noise are exact in FP32 and its y sums
 // (Ly terms) are taken in FP32, about 1e-7 relative, far below the FP32
-// solution's own rounding.  Every sum runs in a fixed order (bitwise
+// solution's own rounding, and except D of the one-derivative loops of an FP32
+// solution.  Every sum runs in a fixed order (bitwise
 // reproducible).
 
 #include <type_traits>

@@ -13,15 +13,18 @@
 // 256 with an XCD-aware block order.
 //
 // The CG iteration on M^dag M is five launches per step:
-//   K1  t = M p,                               block partials of |t|^2
+//   K1  t = M p,                               partials per wave of |t|^2
 //   R1  alpha = |r|^2/|t|^2                    (one block per right-hand side)
-//   K2  q = M^dag t,  r -= alpha q,  x += alpha p,  block partials of |r|^2
+//   K2  q = M^dag t,  r -= alpha q,  x += alpha p,  partials per wave of |r|^2
 //   R2  beta, stop test                        (one block per right-hand side)
 //   K3  p = r + beta p
 // with the scalars of every right-hand side kept on the device.  The
 // reductions are separate launches because a last-block-finalises pattern
 // needs a device-scope release per block, which on a multi-XCD part writes
-// back the XCD's L2 and costs more than the stencil itself.
+// back the XCD's L2 and costs more than the stencil itself.  Where there are few
+// partials (merge_parts) K2 and K3 sum those of the launch before themselves:
+// three launches; on the smallest (use_quad_fold) K1 also does K3: two.  With the
+// directions kept (CgArgs::pn) K2 leaves x alone.
 
 #include "tm_device.h"
 #include "tm_kernels.h"

@@ -22,11 +22,12 @@
 // and every link is read once per half-hop.
 //
 // Per CG iteration (k_eo_lin, k_eo_mp, k_eo_lin, k_eo_upd; the alpha and beta
-// reductions and p = r + beta p are the full-lattice kernels on the half
-// geometry):
+// reductions, where they are not merged into the update and the next, and p = r +
+// beta p are the full-lattice kernels on the half geometry):
 //   y = D^{-1} H_eo p          t = D p - kappa^2 H_oe y,  |t|^2
 //   y = D^{-dag} H_eo^dag t    q = D^dag t - kappa^2 H_oe^dag y,
-//                              r -= alpha q, x += alpha p, |r|^2
+//                              r -= alpha q, |r|^2 (x += alpha p where the
+//                              directions are not kept)
 
 #include <algorithm>
 

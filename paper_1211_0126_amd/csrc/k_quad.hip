@@ -505,10 +505,10 @@ bool use_quad(int64_t V, int nrhs) { return (V + 63) / 64 * nrhs <= 1536; }
 
 // launches whose K1 finishes the step before (k_quad_mp_fold): those whose
 // blocks are all resident at once, one per CU in FP64 and two in FP32.  LP
-// solves without / with: FP64 10x12x8x14, 1 source (210 blocks) 434 / 394 us,
-// 8^4, 4 (256) 437 / 396, 10x12x8x14, 2 (420) 523 / 537, 12^3 x 24, 1 (648)
-// 680 / 775; FP32 9x11x7x13, 1 (141) 795 / 758, 10x12x8x14, 2 (420) 414 / 393,
-// 12^3 x 24, 1 (648) 455 / 454, 2 (1296) 614 / 668.
+// solves without / with: FP64 10x12x8x14, 1 source (210 blocks) 376 / 343 us,
+// 9x11x7x13, 2 (282) 451 / 468, 10x12x8x14, 2 (420) 465 / 471, 12^3 x 24, 1
+// (648) 639 / 733; FP32 9x11x7x13, 1, 3 and 4 (141, 423, 564) 294 / 269, 368 /
+// 353 and 408 / 408, 12^3 x 24, 1 and 2 (648, 1296) 419 / 417 and 575 / 620.
 bool use_quad_fold(int64_t V, int nrhs, int prec) {
     return (V + 63) / 64 * nrhs <= (prec == P_F64 ? 256 : prec == P_F32 ? 512 : 0);
 }

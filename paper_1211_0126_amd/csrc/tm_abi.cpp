@@ -426,7 +426,11 @@ bool geom_setup(const tm_lattice* lat, Geom* gp, Geom* hp, bool* eo_ok, std::str
     // lattice.  At 24^3 x 48 (288 half sites a plane), 32 FP16 LP solves take
     // 19.1 ms in the natural order and 19.1, 18.2, 18.5, 18.3, 18.7 ms with bz
     // = 2, 3, 4, 6, 8; two FP64 applications of M 2.31 ms and 2.17, 2.13,
-    // 2.15, 2.14, 2.19 ms.
+    // 2.15, 2.14, 2.19 ms.  Natural order / these slabs on other lattices, M on
+    // four FP64 fields and CG steps of 16 FP32 sources: 20^3 x 40 0.43 / 0.41
+    // and 10.2 / 9.5 ms, 28^3 x 56 1.62 / 1.54 and 39.1 / 36.3, 36x12x36x24
+    // 0.53 / 0.47 and 12.2 / 10.9; 16 FP16 even-odd LP solves 4.34 / 4.34, 17.8 /
+    // 16.9 and 5.13 / 5.00 ms.
     auto set_slab = [](Geom& q, double target) {
         q.slab = q.slab_m = 0;
         const double plane = (double)(q.V / ((long)q.L[2] * q.L[3]));

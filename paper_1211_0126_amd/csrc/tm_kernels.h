@@ -20,14 +20,14 @@ struct CgArgs {
     void* rho;          // recursive true residual (stop on |eta - M x|)
     const void* eta64;  // reliable updates stopping on |eta - M x|: the FP64 sources
     CgScal* scal;
-    double* partials;   // [nrhs][nblocks]
-    double* partials2;  // [nrhs][nblocks]
+    double* partials;   // [nrhs][npart]
+    double* partials2;  // [nrhs][npart]
     int nrhs;
-    uint32_t npart;     // block partials per right-hand side written by K1 / K2
+    uint32_t npart;     // partials per right-hand side written by K1 / K2
     int tseg;           // time slices per lane of the time-marching K1 / K2
-    // search directions in a ring (even-odd CG without reduced-precision
-    // reliable updates): K3 writes p_{k+1} to pn instead of over p, the step
-    // lengths go to ahist[r][k % ring], and x is formed from them afterwards
+    // search directions in a ring (16-bit storage, and the even-odd CG in FP32
+    // without reliable updates): K3 writes p_{k+1} to pn instead of over p, the
+    // step lengths go to ahist[r][k % ring], and x is formed from them afterwards
     void* pn;           // nullable: p = r + beta p in place
     double* ahist;      // nullable: [nrhs][ring]
     int ring;
@@ -172,14 +172,16 @@ void launch_eo_mp(hipStream_t st, const CgArgs& a, const EoCg& e, int prec, int 
 void launch_eo_upd(hipStream_t st, const CgArgs& a, const EoCg& e, int prec, int nr, bool track);
 // K2b without the solution update (directions kept in a ring), and the
 // update x += sum_k alpha_k p_k over iterations k0 <= k < min(k1, iterations
-// of the source), p_k in slot k % ring of `dirs` (slot_bytes apart)
+// of the source), p_k in slot k % ring of `dirs` (slot_bytes apart); the sum is
+// written to out in out_prec, P_F32 or P_F16 (out nullptr: a.x)
 void launch_eo_upd_xfree(hipStream_t st, const CgArgs& a, const EoCg& e, int prec, int nr, bool track);
-// (the sum is written to out in out_prec, P_F32 or P_F16; out nullptr: a.x)
+void launch_eo_xflush(hipStream_t st, const CgArgs& a, int prec, const void* dirs, size_t slot_bytes, int k0, int k1,
+                      void* out = nullptr, int out_prec = P_F32);
+// the same with reliable updates: into x32 before the ring is full, and into x64
+// where the reliable flag is set (force: everywhere)
 void launch_ring_add(hipStream_t st, const CgArgs& a, int prec, const void* dirs, size_t slot_bytes);
 void launch_ring_rel_flush(hipStream_t st, const CgArgs& a, int prec, const void* dirs, size_t slot_bytes, void* x64,
                            int force);
-void launch_eo_xflush(hipStream_t st, const CgArgs& a, int prec, const void* dirs, size_t slot_bytes, int k0, int k1,
-                      void* out = nullptr, int out_prec = P_F32);
 void launch_eo_rel_resid(hipStream_t st, const CgArgs& a, const EoCg& e, const void* b64, const void* t64,
                          const void* y64, int nr, int prec = P_F32);
 // the same half-hops with the links of a tile of 64 half-sites staged in LDS
@@ -245,9 +247,9 @@ void launch_noise_c128(hipStream_t st, const Geom& g, uint64_t seed_mixed, const
 
 // loops
 void launch_contract(hipStream_t st, const ContractArgs& a, int xprec, bool canon = false);
-// standard loops at all Lx*Ly*Lz momenta: site matrices into buf0, DFTs
-// ping-ponging buf0/buf1 (each nrhs * V * 16 double2), tw the x, y, z
-// phase tables exp(-2 pi i m / L) back to back
+// standard loops at all Lx*Ly*Lz momenta: traces and x DFT into buf0 (nrhs * V *
+// 16 double2), y DFT in place, z DFT into the loops; tw the x, y, z phase tables
+// exp(-2 pi i m / L) back to back
 void launch_contract_all_momenta(hipStream_t st, const ContractArgs& a, bool canon, double2* buf0, const double2* tw);
 void launch_tsm_final(hipStream_t st, const double* ps, long nl, int n_hp, int n_lp, double* out, double* err);
 

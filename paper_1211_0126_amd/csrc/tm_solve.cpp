@@ -1,10 +1,10 @@
 // Solver and TSM drivers: tsm_solve_batch, tsm_contract, tsm_loops.
 //
 // A block of right-hand sides is solved together: all vectors and all
-// per-source scalars live on the device, every CG step is three kernel
-// launches, and the host only polls the per-source stop flags once per
-// chunk of steps.  Each source's arithmetic is independent of the others in
-// its block (per-source scalars, masks and reductions in a fixed order), so
+// per-source scalars live on the device, a CG step is a few kernel launches
+// (k_dslash.hip, k_eo.hip), and the host only polls the per-source stop flags
+// once per chunk of steps.  Each source's arithmetic is independent of the others
+// in its block (per-source scalars, masks and reductions in a fixed order), so
 // the LP solution of a source does not depend on how the sources are
 // batched: the HP-minus-LP correction of Eq. 4 sees one fixed LP map.
 
@@ -77,7 +77,12 @@ static int default_block(const tsm_solve_params* p) {
 // 2 / 4): FP16 even-odd 12^3 x 24 x 4 sources 428 / 442 / 618 us, x 16 855 /
 // 813 / 982, 24^3 x 48 x 16 10.3 / 9.1 / 9.7 ms; with FP32 links in the
 // half-hops (FP32, BF16) 16^3 x 32 x 16 3.3 / 3.8 / 4.6 ms, 24^3 x 48 x 16
-// 16.3 / 15.6 / 18.7 ms.  Four is never the fastest.
+// 16.3 / 15.6 / 18.7 ms.  Four is never the fastest.  On the whole lattice (12
+// steps without marching) 16-bit storage crosses at about 2e6, where the line
+// costs little: FP16 12^3 x 24 x 16 1398 / 1463 / 1614 us, 16^3 x 32 x 4 1223 /
+// 1236 / 1280, x 16 3565 / 3539 / 3768, 24^3 x 48 x 16 19.1 / 18.3 / 18.9 ms,
+// BF16 within 2 % of these; FP32 16^3 x 32 x 16 7.12 / 7.23 / 7.95, 24^3 x 48 x 16
+// 36.9 / 35.3 / 36.7 ms.
 static int lane_rhs(const tm_ctx* ctx, const tsm_solve_params* p, int block, int nsrc) {
     if (p->prec == TM_PREC_F64 || (p->stop == TM_STOP_TRUE && !p->reliable)) return 1;
     const int t = ctx->lane_rhs[p->prec];
@@ -87,12 +92,12 @@ static int lane_rhs(const tm_ctx* ctx, const tsm_solve_params* p, int block, int
     return block % 2 == 0 && nsrc > 1 && work >= (wide ? 8e6 : 5e5) ? 2 : 1;
 }
 
-// time slices per lane of the time-marching K1 / K2 (0: lane per site)
 // autotuner candidates (right-hand sides per lane, time slices per lane)
 constexpr int kTuneCandidates = 8;
 constexpr int kTuneNr[kTuneCandidates] = {1, 2, 4, 1, 1, 1, 2, 2};
 constexpr int kTuneTseg[kTuneCandidates] = {0, 0, 0, 4, 8, 16, 4, 8};
 
+// time slices per lane of the time-marching K1 / K2 (0: lane per site)
 static int march_tseg(const tm_ctx* ctx, const tsm_solve_params* p, int nr) {
     const int t = ctx->march[p->prec];
     if (t <= 0 || nr > 2) return 0;
@@ -292,7 +297,6 @@ tm_status solve_f64_history(tm_ctx* ctx, uint64_t seed_mixed, const uint64_t* id
     const Geom& g = ctx->geo;
     hipStream_t st = ctx->stream;
     tm_status s = TM_OK;
-    const size_t nblk = (size_t)((g.V + 255) / 256);
     const size_t fb = field_bytes(g, P_F64, 1);
     CgArgs a;
     std::memset(&a, 0, sizeof(a));
@@ -390,8 +394,6 @@ static tm_status solve_block_eo(tm_ctx* ctx, const tsm_solve_params* p, uint64_t
     const bool rel = p->reliable != 0;
     const bool track = p->stop == TM_STOP_TRUE && !rel;
     const int xprec = prec == P_F64 ? P_F64 : P_F32;
-    const size_t nblk_full = (size_t)((g.V + 255) / 256);
-    const uint32_t nblk = (uint32_t)((hg.V + 255) / 256);
     const size_t fbh = field_bytes(hg, prec, nrhs);
     // buffers sized for the tag's capacity (at least nrhs)
     const int nc = ws_rhs(ctx, tag, nrhs);
@@ -809,7 +811,6 @@ static tm_status solve_block(tm_ctx* ctx, const tsm_solve_params* p, uint64_t se
     // the recursively tracked true residual; with reliable updates the FP64
     // true residual is taken at each update instead
     const bool track = p->stop == TM_STOP_TRUE && !rel;
-    const size_t nblk = (size_t)((g.V + 255) / 256);
     // buffers sized for the tag's capacity (at least nrhs)
     const int nc = ws_rhs(ctx, tag, nrhs);
     const size_t fb = field_bytes(g, prec, nc);
