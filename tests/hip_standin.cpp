@@ -9,6 +9,7 @@
 #include <cxxabi.h>
 #include <map>
 #include <mutex>
+#include <set>
 #include <string>
 #include <vector>
 
@@ -21,7 +22,8 @@ std::map<const void*, std::string>& names() {
     static std::map<const void*, std::string> m;
     return m;
 }
-std::vector<std::string> launches;  // "name x y z"
+std::vector<std::string> launches;  // "name x y z"; copies to the host "copy bytes 0 0"
+std::set<const void*> pinned;
 thread_local int current = 0;
 struct Owned {
     int device;
@@ -100,19 +102,37 @@ int hipMalloc(void** p, size_t n) {
     *p = host(n);
     return *p ? 0 : 2;
 }
-int hipHostMalloc(void** p, size_t n, unsigned) { return hipMalloc(p, n); }
+int hipHostMalloc(void** p, size_t n, unsigned) {
+    const int e = hipMalloc(p, n);
+    std::lock_guard<std::mutex> l(mu);
+    pinned.insert(*p);
+    return e;
+}
+int hipPointerGetAttributes(int* type, const void* p) {  // (the type is the first member)
+    std::lock_guard<std::mutex> l(mu);
+    *type = pinned.count(p) ? 1 : 0;
+    return 0;
+}
 int hipFree(void* p) {
     free(p);
     return 0;
 }
-int hipHostFree(void* p) { return hipFree(p); }
+int hipHostFree(void* p) {
+    std::lock_guard<std::mutex> l(mu);
+    pinned.erase(p);
+    return hipFree(p);
+}
 int hipGetSymbolAddress(void** p, const void*) {
     static char scratch[4096];
     *p = scratch;
     return 0;
 }
-int hipMemcpyAsync(void* d, const void* s, size_t n, int, void*) {
+int hipMemcpyAsync(void* d, const void* s, size_t n, int kind, void*) {
     memcpy(d, s, n);
+    if (kind == 2) {
+        std::lock_guard<std::mutex> l(mu);
+        launches.push_back("copy " + std::to_string(n) + " 0 0");
+    }
     return 0;
 }
 int hipMemsetAsync(void* d, int v, size_t n, void*) {

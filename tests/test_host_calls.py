@@ -125,3 +125,29 @@ tq.binding_tuning.tm_autotune_eo(c, tq.PREC_BF16, 8)
 assert sum("k_scal_init" in k for k, _ in s.launches()) == 4 * 6
 c.close()
 """)
+
+
+def test_pinned_results_take_one_copy(tmp_path):
+    """A result of 4 MiB into pinned memory is one copy, into pageable memory
+    pieces through the pinned slots."""
+    run(tmp_path, """
+import ctypes
+import numpy as np
+tq = s.tq
+dims = (8, 8, 8, 32)
+c = s.context(dims, tq.tm_workspace_bytes(dims, caps_=tq.caps([], max_sources=1, all_mom_sources=1)))
+sol = np.zeros(c.V * 24)
+ids = np.zeros(1, dtype=np.uint64)
+pinned = ctypes.c_void_p()
+assert s.hip.hipHostMalloc(ctypes.byref(pinned), ctypes.c_size_t(4 << 20), 0) == 0
+page = np.ones(16 * c.V, dtype=np.complex128)
+for out, pieces in ((pinned, [4 << 20]), (page.ctypes.data_as(ctypes.c_void_p), [512 << 10] * 8)):
+    s.launches()
+    rc = s.lib.tsm_contract(c.h, 31, 1, ids.ctypes.data_as(ctypes.c_void_p), sol.ctypes.data_as(ctypes.c_void_p),
+                            tq.binding.ALL_MOMENTA, None, out)
+    assert rc == 0, s.lib.tm_last_error(c.h)
+    got = [g[0] for k, g in s.launches() if k == "copy"]
+    assert got == pieces, got
+assert not page.any()
+c.close()
+""")
