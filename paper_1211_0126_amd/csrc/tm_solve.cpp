@@ -830,17 +830,28 @@ static tm_status solve_block(tm_ctx* ctx, const tsm_solve_params* p, uint64_t se
     if (quad) nr = 1;
     a.npart = a.tseg > 0 ? march_partials(g, a.tseg) : (uint32_t)((g.V + 63) / 64);
     const size_t npart_max = partials_per_rhs(g, ctx->hgeo, ctx->eo_ok);
-    // directions in a ring, as in solve_block_eo; the source is read by the CG
+    // Directions in a ring, as in solve_block_eo; the source is read by the CG
     // start only and takes the slot of the last direction (two such blocks without
-    // the ring are then as large as one with it)
-    const bool ringm = !rel && half_storage(prec) && rings;
+    // the ring are then as large as one with it).  Small launches update x all the
+    // same: a pass over the directions is a launch and a chunk of steps ends with
+    // it, which costs more than the traffic of x up to about 4e5 sites times
+    // sources (4e4 to 1e5 where the launches march).  LP solves in FP16, x updated
+    // / directions kept: 8^3 x 16 x 4 sources 338 / 510 us, 12^3 x 24 x 4 697 / 744,
+    // x 8 1193 / 1200, 16^3 x 32 x 4 1804 / 1738, x 16 5810 / 5162; marching 8^3 x
+    // 16 x 4 1801 / 1942, x 16 2124 / 2046.  (A block's buffers are the same either
+    // way, so that a call's last, smaller one fits where the others do.)
+    const bool room = !rel && half_storage(prec) && rings;
+    const bool ringm = room && (double)g.V * nrhs >= (a.tseg > 0 ? 1e5 : 4e5);
     const int kRing = kEoRing;
     void* dirs = nullptr;
-    if (ringm) {
+    if (room) {
         dirs = ws_get(ctx, tag + "_dirs", fb * kRing, &s);
-        a.ahist = (double*)ws_get(ctx, tag + "_ahist", sizeof(double) * kMaxBlock * kRing, &s);
-        a.ring = kRing;
+        double* ahist = (double*)ws_get(ctx, tag + "_ahist", sizeof(double) * kMaxBlock * kRing, &s);
         a.p = dirs;
+        if (ringm) {
+            a.ahist = ahist;
+            a.ring = kRing;
+        }
     } else {
         a.p = ws_get(ctx, tag + "_p", fb, &s);
     }
@@ -863,7 +874,7 @@ static tm_status solve_block(tm_ctx* ctx, const tsm_solve_params* p, uint64_t se
         x64 = ws_get(ctx, tag + "_x64", f64, &s);
         t64 = ws_get(ctx, tag + "_t64", f64, &s);
     } else {
-        eta = ringm ? slot(kRing - 1) : ws_get(ctx, tag + "_eta", fb, &s);
+        eta = room ? slot(kRing - 1) : ws_get(ctx, tag + "_eta", fb, &s);
     }
     if (s != TM_OK) return s;
     if ((s = ensure_scal_host(ctx, nrhs)) != TM_OK) return s;

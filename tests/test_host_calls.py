@@ -8,6 +8,7 @@ from standin import run
 SOLVES = """
 tq = s.tq
 dims = (8, 8, 8, 8)
+large = (16, 16, 16, 8)  # where 16 sources keep their directions on the whole lattice
 lp = tq.solve_params(prec=tq.PREC_F16, tol=1e-2, rhs_block=16, solver=tq.SOLVER_CG_EO, true_resid=0)
 hp = tq.solve_params(prec=tq.PREC_F16, tol=1e-10, rhs_block=8, solver=tq.SOLVER_CG_EO, reliable=1, delta=3e-3)
 whole = tq.solve_params(prec=tq.PREC_F16, tol=1e-2, rhs_block=16, solver=tq.SOLVER_CG, true_resid=0)
@@ -26,10 +27,10 @@ def test_a_call_without_room_for_directions_does_its_work_once(tmp_path):
     each block of sources is prepared and solved once, in the first call and in
     the second, and without the room x is updated in every iteration."""
     run(tmp_path, SOLVES + """
-calls = [(lambda c: tq.tsm_loops(c, 7, 8, 24, lp, hp, [[0, 0, 0]]), 4, "k_ring_rel_flush"),
-         (lambda c: tq.tsm_solve_batch(c, hp, 7, list(range(8)), want_solutions=False), 1, "k_ring_rel_flush"),
-         (lambda c: tq.tsm_solve_batch(c, whole, 7, list(range(16)), want_solutions=False), 1, "k_eo_xflush")]
-for call, blocks, kept in calls:
+calls = [(lambda c: tq.tsm_loops(c, 7, 8, 24, lp, hp, [[0, 0, 0]]), 4, "k_ring_rel_flush", dims),
+         (lambda c: tq.tsm_solve_batch(c, hp, 7, list(range(8)), want_solutions=False), 1, "k_ring_rel_flush", dims),
+         (lambda c: tq.tsm_solve_batch(c, whole, 7, list(range(16)), want_solutions=False), 1, "k_eo_xflush", large)]
+for call, blocks, kept, dims in calls:
     size = 1 << 30
     for room in (True, True, False):
         c = s.context(dims, size)
@@ -56,7 +57,7 @@ for d in ((4, 4, 4, 4), dims, (32, 32, 32, 64)):
         wide.prec = tq.PREC_F32
         a, b = (tq.tm_workspace_bytes(d, caps_=tq.caps([q], max_sources=32, max_mom=1)) for q in (p, wide))
         assert a < b, (d, a, b)
-for d in (dims, (8, 16, 12, 4)):
+for d in (large, (16, 16, 12, 12)):
     for call, solves, kept in [
             (lambda c: tq.tsm_loops(c, 7, 8, 24, lp, hp, [[0, 0, 0]]), [lp, hp], "k_ring_rel_flush"),
             (lambda c: tq.tsm_loops(c, 7, 8, 24, whole, hp, [[0, 0, 0]]), [whole, hp], "k_ring_rel_flush"),
@@ -149,5 +150,20 @@ for out, pieces in ((pinned, [4 << 20]), (page.ctypes.data_as(ctypes.c_void_p), 
     got = [g[0] for k, g in s.launches() if k == "copy"]
     assert got == pieces, got
 assert not page.any()
+c.close()
+""")
+
+
+def test_small_whole_lattice_solves_update_x(tmp_path):
+    """16-bit solves on the whole lattice keep their directions from 4e5 sites
+    times sources on (marching from 1e5), block by block, with one workspace."""
+    run(tmp_path, SOLVES + """
+size = tq.tm_workspace_bytes(large, caps_=tq.caps([whole], max_sources=32, max_mom=1))
+c = s.context(large, size)
+for n, march, kept in ((16, 0, 1), (12, 0, 0), (17, 0, 1), (4, 8, 1), (3, 8, 0)):
+    tq.tm_set_march(c, tq.PREC_F16, march)
+    tq.tm_set_lane_rhs(c, tq.PREC_F16, 1 if march else 0)
+    tq.tsm_solve_batch(c, whole, 7, list(range(n)), want_solutions=False)
+    assert len(named(s.launches(), "k_eo_xflush")) == kept, (n, march)
 c.close()
 """)
