@@ -505,7 +505,8 @@ tm_status tm_set_lane_rhs(tm_ctx* ctx, int32_t prec, int32_t nr);
    gives one lane per lattice site; tseg > 0 makes each lane walk tseg time
    slices of one spatial site (time-direction hops carried between slices,
    so the time neighbours are loaded once), used with 1 or 2 right-hand
-   sides per lane.  Values above the time extent act as the time extent.
+   sides per lane (where no width is set, in blocks whose sources are not a
+   multiple of 4).  Values above the time extent act as the time extent.
    Results agree with the one-lane-per-site kernels up to rounding (the
    terms of a site are summed in another order).  TM_EINVAL for prec
    outside 0..3 or tseg outside 0..65535. */

@@ -167,3 +167,22 @@ for n, march, kept in ((16, 0, 1), (12, 0, 0), (17, 0, 1), (4, 8, 1), (3, 8, 0))
     assert len(named(s.launches(), "k_eo_xflush")) == kept, (n, march)
 c.close()
 """)
+
+
+def test_marching_needs_a_lane_width(tmp_path):
+    """A set marching length is used with a set width of 1 or 2, or where the
+    block is no multiple of four sources (and in FP64, which has one per lane);
+    a block of 16 without a width runs a lane per site."""
+    run(tmp_path, """
+tq = s.tq
+c = s.context((8, 8, 8, 16), 1 << 30)
+for prec in (tq.PREC_F64, tq.PREC_F32, tq.PREC_F16):
+    tq.tm_set_march(c, prec, 8)
+    for nr, block, marches in ((0, 16, prec == tq.PREC_F64), (0, 6, True), (0, 5, True), (1, 16, True), (2, 16, True),
+                               (4, 16, prec == tq.PREC_F64)):
+        tq.tm_set_lane_rhs(c, prec, nr)
+        p = tq.solve_params(prec=prec, tol=1e-2, rhs_block=block, true_resid=0)
+        tq.tsm_solve_batch(c, p, 7, list(range(2)), want_solutions=False)
+        assert any("k_tm_mp" in k for k, _ in s.launches()) == marches, (prec, nr, block)
+c.close()
+""")
