@@ -143,14 +143,29 @@ __global__ TM_STENCIL_R(NR, R) void k_cg_mp(CgArgs a) {
     }
 }
 
-// Block partials of one right-hand side in a fixed order (the stencil
-// launch that wrote them has completed); valid in thread 0.  Blocks of kSumBlock
-// threads, eight loads in flight per thread: a chip-filling stencil leaves one
-// partial per 64 sites (5184 at 24^3 x 48: 12 us with 256 threads and one load
-// at a time, 6 us so).
+// Partials of one right-hand side in a fixed order (the stencil launch that
+// wrote them has completed), one array or two (p2 not null); valid in thread 0.
+// Up to kOrderParts the order is that of wave_partials: the first wave sums p and
+// the second p2, with all their loads in flight (16^3 x 32, one source, 2048
+// partials of two arrays: an FP32 solve that tracks the true residual 1293 -> 1148
+// us against one array after the other, eight loads at a time).
+// Beyond, blocks of kSumBlock threads with eight loads in flight each: a
+// chip-filling stencil leaves one partial per 64 sites (5184 at 24^3 x 48: 12 us
+// with 256 threads and one load at a time, 6 us so).
 constexpr int kSumBlock = 1024;
-__device__ __forceinline__ double sum_block_partials(const double* p, uint32_t n, double* sh /*[kSumBlock / 64]*/) {
-    if (n <= kOrderParts) return wave_partials(p, n);
+constexpr int kSumShared = kSumBlock / 64;
+__device__ __forceinline__ double wave_partials_wide(const double* p, uint32_t n) {
+    if (n <= 512) return wave_partials(p, n);
+    constexpr uint32_t N = kOrderParts / 64;
+    double x[N], v = 0;
+    const uint32_t l = threadIdx.x & 63u;
+#pragma unroll
+    for (uint32_t j = 0; j < N; j++) x[j] = p[min(l + 64 * j, n - 1)];
+#pragma unroll
+    for (uint32_t j = 0; j < N; j++) v += l + 64 * j < n ? x[j] : 0.0;
+    return wave_sum(v);
+}
+__device__ __forceinline__ double sum_block_partials(const double* p, uint32_t n, double* sh) {
     double v = 0;
     for (uint32_t i = threadIdx.x; i < n; i += 8 * kSumBlock) {
         double x[8];
@@ -164,17 +179,34 @@ __device__ __forceinline__ double sum_block_partials(const double* p, uint32_t n
     __syncthreads();
     double r = 0;
     if (threadIdx.x == 0)
-        for (int w = 0; w < kSumBlock / 64; w++) r += sh[w];
+        for (int w = 0; w < kSumShared; w++) r += sh[w];
     __syncthreads();
     return r;
+}
+__device__ __forceinline__ void sum_partials(const double* p, const double* p2, uint32_t n, double* sh, double& s1,
+                                             double& s2) {
+    if (n <= kOrderParts) {
+        const uint32_t w = threadIdx.x >> 6;
+        if (w == 0 || (w == 1 && p2)) {
+            const double v = wave_partials_wide(w ? p2 : p, n);
+            if ((threadIdx.x & 63u) == 0) sh[w] = v;
+        }
+        __syncthreads();
+        s1 = sh[0];
+        s2 = p2 ? sh[1] : 0.0;
+    } else {
+        s1 = sum_block_partials(p, n, sh);
+        s2 = p2 ? sum_block_partials(p2, n, sh) : 0.0;
+    }
 }
 
 // after K1, one block per right-hand side: alpha = |r|^2 / |t|^2
 __global__ __launch_bounds__(kSumBlock) void k_cg_alpha(CgArgs a, uint32_t nb) {
-    __shared__ double sh[kSumBlock / 64];
+    __shared__ double sh[kSumShared];
     const int r = blockIdx.x;
     if (!a.scal[r].active) return;
-    const double tt = sum_block_partials(a.partials + (size_t)r * nb, nb, sh);
+    double tt, none;
+    sum_partials(a.partials + (size_t)r * nb, nullptr, nb, sh, tt, none);
     if (threadIdx.x == 0) {
         CgScal& q = a.scal[r];
         q.tt = tt;
@@ -187,11 +219,11 @@ __global__ __launch_bounds__(kSumBlock) void k_cg_alpha(CgArgs a, uint32_t nb) {
 // stop test
 template <bool TRACK>
 __global__ __launch_bounds__(kSumBlock) void k_cg_beta(CgArgs a, uint32_t nb) {
-    __shared__ double sh[kSumBlock / 64];
+    __shared__ double sh[kSumShared];
     const int r = blockIdx.x;
     if (!a.scal[r].active) return;
-    const double rrn = sum_block_partials(a.partials + (size_t)r * nb, nb, sh);
-    const double rhon = TRACK ? sum_block_partials(a.partials2 + (size_t)r * nb, nb, sh) : 0.0;
+    double rrn, rhon;
+    sum_partials(a.partials + (size_t)r * nb, TRACK ? a.partials2 + (size_t)r * nb : nullptr, nb, sh, rrn, rhon);
     if (threadIdx.x == 0) cg_finish_step(a.scal[r], rrn, rhon);
 }
 
@@ -372,11 +404,11 @@ __device__ inline void cg_start(CgScal& q, double bb, double ee) {
 // one block per right-hand side; with_ee = 0: |eta|^2 = ee_z4 (12 per site
 // of a Z4 source on the whole lattice)
 __global__ __launch_bounds__(kSumBlock) void k_cg_init_fin(CgArgs a, uint32_t nb, int with_ee, double ee_z4) {
-    __shared__ double sh[kSumBlock / 64];
+    __shared__ double sh[kSumShared];
     const int r = blockIdx.x;
-    const double bb = sum_block_partials(a.partials + (size_t)r * nb, nb, sh);
-    const double ee = with_ee ? sum_block_partials(a.partials2 + (size_t)r * nb, nb, sh) : ee_z4;
-    if (threadIdx.x == 0) cg_start(a.scal[r], bb, ee);
+    double bb, ee;
+    sum_partials(a.partials + (size_t)r * nb, with_ee ? a.partials2 + (size_t)r * nb : nullptr, nb, sh, bb, ee);
+    if (threadIdx.x == 0) cg_start(a.scal[r], bb, with_ee ? ee : ee_z4);
 }
 
 // ---------------------------------------------------------------------------
@@ -494,11 +526,11 @@ __global__ TM_STENCIL_R(1, double) void k_rel_resid(CgArgs a, const void* gauge6
 // recursion from the recomputed residual, stop test on it (or on the FP64
 // true residual |eta - M x| when the solve stops on that)
 __global__ __launch_bounds__(kSumBlock) void k_rel_fin(CgArgs a, uint32_t nb) {
-    __shared__ double sh[kSumBlock / 64];
+    __shared__ double sh[kSumShared];
     const int r = blockIdx.x;
     if (!a.scal[r].rflag) return;
-    const double rrn = sum_block_partials(a.partials + (size_t)r * nb, nb, sh);
-    const double rho2 = a.eta64 ? sum_block_partials(a.partials2 + (size_t)r * nb, nb, sh) : 0.0;
+    double rrn, rho2;
+    sum_partials(a.partials + (size_t)r * nb, a.eta64 ? a.partials2 + (size_t)r * nb : nullptr, nb, sh, rrn, rho2);
     if (threadIdx.x == 0) {
         CgScal& q = a.scal[r];
         // rrn is the true |r|^2; the next p = r + beta p in the new scale
@@ -559,10 +591,10 @@ __global__ TM_STENCIL_R(1, double) void k_true_resid(CgArgs a, const void* gauge
 }
 
 __global__ __launch_bounds__(kSumBlock) void k_true_resid_fin(CgArgs a, uint32_t nb) {
-    __shared__ double sh[kSumBlock / 64];
+    __shared__ double sh[kSumShared];
     const int r = blockIdx.x;
-    const double rr = sum_block_partials(a.partials + (size_t)r * nb, nb, sh);
-    const double ee = sum_block_partials(a.partials2 + (size_t)r * nb, nb, sh);
+    double rr, ee;
+    sum_partials(a.partials + (size_t)r * nb, a.partials2 + (size_t)r * nb, nb, sh, rr, ee);
     if (threadIdx.x == 0) a.scal[r].resid_true = sqrt(rr / ee);
 }
 

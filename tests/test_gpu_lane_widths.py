@@ -109,3 +109,19 @@ def test_folded_steps_are_those_of_larger_blocks(prec):
             assert torch.equal(out[n][0][0], out[1][0][0]), (kw, n)
             assert out[n][1][0]["iters"] == out[1][1][0]["iters"], (kw, n)
     ctx.close()
+
+
+@pytest.mark.parametrize("dims", [(4, 4, 4, 4), (16, 16, 16, 12), (16, 16, 16, 32), (16, 16, 16, 34)])
+@pytest.mark.parametrize("solver", [0, 2])
+def test_tracked_residuals_of_every_sum(dims, solver):
+    """The true residual that a solve tracks (two arrays of 4 to 2176 partials:
+    one pass of a wave, several, a block) is the one computed from the solution,
+    to the rounding of five FP64 steps."""
+    import paper_1211_0126_amd as tq
+    ctx, _ = _ctx(dims)
+    p = tq.solve_params(prec=tq.PREC_F64, tol=0.0, max_iter=5, rhs_block=2, solver=solver, stop=tq.STOP_TRUE,
+                        true_resid=1)
+    _, st, _ = tq.tsm_solve_batch(ctx, p, 29, [0, 1], want_solutions=False)
+    ctx.close()
+    for q in st:
+        assert q["iters"] == 5 and abs(q["resid_iterated"] - q["resid_true"]) < 1e-12
