@@ -246,7 +246,7 @@ size_t tm_workspace_bytes(const tm_lattice* lat, const tm_caps* caps);
    enqueues work (16-bit solves keep their directions where the workspace has
    room for them beside the fields, and do without otherwise).  dev_ws NULL: tm_create allocates ws_bytes itself (once;
    tm_destroy releases it).  tm_create zeroes the workspace and allocates a
-   small pinned host buffer (and the first result of 4 MiB or more that goes to
+   small pinned host buffer (and the first result of 6 MiB or more that goes to
    the host a staging buffer of 8 MiB, kept until tm_destroy).  hip_stream is a hipStream_t (NULL: the null
    stream).  TM_EINVAL for dims < 2 or for lattices whose volume, padded to
    the plane stride (an odd multiple of 256), exceeds 7,456,512 sites

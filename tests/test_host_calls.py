@@ -72,13 +72,13 @@ for d in (large, (16, 16, 12, 12)):
 
 
 def test_large_results_with_another_device_current(tmp_path):
-    """A context on device 1 called with device 0 current: a result of 4 MiB
+    """A context on device 1 called with device 0 current: a result of 8 MiB
     reaches the host, and the caller's device is left as it was."""
     run(tmp_path, """
 import ctypes
 import numpy as np
 tq = s.tq
-dims = (8, 8, 8, 32)
+dims = (8, 8, 8, 64)
 c = s.context(dims, tq.tm_workspace_bytes(dims, caps_=tq.caps([], max_sources=1, all_mom_sources=1)), device=1)
 s.hip.hipSetDevice(0)
 sol = np.zeros(c.V * 24)
@@ -87,7 +87,7 @@ ids = np.zeros(1, dtype=np.uint64)
 rc = s.lib.tsm_contract(c.h, 31, 1, ids.ctypes.data_as(ctypes.c_void_p), sol.ctypes.data_as(ctypes.c_void_p),
                         tq.binding.ALL_MOMENTA, None, out.ctypes.data_as(ctypes.c_void_p))
 assert rc == 0, s.lib.tm_last_error(c.h)
-assert out.nbytes == 4 << 20 and not out.any()
+assert out.nbytes == 8 << 20 and not out.any()
 assert s.hip.standin_device() == 0
 c.close()
 """)
@@ -128,29 +128,30 @@ c.close()
 """)
 
 
-def test_pinned_results_take_one_copy(tmp_path):
-    """A result of 4 MiB into pinned memory is one copy, into pageable memory
-    pieces through the pinned slots."""
+def test_pieces_of_large_results(tmp_path):
+    """A result into pinned memory is one copy, as is one below 6 MiB into
+    pageable memory; larger ones go in pieces through the pinned slots."""
     run(tmp_path, """
 import ctypes
 import numpy as np
 tq = s.tq
-dims = (8, 8, 8, 32)
-c = s.context(dims, tq.tm_workspace_bytes(dims, caps_=tq.caps([], max_sources=1, all_mom_sources=1)))
-sol = np.zeros(c.V * 24)
-ids = np.zeros(1, dtype=np.uint64)
-pinned = ctypes.c_void_p()
-assert s.hip.hipHostMalloc(ctypes.byref(pinned), ctypes.c_size_t(4 << 20), 0) == 0
-page = np.ones(16 * c.V, dtype=np.complex128)
-for out, pieces in ((pinned, [4 << 20]), (page.ctypes.data_as(ctypes.c_void_p), [512 << 10] * 8)):
-    s.launches()
-    rc = s.lib.tsm_contract(c.h, 31, 1, ids.ctypes.data_as(ctypes.c_void_p), sol.ctypes.data_as(ctypes.c_void_p),
-                            tq.binding.ALL_MOMENTA, None, out)
-    assert rc == 0, s.lib.tm_last_error(c.h)
-    got = [g[0] for k, g in s.launches() if k == "copy"]
-    assert got == pieces, got
-assert not page.any()
-c.close()
+for lt, pageable in ((32, [4 << 20]), (48, [512 << 10] * 12), (64, [512 << 10] * 16)):
+    dims = (8, 8, 8, lt)
+    c = s.context(dims, tq.tm_workspace_bytes(dims, caps_=tq.caps([], max_sources=1, all_mom_sources=1)))
+    sol = np.zeros(c.V * 24)
+    ids = np.zeros(1, dtype=np.uint64)
+    pinned = ctypes.c_void_p()
+    assert s.hip.hipHostMalloc(ctypes.byref(pinned), ctypes.c_size_t(16 * 16 * c.V), 0) == 0
+    page = np.ones(16 * c.V, dtype=np.complex128)
+    for out, pieces in ((pinned, [page.nbytes]), (page.ctypes.data_as(ctypes.c_void_p), pageable)):
+        s.launches()
+        rc = s.lib.tsm_contract(c.h, 31, 1, ids.ctypes.data_as(ctypes.c_void_p), sol.ctypes.data_as(ctypes.c_void_p),
+                                tq.binding.ALL_MOMENTA, None, out)
+        assert rc == 0, s.lib.tm_last_error(c.h)
+        got = [g[0] for k, g in s.launches() if k == "copy"]
+        assert got == pieces, got
+    assert not page.any()
+    c.close()
 """)
 
 
